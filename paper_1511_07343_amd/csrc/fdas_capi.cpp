@@ -1104,45 +1104,32 @@ fdas_status fdas_dedisperse(const uint8_t *fil_dev, int32_t nchan, int64_t nsamp
         set_error("fdas_dedisperse: bad filterbank, frequency, sampling or DM arguments");
         return FDAS_E_INVAL;
     }
-    // delays d[i][c] = floor(KDM DM_i (f_c^-2 - f_top^-2) / tsamp + 1/2), FP64
-    constexpr double kKdm = 4.148808e3;  // s MHz^2 pc^-1 cm^3
-    std::vector<int32_t> d(size_t(ndm) * size_t(nchan));
-    int64_t dmax = 0;
+    // delays d[i][c] = floor(KDM DM_i (f_c^-2 - f_top^-2) / tsamp + 1/2), FP64;
+    // every operation is monotone, so the largest DM's at the lowest channel
+    // is the largest
+    double top = 0.0;
     for (int32_t i = 0; i < ndm; ++i) {
         if (!(dms[i] >= 0.0) || !std::isfinite(dms[i])) {
             set_error("fdas_dedisperse: DMs must be finite and >= 0");
             return FDAS_E_INVAL;
         }
-        for (int32_t c = 0; c < nchan; ++c) {
-            const double f = f_top - foff * double(c);
-            const double raw = kKdm * dms[i] * (1.0 / (f * f) - 1.0 / (f_top * f_top)) / tsamp;
-            const double v = std::floor(raw + 0.5);
-            if (!(v < double(nsamp)) || v > 2147483647.0) {
-                set_error("fdas_dedisperse: a delay exceeds the filterbank (or 2^31 samples)");
-                return FDAS_E_INVAL;
-            }
-            d[size_t(i) * nchan + c] = int32_t(v);
-            dmax = std::max<int64_t>(dmax, int64_t(v));
-        }
+        top = std::max(top, kDispersion * dms[i]);
     }
-    if (nout > nsamp - dmax) {
+    const double f = f_top - foff * double(nchan - 1);
+    const double dmax = std::floor(top * (1.0 / (f * f) - 1.0 / (f_top * f_top)) / tsamp + 0.5);
+    if (!(dmax < double(nsamp)) || dmax > 2147483647.0) {
+        set_error("fdas_dedisperse: a delay exceeds the filterbank (or 2^31 samples)");
+        return FDAS_E_INVAL;
+    }
+    if (nout > nsamp - int64_t(dmax)) {
         set_error("fdas_dedisperse: nout exceeds nsamp minus the largest delay");
         return FDAS_E_INVAL;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    int32_t *dd = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&dd), d.size() * sizeof(int32_t));
+    hipError_t e = launch_dedisperse(fil_dev, nchan, nsamp, f_top, foff, tsamp, dms, ndm, nout, out_dev, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
-        set_error("fdas_dedisperse: device allocation failed");
-        return FDAS_E_NOMEM;
-    }
-    if ((e = hipMemcpyAsync(dd, d.data(), d.size() * sizeof(int32_t), hipMemcpyHostToDevice, st)) == hipSuccess &&
-        (e = launch_dedisperse(fil_dev, nchan, nsamp, dd, ndm, nout, out_dev, st)) == hipSuccess)
-        e = hipStreamSynchronize(st);
-    const hipError_t ef = hipFree(dd);
-    if (e != hipSuccess || ef != hipSuccess) {
-        set_error(std::string("fdas_dedisperse: ") + hipGetErrorString(e != hipSuccess ? e : ef));
+        set_error(std::string("fdas_dedisperse: ") + hipGetErrorString(e));
         return FDAS_E_DEVICE;
     }
     return FDAS_OK;

@@ -116,11 +116,14 @@ hipError_t launch_finish_candidates(const DevCand *dc, const uint32_t *count, ui
                                     int64_t nb, int cpb, double zmax, double dz, fdas_cand *out, hipStream_t st,
                                     uint32_t out_cap = 0xffffffffu, uint32_t *count_dst = nullptr);
 
-// De-dispersion: out[i][t] = sum_c fil[c][t + delays[i][c]] for t < nout
+// De-dispersion: out[i][t] = sum_c fil[c][t + d[i][c]] for t < nout
 // (channel-major 8-bit filterbank, nchan x nsamp; exact integer sums stored
-// as float32).  Every t + delay must lie below nsamp (the caller checks).
-hipError_t launch_dedisperse(const uint8_t *fil, int nchan, int64_t nsamp, const int32_t *delays, int ndm,
-                             int64_t nout, float *out, hipStream_t st);
+// as float32), d[i][c] = floor(k DM_i (f_c^-2 - f_top^-2) / tsamp + 1/2) with
+// f_c = f_top - c foff and k = kDispersion.  dms: host array.  Every t + d
+// must lie below nsamp (the caller checks).
+constexpr double kDispersion = 4.148808e3;  // s MHz^2 pc^-1 cm^3
+hipError_t launch_dedisperse(const uint8_t *fil, int nchan, int64_t nsamp, double f_top, double foff, double tsamp,
+                             const double *dms, int ndm, int64_t nout, float *out, hipStream_t st);
 
 // Time-domain resampling search: y = x resampled for drift alpha (relative
 // to the mean frequency; linear interpolation, FP64 positions); normalised
