@@ -2,14 +2,18 @@
 // as one real matrix product on the MFMA units with BF16 or FP16 operands and
 // FP32 accumulation, instead of the overlap-save FFT path.
 //
-// Y_z[k] = sum_{q=-h..h} Xhat[k - q] T_z[q] is, with q' = q + h and the real
-// and imaginary parts interleaved along K (c = 2 q' + part),
-//   [Y_re | Y_im] = A B,  A[k][c] = (Re, Im) Xhat[k - q' + h],
-//   B = [[ Re T, Im T], [-Im T, Re T]]   (rows: Re / Im of the input,
-//                                          columns: Re / Im of the output).
-// A is a Toeplitz matrix: row k + 1 is row k shifted by one complex value, so
-// a block of rows needs only a window of the spectrum.  The power |Y|^2 and
-// its screening code go to the same plane layout the FFT path writes.
+// Y_z[k] = sum_{q=-h..h} Xhat[k - q] T_z[q].  At integer offsets the response
+// of Sec. 2 is even in q and A(q, -z) = conj A(-q, z), so with T_z = C + i D
+// (real and imaginary parts of the taps) T_-z = C - i D, and the four real
+// products of a pair of templates +-z,
+//   Ur = Re Xhat * C,  Ui = Im Xhat * C,  Vr = Re Xhat * D,  Vi = Im Xhat * D,
+// give both: Y_z = (Ur - Vi) + i (Ui + Vr), Y_-z = (Ur + Vi) + i (Ui - Vr).
+// That is half the multiplications of one product per template.  With
+// q' = q + h, a product is A B, A[k][q'] = Xhat[k - q' + h] (its real or
+// imaginary part) and B the taps.  A is a Toeplitz matrix: row k + 1 is row k
+// shifted by one value, so a block of rows needs only a window of the
+// spectrum.  The powers |Y|^2 and their screening codes go to the same plane
+// layout the FFT path writes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,27 +30,20 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-// v_mfma_f32_16x16x32_{bf16,f16}: lane l holds A[l % 16][8 (l / 16) + s] and
-// B[8 (l / 16) + s][l % 16] (s < 8) and receives D[4 (l / 16) + r][l % 16]
-// (r < 4).
+// v_mfma_f32_32x32x16_{bf16,f16}: lane l holds A[l % 32][8 (l / 32) + s] and
+// B[8 (l / 32) + s][l % 32] (s < 8) and receives
+// D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32] (r < 16).
 template <bool BF16>
-struct Mfma;
-template <>
-struct Mfma<true> {
-    static __device__ __forceinline__ f32x4 op(uint4 a, uint4 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
-                                                       c, 0, 0, 0);
-    }
-};
-template <>
-struct Mfma<false> {
-    static __device__ __forceinline__ f32x4 op(uint4 a, uint4 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c,
-                                                      0, 0, 0);
-    }
-};
+__device__ __forceinline__ f32x16 mfma(uint4 a, uint4 b, f32x16 c) {
+    if constexpr (BF16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
+                                                      0, 0);
+}
 
 // 16-bit encodings, round to nearest even (the same conversions on host and
 // device).
@@ -57,22 +54,18 @@ __host__ __device__ inline uint16_t to_half_bits(float x) {
 }
 
 constexpr int GM_WAVES = 4;
-constexpr int GM_RT = 8;                         // row tiles of 16 bins per wave
-constexpr int GM_ROWS = GM_WAVES * GM_RT * 16;   // bins per row block
-constexpr int GM_TZ = 16;                        // templates per slice
-constexpr int GM_CT = 2 * GM_TZ / 16;            // column tiles: Re, then Im, of the slice's templates
-constexpr int GM_WIN = 16;                       // A fragments kept per wave (power of two >= GM_RT + 1)
+constexpr int GM_RT = 4;                         // row tiles of 32 bins per wave
+constexpr int GM_ROWS = GM_WAVES * GM_RT * 32;   // bins per row block
+constexpr int GM_PAIRS = 16;                     // template pairs per slice: columns C, then D
+constexpr int GM_WIN = 8;                        // A fragments of each part kept per wave
 constexpr int GM_FRAG = 64;                      // 16-byte fragments per MFMA operand (one per lane)
-constexpr int GM_SLICE_FRAGS = GM_CT * GM_FRAG;  // B fragments of one K step of a slice
-constexpr int GM_WORDS(int nk) { return GM_ROWS + 16 * nk; }  // window words per copy
-// Words from one copy of the window to the next: at least GM_WORDS(nk), and
-// 16 more than a multiple of 64, so that the four lanes of a fragment read
-// that take the four copies start 16 banks apart (with a stride that is a
-// multiple of 64 words they start on the same bank: a 4-way conflict on every
-// A-fragment read).
-constexpr int GM_STRIDE(int nk) { return GM_WORDS(nk) + ((16 - GM_WORDS(nk)) % 64 + 64) % 64; }
-// window words loaded per thread (copies are written from registers)
-constexpr int GM_WLOAD = (GM_WORDS(GM_MAX_KSTEPS) + 3 + 64 * GM_WAVES - 1) / (64 * GM_WAVES);
+constexpr int GM_WORDS(int nk) { return GM_ROWS + 16 * nk; }  // window values (a multiple of 8)
+// Bytes from one copy of the window to the next: 32 more than a multiple of
+// 256, so that the 16 lanes of a fragment read that take eight copies, two
+// neighbouring pieces each, cover 256 consecutive bytes' worth of banks.
+constexpr int GM_STRIDE(int nk) { return (2 * GM_WORDS(nk) - 32 + 255) / 256 * 256 + 32; }
+
+static_assert(GM_WORDS(GM_MAX_KSTEPS) / 8 <= 64 * GM_WAVES, "8 window values per thread");
 
 // Templates scaled by 16 (exactly) so that FP16 keeps the tails of the taps
 // away from its subnormal range; powers are scaled back by 1/256.
@@ -94,20 +87,19 @@ __global__ __launch_bounds__(256) void k_lowp_spectrum(const float2 *__restrict_
     out[g] = uint32_t(to_half_bits<BF16>(x.x)) | (uint32_t(to_half_bits<BF16>(x.y)) << 16);
 }
 
-// One workgroup: the B fragments of one template slice (all K) staged in LDS,
-// then row blocks of GM_ROWS bins, each through a spectrum window in LDS.
-// The LDS holds gemm_lds_bytes(nk): slices of 16 templates keep it small
-// enough for two workgroups per CU up to about 30 K steps, so that the MFMA
-// units of a SIMD have two waves to switch between.
-// Wave w owns rows [128 w, 128 w + 128) of a block (8 row tiles) and all
-// GM_CT column tiles (Re of the slice's templates, 16 per tile, then Im).
+// One workgroup: the B fragments of one slice of 16 template pairs (all K)
+// staged in LDS, then row blocks of GM_ROWS bins, each through a spectrum
+// window in LDS.  Wave w owns rows [128 w, 128 w + 128) of a block (4 row
+// tiles) times 32 columns (C and D of the pairs), once for the real and once
+// for the imaginary part of the spectrum: 8 accumulators, 8 products per K
+// step of 16 for 3 fragment reads.
 //
-// The A fragment of (row tile rt, K step ks) holds window words
-// u = (GM_ROWS - 1 - row) + 16 ks + 4 (l / 16) .. + 3, which depend on ks - rt
-// only: F(d) with d = ks - rt.  A wave keeps F(ks - 15) .. F(ks + 1) in
-// registers and loads one new fragment per K step.  The window is stored in
-// four copies shifted by one word, so that every lane's fragment is a 16-byte
-// aligned LDS read (copy (3 - l % 16) mod 4).
+// The A fragment of (row tile rt, K step ks) holds the 8 window values from
+// u = (GM_ROWS - 1 - row) + 16 ks + 8 (l / 32) on, which depend on ks - 2 rt
+// only: F(d) with d = ks - 2 rt.  A wave keeps F(ks - 6) .. F(ks + 1) of each
+// part in registers and loads one new fragment of each per K step.  The
+// window is stored in eight copies shifted by one value, so that every
+// lane's fragment is a 16-byte aligned LDS read (copy (7 - l) mod 8).
 //
 // The next block's window is loaded into registers before this block's
 // powers are stored, so that the stores drain while the next block runs
@@ -118,118 +110,137 @@ __global__ __launch_bounds__(64 * GM_WAVES, 2) void k_corr_gemm(
     int64_t nrb, int64_t per, float power_scale, float *__restrict__ plane, uint8_t *__restrict__ codes,
     float code_inv) {
     extern __shared__ uint4 gm_lds[];
-    uint4 *__restrict__ bl = gm_lds;  // nk GM_SLICE_FRAGS fragments
-    // then 4 copies of GM_WORDS(nk) words, GM_STRIDE(nk) words apart
-    uint32_t *__restrict__ win = reinterpret_cast<uint32_t *>(gm_lds + nk * GM_SLICE_FRAGS);
+    uint4 *__restrict__ bl = gm_lds;  // nk GM_FRAG fragments
+    // then 8 copies of the real parts' window, 8 of the imaginary parts'
+    char *__restrict__ win = reinterpret_cast<char *>(gm_lds + nk * GM_FRAG);
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int i16 = lane & 15, kg = lane >> 4;
-    const int uw = GM_WORDS(nk);
-    const int ust = GM_STRIDE(nk);
-    const int sig = (3 - i16) & 3;
-    // word of F(0) in copy sig (a multiple of 4; F(d) is 16 d words further)
-    const int fbase = sig * ust + (GM_ROWS - 1 - 128 * wave - i16) + 4 * kg - sig;
+    const int uw = GM_WORDS(nk), ust = GM_STRIDE(nk);
+    const int sig = (7 - lane) & 7;
+    // byte of F(0) of the real parts in copy sig; F(d) is 32 d bytes further
+    const char *__restrict__ fr = win + sig * ust + 2 * (GM_ROWS - 1 - 128 * wave - (lane & 31) + 8 * (lane >> 5) - sig);
+    const char *__restrict__ fi = fr + 8 * ust;
+    auto frag = [](const char *p, int d) { return *reinterpret_cast<const uint4 *>(p + 32 * d); };
 
     // this workgroup's items: (slice, row block) pairs [item0, item1), slice-major
     const int64_t total = int64_t(nsl) * nrb;
     const int64_t item0 = int64_t(blockIdx.x) * per;
     const int64_t item1 = min(total, item0 + per);
     if (item0 >= item1) return;
-    // window words W[u] = xl[P0 - u], u < uw + 3 (zero outside the spectrum),
-    // thread t holding u = t + 256 i
-    uint32_t wreg[GM_WLOAD];
+    // window values W[u] = xl[P0 - u] (zero outside the spectrum), thread t
+    // holding u = 8 t .. 8 t + 14, of which copy s takes W[8 t + s] .. + 7
+    constexpr int NW = 15;
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(xl), short(0), int(4 * nb), 0x00020000);
+    uint32_t wreg[NW];
+    const bool fills = 8 * t < uw;
     auto load_window = [&](int64_t item) {
         const int sl = int(item / nrb);
-        const int64_t p0 = (item - int64_t(sl) * nrb) * GM_ROWS + GM_ROWS - 1 + h;
+        const int p0 = int(item - int64_t(sl) * nrb) * GM_ROWS + GM_ROWS - 1 + h - 8 * t;
+        if (fills) {  // bytes outside the spectrum, before (negative, a large unsigned offset) or past it, read 0
 #pragma unroll
-        for (int i = 0; i < GM_WLOAD; ++i) {
-            const int u = t + 64 * GM_WAVES * i;
-            const int64_t p = p0 - u;
-            wreg[i] = (u < uw + 3 && p >= 0 && p < nb) ? xl[p] : 0u;
+            for (int i = 0; i < NW; ++i) wreg[i] = __builtin_amdgcn_raw_buffer_load_b32(rx, 4 * (p0 - i), 0, 0);
         }
     };
     load_window(item0);
+    const int pairs = (nz + 1) / 2;
     int cur_slice = -1;
     for (int64_t item = item0; item < item1; ++item) {
         const int sl = int(item / nrb);
         const int64_t k0 = (item - int64_t(sl) * nrb) * GM_ROWS;
         __syncthreads();  // the previous item's LDS reads are done
         if (sl != cur_slice) {
-            const uint4 *__restrict__ src = bfrag + int64_t(sl) * nk * GM_SLICE_FRAGS;
-            for (int i = t; i < nk * GM_SLICE_FRAGS; i += 64 * GM_WAVES) bl[i] = src[i];
+            const uint4 *__restrict__ src = bfrag + int64_t(sl) * nk * GM_FRAG;
+            for (int i = t; i < nk * GM_FRAG; i += 64 * GM_WAVES) bl[i] = src[i];
             cur_slice = sl;
         }
-        // copy s holds W[v + s] at v
+        if (fills) {
 #pragma unroll
-        for (int i = 0; i < GM_WLOAD; ++i) {
-            const int u = t + 64 * GM_WAVES * i;
+            for (int part = 0; part < 2; ++part) {
+                uint32_t pr[NW - 1];  // (W[i], W[i + 1]) of this part
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int v = u - c;
-                if (v >= 0 && v < uw) win[c * ust + v] = wreg[i];
+                for (int i = 0; i < NW - 1; ++i)
+                    pr[i] = __builtin_amdgcn_perm(wreg[i + 1], wreg[i], part ? 0x07060302u : 0x05040100u);
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    *reinterpret_cast<uint4 *>(win + (8 * part + c) * ust + 16 * t) =
+                        make_uint4(pr[c], pr[c + 2], pr[c + 4], pr[c + 6]);
             }
         }
         __syncthreads();
 
-        f32x4 acc[GM_RT][GM_CT];
+        f32x16 acc[GM_RT][2];
 #pragma unroll
         for (int rt = 0; rt < GM_RT; ++rt)
 #pragma unroll
-            for (int ct = 0; ct < GM_CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-        uint4 F[GM_WIN];
+            for (int part = 0; part < 2; ++part)
 #pragma unroll
-        for (int d = 1; d < GM_RT; ++d)  // F(-7) .. F(-1)
-            F[(GM_WIN - d) % GM_WIN] = *reinterpret_cast<const uint4 *>(win + fbase - 16 * d);
-        F[0] = *reinterpret_cast<const uint4 *>(win + fbase);
-        uint4 b[GM_CT];
+                for (int r = 0; r < 16; ++r) acc[rt][part][r] = 0.f;
+        uint4 Fr[GM_WIN], Fi[GM_WIN];
 #pragma unroll
-        for (int ct = 0; ct < GM_CT; ++ct) b[ct] = bl[ct * GM_FRAG + lane];
+        for (int d = 0; d <= 2 * (GM_RT - 1); ++d) {  // F(0), F(-1) .. F(-6)
+            Fr[(GM_WIN - d) % GM_WIN] = frag(fr, -d);
+            Fi[(GM_WIN - d) % GM_WIN] = frag(fi, -d);
+        }
+        uint4 b = bl[lane];
         for (int kb = 0; kb < nk; kb += GM_WIN) {
 #pragma unroll
             for (int j = 0; j < GM_WIN; ++j) {
                 const int ks = kb + j;
                 if (ks < nk) {
-                    // prefetch step ks + 1 (F(ks + 1) replaces F(ks - 15), no longer used)
-                    uint4 bn[GM_CT];
+                    // prefetch step ks + 1 (F(ks + 1) replaces F(ks - 7), no longer used)
+                    uint4 bn = b;
                     if (ks + 1 < nk) {
-                        F[(j + 1) % GM_WIN] = *reinterpret_cast<const uint4 *>(win + fbase + 16 * (ks + 1));
-#pragma unroll
-                        for (int ct = 0; ct < GM_CT; ++ct) bn[ct] = bl[((ks + 1) * GM_CT + ct) * GM_FRAG + lane];
+                        Fr[(j + 1) % GM_WIN] = frag(fr, ks + 1);
+                        Fi[(j + 1) % GM_WIN] = frag(fi, ks + 1);
+                        bn = bl[(ks + 1) * GM_FRAG + lane];
                     }
 #pragma unroll
                     for (int rt = 0; rt < GM_RT; ++rt) {
-                        const uint4 a = F[(j - rt + GM_WIN) % GM_WIN];
-#pragma unroll
-                        for (int ct = 0; ct < GM_CT; ++ct) acc[rt][ct] = Mfma<BF16>::op(a, b[ct], acc[rt][ct]);
+                        acc[rt][0] = mfma<BF16>(Fr[(j - 2 * rt + GM_WIN) % GM_WIN], b, acc[rt][0]);
+                        acc[rt][1] = mfma<BF16>(Fi[(j - 2 * rt + GM_WIN) % GM_WIN], b, acc[rt][1]);
                     }
-                    if (ks + 1 < nk) {
-#pragma unroll
-                        for (int ct = 0; ct < GM_CT; ++ct) b[ct] = bn[ct];
-                    }
+                    b = bn;
                 }
             }
         }
         if (item + 1 < item1) load_window(item + 1);
 
-        // powers: column tile c < GM_CT / 2 is Re of templates 16 c + i16, tile
-        // c + GM_CT / 2 their Im; rows 4 (l / 16) + r of each row tile
-#pragma unroll
-        for (int half = 0; half < GM_CT / 2; ++half) {
-            const int z = sl * GM_TZ + 16 * half + i16;
-            if (z >= nz) continue;
-            float *__restrict__ prow = plane + int64_t(z) * nb;
-            uint8_t *__restrict__ qrow = codes + int64_t(z) * (nb / 2);
+        // Powers.  Lanes with l % 32 < 16 hold U of pair l % 16, the others V:
+        // exchanging registers 4 g + i and 4 (g + 1) + i between the odd and
+        // the even rows of 16 lanes leaves both of U and V of 4 consecutive
+        // bins in every lane (of the tile's group g or g + 1 of 8 bins).
+        const int pr = sl * GM_PAIRS + (lane & 15);
+        if (pr < pairs) {
+            const int mirror = nz - 1 - pr;
+            float *__restrict__ prow = plane + int64_t(pr) * nb, *__restrict__ mrow = plane + int64_t(mirror) * nb;
+            uint8_t *__restrict__ pcode = codes + int64_t(pr) * (nb / 2), *__restrict__ mcode = codes + int64_t(mirror) * (nb / 2);
 #pragma unroll
             for (int rt = 0; rt < GM_RT; ++rt) {
-                const int64_t k = k0 + 128 * wave + 16 * rt + 4 * kg;
-                if (k >= nb) continue;
-                const f32x4 re = acc[rt][half], im = acc[rt][half + GM_CT / 2];
-                float4 pw;
-                pw.x = fmaf(re[0], re[0], im[0] * im[0]) * power_scale;
-                pw.y = fmaf(re[1], re[1], im[1] * im[1]) * power_scale;
-                pw.z = fmaf(re[2], re[2], im[2] * im[2]) * power_scale;
-                pw.w = fmaf(re[3], re[3], im[3] * im[3]) * power_scale;
-                *reinterpret_cast<float4 *>(prow + k) = pw;
-                *reinterpret_cast<uint16_t *>(qrow + (k >> 1)) = block_codes4(pw, code_inv);
+#pragma unroll
+                for (int g = 0; g < 4; g += 2) {
+                    float pz[4], pm[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rt][0][4 * g + i]),
+                                                                        __float_as_uint(acc[rt][0][4 * (g + 1) + i]), false, false);
+                        const auto m = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rt][1][4 * g + i]),
+                                                                        __float_as_uint(acc[rt][1][4 * (g + 1) + i]), false, false);
+                        const float ur = __uint_as_float(r[0]), vr = __uint_as_float(r[1]);
+                        const float ui = __uint_as_float(m[0]), vi = __uint_as_float(m[1]);
+                        const float ar = ur - vi, ai = ui + vr, br = ur + vi, bi = ui - vr;
+                        pz[i] = fmaf(ar, ar, ai * ai) * power_scale;
+                        pm[i] = fmaf(br, br, bi * bi) * power_scale;
+                    }
+                    const int64_t k = k0 + 128 * wave + 32 * rt + 8 * (g + ((lane >> 4) & 1)) + 4 * (lane >> 5);
+                    if (k >= nb) continue;
+                    const float4 z4 = make_float4(pz[0], pz[1], pz[2], pz[3]), m4 = make_float4(pm[0], pm[1], pm[2], pm[3]);
+                    *reinterpret_cast<float4 *>(prow + k) = z4;
+                    *reinterpret_cast<uint16_t *>(pcode + (k >> 1)) = block_codes4(z4, code_inv);
+                    if (mirror != pr) {
+                        *reinterpret_cast<float4 *>(mrow + k) = m4;
+                        *reinterpret_cast<uint16_t *>(mcode + (k >> 1)) = block_codes4(m4, code_inv);
+                    }
+                }
             }
         }
     }
@@ -237,36 +248,29 @@ __global__ __launch_bounds__(64 * GM_WAVES, 2) void k_corr_gemm(
 
 }  // namespace
 
-int gemm_ksteps(int h) { return (2 * (2 * h + 1) + 31) / 32; }
+int gemm_ksteps(int h) { return (2 * h + 1 + 15) / 16; }
 
-static size_t gemm_lds_bytes(int nk) { return size_t(nk * GM_SLICE_FRAGS + GM_STRIDE(nk)) * 16; }
+static size_t gemm_lds_bytes(int nk) { return size_t(nk) * GM_FRAG * 16 + 16 * size_t(GM_STRIDE(nk)); }
 
-size_t gemm_bank_bytes(int nz, int h) {
-    return size_t((nz + GM_TZ - 1) / GM_TZ) * size_t(gemm_ksteps(h)) * GM_SLICE_FRAGS * 16;
-}
+static int gemm_slices(int nz) { return ((nz + 1) / 2 + GM_PAIRS - 1) / GM_PAIRS; }
 
+size_t gemm_bank_bytes(int nz, int h) { return size_t(gemm_slices(nz)) * size_t(gemm_ksteps(h)) * GM_FRAG * 16; }
+
+// The taps of templates 0 .. (nz - 1) / 2; the others are their conjugates.
 void build_gemm_bank(const double *taps, int nz, int h, bool bf16, void *out) {
-    const int ntap = 2 * h + 1, nk = gemm_ksteps(h), nsl = (nz + GM_TZ - 1) / GM_TZ;
+    const int ntap = 2 * h + 1, nk = gemm_ksteps(h), nsl = gemm_slices(nz), pairs = (nz + 1) / 2;
     uint16_t *o = static_cast<uint16_t *>(out);
     size_t idx = 0;
     for (int sl = 0; sl < nsl; ++sl)
         for (int ks = 0; ks < nk; ++ks)
-            for (int ct = 0; ct < GM_CT; ++ct)
-                for (int l = 0; l < 64; ++l)
-                    for (int s = 0; s < 8; ++s, ++idx) {
-                        const int c = 32 * ks + 8 * (l / 16) + s;  // K index
-                        const int col = 16 * ct + (l % 16);        // output column of the slice
-                        const int qp = c / 2, part_in = c % 2;
-                        const int z = sl * GM_TZ + (col % GM_TZ), part_out = col / GM_TZ;
-                        double v = 0.0;
-                        if (qp < ntap && z < nz) {
-                            const double tr = taps[2 * (size_t(z) * ntap + qp)];
-                            const double ti = taps[2 * (size_t(z) * ntap + qp) + 1];
-                            v = part_in == 0 ? (part_out == 0 ? tr : ti) : (part_out == 0 ? -ti : tr);
-                        }
-                        const float f = float(v * GM_TAP_SCALE);
-                        o[idx] = bf16 ? to_half_bits<true>(f) : to_half_bits<false>(f);
-                    }
+            for (int l = 0; l < 64; ++l)
+                for (int s = 0; s < 8; ++s, ++idx) {
+                    const int qp = 16 * ks + 8 * (l / 32) + s;
+                    const int col = l % 32, z = sl * GM_PAIRS + col % GM_PAIRS, part = col / GM_PAIRS;
+                    const double v = qp < ntap && z < pairs ? taps[2 * (size_t(z) * ntap + qp) + part] : 0.0;
+                    const float f = float(v * GM_TAP_SCALE);
+                    o[idx] = bf16 ? to_half_bits<true>(f) : to_half_bits<false>(f);
+                }
 }
 
 hipError_t launch_lowp_spectrum(const float2 *X, const double *med, int W, int64_t nb, bool bf16, uint32_t *out,
@@ -282,7 +286,7 @@ hipError_t launch_corr_gemm(const uint32_t *xl, int64_t nb, int h, const void *b
                             int workgroups, float *plane, uint8_t *codes, float code_inv, hipStream_t st) {
     const int nk = gemm_ksteps(h);
     if (nk > GM_MAX_KSTEPS || nb % 4 != 0 || workgroups <= 0) return hipErrorInvalidValue;
-    const int nsl = (nz + GM_TZ - 1) / GM_TZ;
+    const int nsl = gemm_slices(nz);
     const int64_t nrb = (nb + GM_ROWS - 1) / GM_ROWS;
     const size_t lds = gemm_lds_bytes(nk);
     // workgroups per CU that fit beside each other (the LDS decides)

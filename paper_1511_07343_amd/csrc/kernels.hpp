@@ -59,13 +59,14 @@ hipError_t launch_correlate(const float2 *segspec, const float2 *bank, const flo
                             hipStream_t st);
 
 // Matrix-core correlator (BF16 or FP16 operands, FP32 accumulation).
-// gemm_ksteps(h): K steps of 32 (real K = 2 (2h + 1), zero padded); at most
-// GM_MAX_KSTEPS (the template slice must fit the workgroup's LDS).
+// gemm_ksteps(h): K steps of 16 taps (2h + 1, zero padded); at most
+// GM_MAX_KSTEPS (a slice of templates must fit the workgroup's LDS).
 constexpr int GM_MAX_KSTEPS = 34;
 int gemm_ksteps(int h);
-// Template matrix in MFMA fragment order: gemm_bank_bytes(nz, h) bytes,
-// built on the host from the FP64 taps (nz x (2h + 1) complex, tap q at
-// column q + h).
+// Taps in MFMA fragment order: gemm_bank_bytes(nz, h) bytes, built on the host
+// from the FP64 taps (nz x (2h + 1) complex, tap q at column q + h) of the
+// first half of the templates: those of -z are the conjugates of those of z,
+// rows iz and nz - 1 - iz of every bank.
 size_t gemm_bank_bytes(int nz, int h);
 void build_gemm_bank(const double *taps, int nz, int h, bool bf16, void *out);
 // Xhat = X sqrt(ln2 / m(k)) (or X when med is NULL) as 16-bit (Re, Im) pairs.
