@@ -30,25 +30,27 @@ __device__ __forceinline__ double median_curve(const double *__restrict__ med, i
     return med[b] + (med[b + 1] - med[b]) * f;
 }
 
-// Screening code of a power: min(255, ceil(P / delta)) with code_inv = 1 / delta,
-// never below P / delta (up to one rounding of the product), so integer sums of
-// codes bound power sums from above; NaN and huge powers saturate at 255.
-__device__ __forceinline__ uint8_t power_code(float pw, float code_inv) {
-    return uint8_t(fminf(ceilf(pw * code_inv), 255.f));
+// Screening code of a power: floor(P / delta) + 1, at most 255, with
+// code_inv = 1 / delta: above P / delta (a fused multiply-add rounds
+// monotonically, so also after its rounding; a conversion that rounded to
+// nearest would bound it too), so integer sums of codes bound power sums from
+// above; NaN and huge powers saturate at 255 (the minimum drops a NaN).
+// Inserted as byte `b` of w: three instructions a code.
+__device__ __forceinline__ uint32_t put_code(float pw, float code_inv, int b, uint32_t w) {
+    return __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaf(pw, code_inv, 1.f), 255.f), uint32_t(b), w);
 }
 
-// Code of a 2-bin block: the larger of its bins' codes, 255 if either is NaN.
-// Powers are non-negative (or NaN), and non-negative floats, with NaN above
-// +inf, order as their unsigned bit patterns, so one integer maximum picks
-// the larger power and keeps a NaN (fmaxf alone would drop it).
-__device__ __forceinline__ uint8_t block_code(float a, float b, float code_inv) {
-    const float m = __uint_as_float(max(__float_as_uint(a), __float_as_uint(b)));
-    return uint8_t(fminf(ceilf(m * code_inv), 255.f));
+// The larger power of a 2-bin block, a NaN if either is one: powers are
+// non-negative (or NaN), and non-negative floats, with NaN above +inf, order
+// as their unsigned bit patterns, so one integer maximum picks the larger
+// power and keeps a NaN (fmaxf alone would drop it).
+__device__ __forceinline__ float block_power(float a, float b) {
+    return __uint_as_float(max(__float_as_uint(a), __float_as_uint(b)));
 }
 
 // The codes of the two 2-bin blocks of 4 consecutive bins, as 2 bytes.
 __device__ __forceinline__ uint16_t block_codes4(float4 p, float code_inv) {
-    return uint16_t(block_code(p.x, p.y, code_inv)) | uint16_t(uint16_t(block_code(p.z, p.w, code_inv)) << 8);
+    return uint16_t(put_code(block_power(p.z, p.w), code_inv, 1, put_code(block_power(p.x, p.y), code_inv, 0, 0u)));
 }
 
 // Single-trial significance in FP64: log Q(n, s) of a sum of n unit-mean

@@ -67,9 +67,10 @@ constexpr int GM_STRIDE(int nk) { return (2 * GM_WORDS(nk) - 32 + 255) / 256 * 2
 
 static_assert(GM_WORDS(GM_MAX_KSTEPS) / 8 <= 64 * GM_WAVES, "8 window values per thread");
 
-// Templates scaled by 16 (exactly) so that FP16 keeps the tails of the taps
-// away from its subnormal range; powers are scaled back by 1/256.
-constexpr double GM_TAP_SCALE = 16.0;
+// FP16 taps are scaled by 16 (exactly), which keeps the tails of the templates
+// away from its subnormal range, and their powers back by 1/256.  BF16 has the
+// range of FP32 and needs neither.
+constexpr double gm_tap_scale(bool bf16) { return bf16 ? 1.0 : 16.0; }
 
 // Word k = (Re, Im) of Xhat[k] as two 16-bit floats, Re in the low half.
 template <bool BF16>
@@ -85,6 +86,26 @@ __global__ __launch_bounds__(256) void k_lowp_spectrum(const float2 *__restrict_
         x = make_float2(x.x * sc, x.y * sc);
     }
     out[g] = uint32_t(to_half_bits<BF16>(x.x)) | (uint32_t(to_half_bits<BF16>(x.y)) << 16);
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_nt(float *p, const float (&v)[4]) {
+    __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4 *>(p));
+}
+
+// Codes of 128 bins of one template, spread over the four lanes l % 16 + 16 j:
+// lane j' = 2 ((l / 16) % 2) + l / 32 holds the two codes of bins
+// 32 rt + 8 g + 4 j' .. + 3 of tile rt in the low (g = 0) and the high (g = 2)
+// half of w[rt].  On return, the 16 codes of tile j' in bin order.
+__device__ __forceinline__ uint4 gather_codes(const uint32_t (&w)[GM_RT]) {
+    static_assert(GM_RT == 4, "a tile per lane");
+    const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[1], false, false);  // a[e]: from lanes l / 32 = e,
+    const auto b = __builtin_amdgcn_permlane32_swap(w[2], w[3], false, false);  // tile l / 32 (b: + 2)
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);  // c[hi]: from (l / 16) % 2 = hi, e = 0
+    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);  // ... e = 1
+    constexpr uint32_t lo = 0x05040100u, hi = 0x07060302u;  // the low (high) halves of two words
+    return make_uint4(__builtin_amdgcn_perm(d[0], c[0], lo), __builtin_amdgcn_perm(d[1], c[1], lo),
+                      __builtin_amdgcn_perm(d[0], c[0], hi), __builtin_amdgcn_perm(d[1], c[1], hi));
 }
 
 // One workgroup: the B fragments of one slice of 16 template pairs (all K)
@@ -107,7 +128,7 @@ __global__ __launch_bounds__(256) void k_lowp_spectrum(const float2 *__restrict_
 template <bool BF16>
 __global__ __launch_bounds__(64 * GM_WAVES, 2) void k_corr_gemm(
     const uint32_t *__restrict__ xl, int64_t nb, int h, int nk, const uint4 *__restrict__ bfrag, int nz, int nsl,
-    int64_t nrb, int64_t per, float power_scale, float *__restrict__ plane, uint8_t *__restrict__ codes,
+    int64_t nrb, int64_t per, float *__restrict__ plane, uint8_t *__restrict__ codes,
     float code_inv) {
     extern __shared__ uint4 gm_lds[];
     uint4 *__restrict__ bl = gm_lds;  // nk GM_FRAG fragments
@@ -212,8 +233,9 @@ __global__ __launch_bounds__(64 * GM_WAVES, 2) void k_corr_gemm(
         const int pr = sl * GM_PAIRS + (lane & 15);
         if (pr < pairs) {
             const int mirror = nz - 1 - pr;
-            float *__restrict__ prow = plane + int64_t(pr) * nb, *__restrict__ mrow = plane + int64_t(mirror) * nb;
-            uint8_t *__restrict__ pcode = codes + int64_t(pr) * (nb / 2), *__restrict__ mcode = codes + int64_t(mirror) * (nb / 2);
+            const int64_t kw = k0 + 128 * wave;
+            float *__restrict__ prow = plane + int64_t(pr) * nb + kw, *__restrict__ mrow = plane + int64_t(mirror) * nb + kw;
+            uint32_t pc[GM_RT], mc[GM_RT];  // codes of each tile: group g = 0 low, 2 high
 #pragma unroll
             for (int rt = 0; rt < GM_RT; ++rt) {
 #pragma unroll
@@ -221,27 +243,34 @@ __global__ __launch_bounds__(64 * GM_WAVES, 2) void k_corr_gemm(
                     float pz[4], pm[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rt][0][4 * g + i]),
-                                                                        __float_as_uint(acc[rt][0][4 * (g + 1) + i]), false, false);
-                        const auto m = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[rt][1][4 * g + i]),
-                                                                        __float_as_uint(acc[rt][1][4 * (g + 1) + i]), false, false);
+                        const auto r = __builtin_amdgcn_permlane16_swap(
+                            __float_as_uint(acc[rt][0][4 * g + i]), __float_as_uint(acc[rt][0][4 * (g + 1) + i]), false, false);
+                        const auto m = __builtin_amdgcn_permlane16_swap(
+                            __float_as_uint(acc[rt][1][4 * g + i]), __float_as_uint(acc[rt][1][4 * (g + 1) + i]), false, false);
                         const float ur = __uint_as_float(r[0]), vr = __uint_as_float(r[1]);
                         const float ui = __uint_as_float(m[0]), vi = __uint_as_float(m[1]);
                         const float ar = ur - vi, ai = ui + vr, br = ur + vi, bi = ui - vr;
-                        pz[i] = fmaf(ar, ar, ai * ai) * power_scale;
-                        pm[i] = fmaf(br, br, bi * bi) * power_scale;
+                        pz[i] = fmaf(ar, ar, ai * ai);
+                        pm[i] = fmaf(br, br, bi * bi);
+                        if constexpr (!BF16) {
+                            constexpr float scale = float(1.0 / (gm_tap_scale(false) * gm_tap_scale(false)));
+                            pz[i] *= scale;
+                            pm[i] *= scale;
+                        }
                     }
-                    const int64_t k = k0 + 128 * wave + 32 * rt + 8 * (g + ((lane >> 4) & 1)) + 4 * (lane >> 5);
-                    if (k >= nb) continue;
-                    const float4 z4 = make_float4(pz[0], pz[1], pz[2], pz[3]), m4 = make_float4(pm[0], pm[1], pm[2], pm[3]);
-                    *reinterpret_cast<float4 *>(prow + k) = z4;
-                    *reinterpret_cast<uint16_t *>(pcode + (k >> 1)) = block_codes4(z4, code_inv);
-                    if (mirror != pr) {
-                        *reinterpret_cast<float4 *>(mrow + k) = m4;
-                        *reinterpret_cast<uint16_t *>(mcode + (k >> 1)) = block_codes4(m4, code_inv);
-                    }
+                    const int k = 32 * rt + 8 * (g + ((lane >> 4) & 1)) + 4 * (lane >> 5);
+                    store_nt(prow + k, pz);
+                    if (mirror != pr) store_nt(mrow + k, pm);
+                    const uint32_t cp = block_codes4(make_float4(pz[0], pz[1], pz[2], pz[3]), code_inv);
+                    const uint32_t cm = block_codes4(make_float4(pm[0], pm[1], pm[2], pm[3]), code_inv);
+                    pc[rt] = g == 0 ? cp : pc[rt] | (cp << 16);
+                    mc[rt] = g == 0 ? cm : mc[rt] | (cm << 16);
                 }
             }
+            const int tile = 2 * ((lane >> 4) & 1) + (lane >> 5);  // the tile whose codes this lane stores
+            uint8_t *__restrict__ code0 = codes + kw / 2 + 16 * tile;
+            *reinterpret_cast<uint4 *>(code0 + int64_t(pr) * (nb / 2)) = gather_codes(pc);
+            if (mirror != pr) *reinterpret_cast<uint4 *>(code0 + int64_t(mirror) * (nb / 2)) = gather_codes(mc);
         }
     }
 }
@@ -268,7 +297,7 @@ void build_gemm_bank(const double *taps, int nz, int h, bool bf16, void *out) {
                     const int qp = 16 * ks + 8 * (l / 32) + s;
                     const int col = l % 32, z = sl * GM_PAIRS + col % GM_PAIRS, part = col / GM_PAIRS;
                     const double v = qp < ntap && z < pairs ? taps[2 * (size_t(z) * ntap + qp) + part] : 0.0;
-                    const float f = float(v * GM_TAP_SCALE);
+                    const float f = float(v * gm_tap_scale(bf16));
                     o[idx] = bf16 ? to_half_bits<true>(f) : to_half_bits<false>(f);
                 }
 }
@@ -285,7 +314,7 @@ hipError_t launch_lowp_spectrum(const float2 *X, const double *med, int W, int64
 hipError_t launch_corr_gemm(const uint32_t *xl, int64_t nb, int h, const void *bank, int nz, bool bf16,
                             int workgroups, float *plane, uint8_t *codes, float code_inv, hipStream_t st) {
     const int nk = gemm_ksteps(h);
-    if (nk > GM_MAX_KSTEPS || nb % 4 != 0 || workgroups <= 0) return hipErrorInvalidValue;
+    if (nk > GM_MAX_KSTEPS || nb % GM_ROWS != 0 || nb > (int64_t(1) << 28) || workgroups <= 0) return hipErrorInvalidValue;
     const int nsl = gemm_slices(nz);
     const int64_t nrb = (nb + GM_ROWS - 1) / GM_ROWS;
     const size_t lds = gemm_lds_bytes(nk);
@@ -297,14 +326,13 @@ hipError_t launch_corr_gemm(const uint32_t *xl, int64_t nb, int h, const void *b
     workgroups *= std::max(per_cu, 1);
     const int64_t per = (int64_t(nsl) * nrb + workgroups - 1) / workgroups;
     const int64_t grid = (int64_t(nsl) * nrb + per - 1) / per;
-    const float scale = float(1.0 / (GM_TAP_SCALE * GM_TAP_SCALE));
     const uint4 *bf = static_cast<const uint4 *>(bank);
     if (bf16)
         hipLaunchKernelGGL(k_corr_gemm<true>, dim3(unsigned(grid)), dim3(64 * GM_WAVES), lds, st, xl, nb, h, nk, bf, nz,
-                           nsl, nrb, per, scale, plane, codes, code_inv);
+                           nsl, nrb, per, plane, codes, code_inv);
     else
         hipLaunchKernelGGL(k_corr_gemm<false>, dim3(unsigned(grid)), dim3(64 * GM_WAVES), lds, st, xl, nb, h, nk, bf,
-                           nz, nsl, nrb, per, scale, plane, codes, code_inv);
+                           nz, nsl, nrb, per, plane, codes, code_inv);
     return hipGetLastError();
 }
 

@@ -20,17 +20,12 @@ constexpr int fft_threads(int log2s) {
 }
 
 // Threads per workgroup of the fused correlation kernel, and the waves per
-// SIMD its register budget is held to (4096 points on the integer grid fit
-// 128 registers).
+// SIMD its register budget is held to.  Up to 4096 points every form fits 128
+// registers with the segment's spectrum held in them (4096 points: 120, with
+// the half-bin plane 124); at 8192 points 202 of 256, and the 66 KB of LDS
+// allow two workgroups per compute unit anyway.
 constexpr int corr_threads(int log2s) { return fft_threads(log2s); }
-constexpr int corr_waves(int log2s, bool interbin) { return log2s == 12 && !interbin ? 4 : 2; }
-// Whether the fused correlation kernel holds its segment's spectrum in
-// registers across the templates of its block (the persistent kernel's
-// correlation tiles always do): at 8192 points (218 VGPRs,
-// still two waves per SIMD) and 2048 (139 VGPRs, three waves instead of
-// four, yet faster); not at 4096, whose 128-register budget would spill, nor
-// for the half-bin plane, which measured slower.
-constexpr bool corr_hold(int log2s, bool interbin) { return (log2s == 13 || log2s == 11) && !interbin; }
+constexpr int corr_waves(int log2s) { return log2s == 13 ? 2 : 4; }
 
 // 8 XCDs on MI355X; workgroups are dispatched to XCDs round-robin by index.
 constexpr int kXcds = 8;
@@ -424,8 +419,9 @@ __global__ __launch_bounds__(256) void k_normalise(const float2 *__restrict__ X,
 // (same thread, same chunk) reads that word back and keeps the larger code
 // of each pair.
 // Work item (segment s, template block tb): templates [tb tpb, min(nz, (tb + 1) tpb)).
-template <int LOG2S, bool INTERBIN, bool HOLD = false>
-__device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftShape<LOG2S, corr_threads(LOG2S)>, +1> &tw,
+template <int LOG2S, bool INTERBIN>
+__device__ __forceinline__ void correlate_item(float2 *lds,
+                                               const FusedTwiddles<FftShape<LOG2S, corr_threads(LOG2S)>, +1> &tw,
                                                int t, const float2 *__restrict__ segspec,
                                                const float2 *__restrict__ bank, const float2 *__restrict__ bank_half,
                                                int nz, int tpb, int64_t nb, int h, int64_t s, int64_t tb,
@@ -435,10 +431,11 @@ __device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftSh
     const int64_t L = seg_valid(Sh::S, h);
     const int iz0 = int(tb) * tpb;
     const int iz1 = min(nz, iz0 + tpb);
-    // HOLD: the segment spectrum is loaded once into registers and reused by
-    // every template (at 8192 points 12 % less time than re-reading it per
-    // template).  Otherwise it is re-read per template, from L2 (consecutive
-    // workgroups of an XCD share it).
+    // The segment spectrum is loaded once into registers and reused by every
+    // template.  201 templates, bound by the FP32 instructions: 2^23 samples,
+    // 4096 points 1.43 ms re-reading it from L2 against 1.25, 8192 points 1.70
+    // against 1.42; 2^21 samples, 1024 points 0.37 against 0.30, half-bin
+    // plane at 4096 points 0.76 against 0.68.
     // Operands come through buffer loads: one 32-bit lane offset and a
     // per-point constant offset, no 64-bit address arithmetic per load.
     const __amdgpu_buffer_rsrc_t rsp = buffer_rsrc(segspec + s * Sh::S, Sh::S * 8);
@@ -448,11 +445,9 @@ __device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftSh
     const int nend = int(min(int64_t(h) + L, nb - kbase));
     const int sh = int(((kbase % 4) + 4) % 4);  // plane row offset of point 0 modulo 4
     constexpr int PASSES = INTERBIN ? 2 : 1;
-    float2 xh[HOLD ? Sh::R : 1];
-    if constexpr (HOLD) {
+    float2 xh[Sh::R];
 #pragma unroll
-        for (int m = 0; m < Sh::R; ++m) xh[m] = buffer_load_f2(rsp, t, Sh::NT * m);
-    }
+    for (int m = 0; m < Sh::R; ++m) xh[m] = buffer_load_f2(rsp, t, Sh::NT * m);
     for (int it = iz0 * PASSES; it < iz1 * PASSES; ++it) {
         const int iz = INTERBIN ? (it >> 1) : it;
         const bool second = INTERBIN && (it & 1);
@@ -461,7 +456,7 @@ __device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftSh
         int to = t;
         asm volatile("" : "+v"(to));
         const __amdgpu_buffer_rsrc_t rbz = buffer_rsrc((second ? bank_half : bank) + int64_t(iz) * Sh::S, Sh::S * 8);
-        // The operand loads go out in two batches of R / 2 points, each
+        // The template's loads go out in two batches of R / 2 points, each
         // batch issued before any of its products is formed (the scheduling
         // barriers keep the compiler from interleaving loads and multiplies,
         // which under register pressure it does by waiting for each pair in
@@ -471,14 +466,10 @@ __device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftSh
             constexpr int m0 = decltype(hc)::value * (Sh::R / 2);
             float2 b[Sh::R / 2];
 #pragma unroll
-            for (int m = 0; m < Sh::R / 2; ++m) {
-                if constexpr (HOLD) v[m0 + m] = xh[m0 + m];
-                else v[m0 + m] = buffer_load_f2(rsp, to, Sh::NT * (m0 + m));
-                b[m] = buffer_load_f2(rbz, to, Sh::NT * (m0 + m));
-            }
+            for (int m = 0; m < Sh::R / 2; ++m) b[m] = buffer_load_f2(rbz, to, Sh::NT * (m0 + m));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int m = 0; m < Sh::R / 2; ++m) v[m0 + m] = cmul(v[m0 + m], b[m]);
+            for (int m = 0; m < Sh::R / 2; ++m) v[m0 + m] = cmul(xh[m0 + m], b[m]);
             __builtin_amdgcn_sched_barrier(0);
         });
         fft_wg<Sh, +1>(v, lds, tw, t);
@@ -525,9 +516,8 @@ __device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftSh
                 const float4 p4 = *reinterpret_cast<const float4 *>(lf + 4 * c);
                 if (n0 >= h && n0 + 4 <= nend) {
                     __builtin_nontemporal_store(__builtin_bit_cast(f32x4v, p4), reinterpret_cast<f32x4v *>(row + n0));
-                    uint32_t q = uint32_t(power_code(p4.x, code_inv)) | (uint32_t(power_code(p4.y, code_inv)) << 8) |
-                                 (uint32_t(power_code(p4.z, code_inv)) << 16) |
-                                 (uint32_t(power_code(p4.w, code_inv)) << 24);
+                    const uint32_t q = put_code(p4.w, code_inv, 3, put_code(p4.z, code_inv, 2,
+                                       put_code(p4.y, code_inv, 1, put_code(p4.x, code_inv, 0, 0u))));
                     uint32_t *__restrict__ qw = reinterpret_cast<uint32_t *>(qrow + kbase + n0);
                     if (!second) {
                         *qw = q;  // read back by the half-bin pass
@@ -546,7 +536,7 @@ __device__ __forceinline__ void correlate_item(float2 *lds, const Twiddles<FftSh
 }
 
 template <int LOG2S, bool INTERBIN>
-__global__ __launch_bounds__(corr_threads(LOG2S), corr_waves(LOG2S, INTERBIN)) void k_correlate(
+__global__ __launch_bounds__(corr_threads(LOG2S), corr_waves(LOG2S)) void k_correlate(
     const float2 *__restrict__ segspec, const float2 *__restrict__ bank, const float2 *__restrict__ bank_half,
     int nz, int tpb, int64_t nb, int h, int64_t nseg, int64_t total, int64_t per, int grp,
     float *__restrict__ plane, uint8_t *__restrict__ codes, float code_inv) {
@@ -560,10 +550,9 @@ __global__ __launch_bounds__(corr_threads(LOG2S), corr_waves(LOG2S, INTERBIN)) v
     const int64_t gr = u - gi * gsz;
     const int64_t s = gr / grp;
     const int64_t tb = gi * grp + (gr - s * grp);
-    Twiddles<Sh, +1> tw;
+    FusedTwiddles<Sh, +1> tw;
     tw.init(t);
-    correlate_item<LOG2S, INTERBIN, corr_hold(LOG2S, INTERBIN)>(lds, tw, t, segspec, bank, bank_half, nz, tpb, nb, h,
-                                                                 s, tb, plane, codes, code_inv);
+    correlate_item<LOG2S, INTERBIN>(lds, tw, t, segspec, bank, bank_half, nz, tpb, nb, h, s, tb, plane, codes, code_inv);
 }
 
 // ------------------------------------------------ harmonic sum and peaks
@@ -1240,11 +1229,9 @@ __global__ __launch_bounds__(256, 2) void k_batch(BatchArgs a) {
             segfft_item<LOG2S>(lds, to, tr.X, tr.med, a.W, tr.nb, a.h, int64_t(idx), tr.seg);
         } else if (stage == BST_CORR) {
             const int64_t s = int64_t(idx) % tr.nseg, tb = int64_t(idx) / tr.nseg;
-            Twiddles<Sh, +1> tw;
+            FusedTwiddles<Sh, +1> tw;
             tw.init(to);
-            // the segment spectrum held in registers (256 VGPRs, no spills:
-            // 12 % more trials per second at 8192 points)
-            correlate_item<LOG2S, false, true>(lds, tw, to, tr.seg, a.bank, nullptr, a.nz, a.tpb, tr.nb, a.h, s, tb,
+            correlate_item<LOG2S, false>(lds, tw, to, tr.seg, a.bank, nullptr, a.nz, a.tpb, tr.nb, a.h, s, tb,
                                                tr.plane, tr.codes, a.code_inv);
         } else {
             const HarmLists hl = harm_lists(tr.hits, a.cell_cap, a.group_cap);

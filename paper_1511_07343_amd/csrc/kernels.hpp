@@ -49,7 +49,7 @@ hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t n
 //   y = IDFT_S(segspec[s] * bank[iz]) (unnormalised; bank carries 1/S),
 //   plane[iz][s L + n - h] = |y[n]|^2 for n in [h, h + L), inside [0, nb),
 // and beside it the screening codes of 2-bin blocks (nz x nb/2 bytes)
-//   codes[iz][b] = max_{k in {2b, 2b + 1}} min(255, ceil(plane[iz][k] * code_inv)).
+//   codes[iz][b] = max_{k in {2b, 2b + 1}} min(255, floor(plane[iz][k] * code_inv) + 1).
 // With bank_half (the half-bin offsets' bank) each plane row holds 2 nb
 // floats, the bins k from bank in [0, nb) and the points k + 1/2 from
 // bank_half in [nb, 2 nb), and the nz x nb codes cover the pairs
@@ -73,7 +73,7 @@ void build_gemm_bank(const double *taps, int nz, int h, bool bf16, void *out);
 hipError_t launch_lowp_spectrum(const float2 *X, const double *med, int W, int64_t nb, bool bf16, uint32_t *out,
                                 hipStream_t st);
 // plane[iz][k] = |sum_q Xhat[k - q] T_iz[q]|^2 and its block screening codes
-// (as launch_correlate), over `workgroups` persistent workgroups.  nb % 4 == 0.
+// (as launch_correlate), over `workgroups` persistent workgroups.  nb % 512 == 0.
 hipError_t launch_corr_gemm(const uint32_t *xl, int64_t nb, int h, const void *bank, int nz, bool bf16,
                             int workgroups, float *plane, uint8_t *codes, float code_inv, hipStream_t st);
 
