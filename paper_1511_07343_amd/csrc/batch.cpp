@@ -341,8 +341,10 @@ static fdas_status run_persistent_chunk(fdas_plan_s *p, int i0, int m, const flo
         const int64_t n = std::min<int64_t>(std::min<int64_t>(found, p->cand_cap), cap[j]);
         ncands[j] = found;
         if (n > 0) {
-            e = launch_finish_candidates(pb->h_trials[i].cands, pb->h_trials[i].cnt, p->cand_cap, pb->sort, p->nz,
-                                         nbs[size_t(i)], 1, p->zmax, p->dz, pb->final, st);
+            FinishArgs a = finish_args(p, pb->h_trials[i].cands, pb->h_trials[i].cnt, nbs[size_t(i)]);
+            a.out = pb->final;
+            e = std::min(found, p->cand_cap) > kFinishSmall ? launch_finish_large(a, pb->sort, st)
+                                                            : launch_finish_small(a, st);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(cands_host + offset[j], pb->final, size_t(n) * sizeof(fdas_cand),
                                    hipMemcpyDeviceToHost, st);
@@ -495,13 +497,17 @@ extern "C" fdas_status fdas_search_batch(fdas_plan_t *plan, int32_t n, const flo
 
     fdas_status first_err = FDAS_OK;
     bool overflow = false;
-    // Finish trial j: its count is already copied (event ev[j % 2]); copy the
-    // records and convert them.
+    // Finish trial j: its counters are on the host (event ev[j % 2]); sort a
+    // long list and copy the records.
     auto finish = [&](int32_t j) -> fdas_status {
         const int slot = j % 2;
         hipError_t ee = hipEventSynchronize(plan->events[slot]);
         if (ee != hipSuccess) return hip_fail(plan, ee, "batch trial");
-        fdas_status r = copy_candidates(plan, slot_ws(plan, slot), cands_host + offset[size_t(j)], cap[j], &ncands[j],
+        fdas_status r = FDAS_OK;
+        if (long_list(plan, slot_ws(plan, slot)) && !finishes_all(plan, false))
+            r = finish_rest(plan, slot_ws(plan, slot), nsamp[j], nullptr, plan->aux[slot]);
+        if (r != FDAS_OK) return r;
+        r = copy_candidates(plan, slot_ws(plan, slot), cands_host + offset[size_t(j)], cap[j], &ncands[j],
                                         plan->aux[slot]);
         if (r == FDAS_E_OVERFLOW) {
             overflow = true;
@@ -524,11 +530,6 @@ extern "C" fdas_status fdas_search_batch(fdas_plan_t *plan, int32_t n, const flo
         if (e == hipSuccess) e = hipGraphLaunch(exec, plan->aux[slot]);
         if (e != hipSuccess) {
             first_err = hip_fail(plan, e, "batch trial launch");
-            break;
-        }
-        e = hipMemcpyAsync(ws.h_count, ws.count, 24, hipMemcpyDeviceToHost, plan->aux[slot]);
-        if (e != hipSuccess) {
-            first_err = hip_fail(plan, e, "copy candidate count");
             break;
         }
         e = hipEventRecord(plan->events[slot], plan->aux[slot]);

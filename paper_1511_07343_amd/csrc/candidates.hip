@@ -1,8 +1,9 @@
 // Candidate finishing on the device: order the harmonic-sum kernel's
-// (unordered) records by (nharm, k, iz) with an LSD radix sort (per 8-bit
-// digit a count kernel and a scatter kernel that scans the counts itself),
-// then write the public records with r, z and the FP64 single-trial
-// significance.
+// (unordered) records by (nharm, k, iz) and write the public records with r,
+// z and the FP64 single-trial significance.  Lists of at most kFinishSmall
+// records, nearly every trial's, take one kernel; longer ones an LSD radix
+// sort (per 8-bit digit a count kernel and a scatter kernel that scans the
+// counts itself).
 // The record count stays on the device: every kernel reads it and clamps it
 // to the buffer capacity, so nothing waits for the host in between.
 #include <hip/hip_runtime.h>
@@ -39,22 +40,83 @@ __device__ __forceinline__ void block_range(uint32_t n, uint32_t &beg, uint32_t 
 // key = (level nb + k) nz + iz, level = log2(nharm) in 0..4, k < nb, iz < nz:
 // ascending keys are ascending (nharm, k, iz), and all keys are below
 // 5 nb nz (32 bits, four 8-bit passes, at 2^23 samples and 201 templates).
-// One workgroup per block range (RS_BLOCKS of them): the keys and values of
-// the range and the first pass's digit counts of the range.
+__device__ __forceinline__ uint64_t cand_key(const DevCand &c, int64_t nb, int nz) {
+    const uint64_t level = uint64_t(31 - __clz(c.nharm));
+    return (level * uint64_t(nb) + uint64_t(uint32_t(c.k))) * uint64_t(nz) + uint64_t(uint32_t(c.iz));
+}
+
+// The public record of c.
+__device__ __forceinline__ fdas_cand public_record(const DevCand &c, const FinishArgs &a) {
+    fdas_cand o;
+    o.k = c.k;
+    o.iz = c.iz;
+    o.nharm = c.nharm;
+    o.r = double(c.k) / (double(c.nharm) * double(a.cpb));
+    if (a.td) {
+        // -alpha_max + d iz with two roundings, as the trials are formed (a
+        // fused multiply-add would round once and can differ in the last bit)
+#pragma clang fp contract(off)
+        const double alpha = a.nz == 1 ? 0.0 : -a.zmax + a.dz * double(c.iz);
+        o.z = alpha * o.r;
+    } else {
+        o.z = (-a.zmax + double(c.iz) * a.dz) / double(c.nharm);
+    }
+    o.power = c.power;
+    o.sigma = float(significance_d(double(c.power), c.nharm));
+    return o;
+}
+
+// Lists of at most kFinishSmall records: every workgroup loads all the keys
+// into LDS and ranks FS_RECORDS of the records among them, a quarter of the
+// keys per wave, all lanes reading the same key (no two records share a key,
+// so the ranks are the order); then it writes its records at their ranks.
+// One launch and no pass over memory in between: 130 records take 6 us, where
+// a one-workgroup sort, seven empty radix kernels and the records' kernel
+// took 40.
+constexpr int FS_RECORDS = 64;
+constexpr int FS_THREADS = 256;
+
+__global__ __launch_bounds__(FS_THREADS) void k_finish_small(FinishArgs a) {
+    __shared__ __align__(16) uint64_t key[kFinishSmall];
+    __shared__ uint32_t less[FS_THREADS / 64][FS_RECORDS];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (a.count_dst && blockIdx.x == 0 && t < 6) a.count_dst[t] = a.count[t];
+    const uint32_t n = clamp_count(a.count, a.cap), first = blockIdx.x * FS_RECORDS;
+    if (n > kFinishSmall || first >= n) return;
+    const uint32_t share = (n + 7) / 8 * 2;  // keys per wave, a whole number of pairs
+    for (uint32_t i = t; i < 4 * share; i += FS_THREADS) key[i] = i < n ? cand_key(a.dc[i], a.nb, a.nz) : ~uint64_t(0);
+    __syncthreads();
+    const uint32_t r = first + lane;
+    const uint64_t mine = key[min(r, n - 1)];
+    uint32_t below = 0;
+#pragma unroll 4
+    for (uint32_t i = w * share; i < (w + 1) * share; i += 2) {
+        const ulonglong2 k2 = *reinterpret_cast<const ulonglong2 *>(key + i);
+        below += (k2.x < mine ? 1u : 0u) + (k2.y < mine ? 1u : 0u);
+    }
+    less[w][lane] = below;
+    __syncthreads();
+    if (w != 0 || r >= n) return;
+    const uint32_t rank = less[0][lane] + less[1][lane] + less[2][lane] + less[3][lane];
+    if (rank < a.out_cap) a.out[rank] = public_record(a.dc[r], a);
+}
+
+// The radix sort of longer lists.  One workgroup per block range (RS_BLOCKS of
+// them): the keys and values of the range and the first pass's digit counts
+// of the range.
 __global__ __launch_bounds__(RS_THREADS) void k_cand_keys(const DevCand *__restrict__ dc, const uint32_t *__restrict__ count,
                                                           uint32_t cap, int64_t nb, int nz, uint64_t *__restrict__ keys,
                                                           uint32_t *__restrict__ vals, uint32_t *__restrict__ hist) {
     __shared__ uint32_t lh[RS_DIGITS];
     const uint32_t n = clamp_count(count, cap);
+    if (n <= kFinishSmall) return;
     const int t = threadIdx.x;
     lh[t] = 0u;
     __syncthreads();
     uint32_t beg, end;
     block_range(n, beg, end);
     for (uint32_t i = beg + t; i < end; i += RS_THREADS) {
-        const DevCand c = dc[i];
-        const uint64_t level = uint64_t(31 - __clz(c.nharm));
-        const uint64_t key = (level * uint64_t(nb) + uint64_t(uint32_t(c.k))) * uint64_t(nz) + uint64_t(uint32_t(c.iz));
+        const uint64_t key = cand_key(dc[i], nb, nz);
         keys[i] = key;
         vals[i] = i;
         atomicAdd(&lh[uint32_t(key) & (RS_DIGITS - 1u)], 1u);
@@ -63,53 +125,13 @@ __global__ __launch_bounds__(RS_THREADS) void k_cand_keys(const DevCand *__restr
     hist[blockIdx.x * RS_DIGITS + t] = lh[t];
 }
 
-// Lists of at most SMALL records are sorted by one workgroup in LDS
-// (bitonic, not stable, which is harmless: no two records share a key); the
-// radix passes skip them.
-constexpr uint32_t SMALL = 2048;
-constexpr int SMALL_THREADS = 1024;
-
-__global__ __launch_bounds__(SMALL_THREADS) void k_small_sort(const uint64_t *__restrict__ kin,
-                                                              const uint32_t *__restrict__ vin,
-                                                              const uint32_t *__restrict__ count, uint32_t cap,
-                                                              uint32_t *__restrict__ vout) {
-    __shared__ uint64_t key[SMALL];
-    __shared__ uint32_t val[SMALL];
-    const uint32_t n = clamp_count(count, cap);
-    if (n > SMALL) return;
-    const int t = threadIdx.x;
-    for (uint32_t i = t; i < SMALL; i += SMALL_THREADS) {
-        key[i] = i < n ? kin[i] : ~uint64_t(0);
-        val[i] = i < n ? vin[i] : 0u;
-    }
-    for (uint32_t size = 2; size <= SMALL; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            __syncthreads();
-            for (uint32_t i = t; i < SMALL / 2; i += SMALL_THREADS) {
-                const uint32_t lo = 2 * stride * (i / stride) + (i % stride), hi = lo + stride;
-                const bool asc = (lo & size) == 0;
-                const uint64_t a = key[lo], b = key[hi];
-                if ((a > b) == asc) {
-                    key[lo] = b;
-                    key[hi] = a;
-                    const uint32_t v = val[lo];
-                    val[lo] = val[hi];
-                    val[hi] = v;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    for (uint32_t i = t; i < n; i += SMALL_THREADS) vout[i] = val[i];
-}
-
 // Digit counts of the pass at `shift` (passes after the first).
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint64_t *__restrict__ keys,
                                                         const uint32_t *__restrict__ count, uint32_t cap, int shift,
                                                         uint32_t *__restrict__ hist) {
     __shared__ uint32_t lh[RS_DIGITS];
     const uint32_t n = clamp_count(count, cap);
-    if (n <= SMALL) return;
+    if (n <= kFinishSmall) return;
     const int t = threadIdx.x;
     lh[t] = 0u;
     __syncthreads();
@@ -148,7 +170,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restri
     __shared__ uint32_t cnt[RS_THREADS / 64][RS_DIGITS];
     __shared__ uint32_t wsum[RS_THREADS / 64];
     const uint32_t n = clamp_count(count, cap);
-    if (n <= SMALL) return;
+    if (n <= kFinishSmall) return;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     uint32_t before = 0, total = 0;
 #pragma unroll 16
@@ -224,28 +246,14 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restri
     }
 }
 
-// The public records of the first min(count, cap, out_cap) sorted records;
-// with count_dst, also the six counter words there (out and count_dst may be
-// device aliases of page-locked host memory).
-__global__ __launch_bounds__(256) void k_cand_finalize(const DevCand *__restrict__ dc,
-                                                       const uint32_t *__restrict__ order,
-                                                       const uint32_t *__restrict__ count, uint32_t cap, int cpb,
-                                                       double zmax, double dz, fdas_cand *__restrict__ out,
-                                                       uint32_t out_cap, uint32_t *__restrict__ count_dst) {
-    if (count_dst && blockIdx.x == 0 && threadIdx.x < 6) count_dst[threadIdx.x] = count[threadIdx.x];
-    const uint32_t n = min(clamp_count(count, cap), out_cap);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const DevCand c = dc[order[i]];
-        fdas_cand o;
-        o.k = c.k;
-        o.iz = c.iz;
-        o.nharm = c.nharm;
-        o.r = double(c.k) / (double(c.nharm) * double(cpb));
-        o.z = (-zmax + double(c.iz) * dz) / double(c.nharm);
-        o.power = c.power;
-        o.sigma = float(significance_d(double(c.power), c.nharm));
-        out[i] = o;
-    }
+// The public records of the first min(count, cap, out_cap) sorted records, and
+// the counters where they are wanted.
+__global__ __launch_bounds__(256) void k_cand_finalize(FinishArgs a, const uint32_t *__restrict__ order) {
+    const uint32_t n = clamp_count(a.count, a.cap);
+    if (n <= kFinishSmall) return;
+    if (a.count_dst && blockIdx.x == 0 && threadIdx.x < 6) a.count_dst[threadIdx.x] = a.count[threadIdx.x];
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < min(n, a.out_cap); i += gridDim.x * blockDim.x)
+        a.out[i] = public_record(a.dc[order[i]], a);
 }
 
 // min(count, cap) records, and the six counter words, written straight into
@@ -280,14 +288,20 @@ size_t cand_sort_scratch_bytes(uint32_t cap) {
     return size_t(cap) * (2 * sizeof(uint64_t) + 2 * sizeof(uint32_t)) + 16 + size_t(RS_DIGITS) * RS_BLOCKS * 4;
 }
 
-// Launches: keys (with the first pass's counts), the one-workgroup sort of
-// short lists, per radix pass the digit counts (after the first) and the
-// scatter (each returns at once for short lists), the public records.
-hipError_t launch_finish_candidates(const DevCand *dc, const uint32_t *count, uint32_t cap, void *scratch, int nz,
-                                    int64_t nb, int cpb, double zmax, double dz, fdas_cand *out, hipStream_t st,
-                                    uint32_t out_cap, uint32_t *count_dst) {
-    if (cap == 0) return hipSuccess;
-    const uint64_t span = 5 * uint64_t(nb) * uint64_t(nz);  // keys are below this
+hipError_t launch_finish_small(const FinishArgs &a, hipStream_t st) {
+    const uint32_t most = a.cap < kFinishSmall ? a.cap : kFinishSmall;
+    const unsigned grid = most > 0 ? (most + FS_RECORDS - 1) / FS_RECORDS : 1;
+    hipLaunchKernelGGL(k_finish_small, dim3(grid), dim3(FS_THREADS), 0, st, a);
+    return hipGetLastError();
+}
+
+// Launches: keys (with the first pass's counts), per radix pass the digit
+// counts (after the first) and the scatter, the public records.  Each returns
+// at once for lists that launch_finish_small has finished.
+hipError_t launch_finish_large(const FinishArgs &a, void *scratch, hipStream_t st) {
+    const uint32_t cap = a.cap;
+    if (cap <= kFinishSmall) return hipSuccess;
+    const uint64_t span = 5 * uint64_t(a.nb) * uint64_t(a.nz);  // keys are below this
     int bits = 1;
     while (bits < 64 && (uint64_t(1) << bits) < span) ++bits;
     const int passes = (bits + 7) / 8;
@@ -301,18 +315,16 @@ hipError_t launch_finish_candidates(const DevCand *dc, const uint32_t *count, ui
     // threads than records (about two each for 241 k records) a wave's writes
     // of one record go out while it computes its next significance, instead
     // of every significance first and then all the writes (about 12 us less).
-    const uint64_t gmax = count_dst ? 512 : 1024;
+    const uint64_t gmax = a.count_dst ? 512 : 1024;
     const unsigned grid = unsigned(blocks < gmax ? blocks : gmax);
-    hipLaunchKernelGGL(k_cand_keys, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, dc, count, cap, nb, nz, k0, v0, hist);
+    hipLaunchKernelGGL(k_cand_keys, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, a.dc, a.count, cap, a.nb, a.nz, k0, v0,
+                       hist);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // the order ends in v0 after an even number of passes, else in v1
-    hipLaunchKernelGGL(k_small_sort, dim3(1), dim3(SMALL_THREADS), 0, st, k0, v0, count, cap,
-                       (passes % 2) ? v1 : v0);
     for (int p = 0; p < passes; ++p) {
         if (p > 0)
-            hipLaunchKernelGGL(k_rs_hist, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, k0, count, cap, 8 * p, hist);
-        hipLaunchKernelGGL(k_rs_pass, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, k0, v0, count, cap, 8 * p, hist, k1,
+            hipLaunchKernelGGL(k_rs_hist, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, k0, a.count, cap, 8 * p, hist);
+        hipLaunchKernelGGL(k_rs_pass, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, k0, v0, a.count, cap, 8 * p, hist, k1,
                            v1);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -323,8 +335,7 @@ hipError_t launch_finish_candidates(const DevCand *dc, const uint32_t *count, ui
         v0 = v1;
         v1 = tv;
     }
-    hipLaunchKernelGGL(k_cand_finalize, dim3(grid), dim3(256), 0, st, dc, v0, count, cap, cpb, zmax, dz, out, out_cap,
-                       count_dst);
+    hipLaunchKernelGGL(k_cand_finalize, dim3(grid), dim3(256), 0, st, a, v0);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <array>
 #include <cstdint>
 #include <map>
@@ -43,7 +44,11 @@ struct Workspace {
     void *hits = nullptr;         // harmonic-sum screen lists, exact sums and group map
     void *sort = nullptr;         // radix-sort scratch
     fdas_cand *final = nullptr;   // sorted public records
-    uint32_t *h_count = nullptr;  // pinned host copy of the count
+    // Page-locked: the host copy of the counters (the finishing kernel writes
+    // it), then kFinishSmall records, where a search whose caller's buffer is
+    // ordinary memory has its records written; and their device aliases.
+    uint32_t *h_count = nullptr, *d_h_count = nullptr;
+    fdas_cand *h_final = nullptr, *d_h_final = nullptr;
     float *series = nullptr;      // graph input: the trial is copied here first (batched path)
     float *resampled = nullptr;   // time-domain search: the series resampled for one trial
 };
@@ -125,19 +130,27 @@ void destroy_workspace(Workspace &ws);
 // state alone; X_out / med_out (may be NULL) receive the normalised
 // spectrum's source buffer and medians the search used (NULL for a
 // time-domain plan, medians NULL for an already normalised spectrum).
-// direct (may be NULL): the public records go to direct->out (at most
-// direct->cap of them) and the counters to direct->count instead of
-// ws.final (device aliases of page-locked host memory; FFT and matrix
-// plans without refinement only).
+// The counters go to *ws.h_count, the public records to ws.final or, with
+// direct (may be NULL; plans without refinement only), at most direct->cap of
+// them to direct->out (a device alias of page-locked host memory).  Unless
+// finishes_all(p, timed), a list of more than kFinishSmall records is left
+// unfinished: once the counters are on the host, finish_rest does it.
 struct DirectOut {
     fdas_cand *out;
     uint32_t cap;
-    uint32_t *count;
 };
 fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &g, int32_t in_kind,
                            const void *in_dev, float *plane, DevCand *dcands, uint32_t *dcount, hipStream_t st,
                            bool timed = false, const float2 **X_out = nullptr, const double **med_out = nullptr,
                            const DirectOut *direct = nullptr);
+// Whether enqueue_search also enqueues the kernels that finish long lists:
+// when records are refined afterwards, and within timed stages.
+inline bool finishes_all(const fdas_plan_s *p, bool timed) { return timed || p->opts.refine_levels > 0; }
+inline bool long_list(const fdas_plan_s *p, const Workspace &ws) {
+    return std::min(ws.h_count[0], p->cand_cap) > kFinishSmall;
+}
+fdas_status finish_rest(fdas_plan_s *p, const Workspace &ws, int64_t nsamp, const DirectOut *direct, hipStream_t st);
+FinishArgs finish_args(const fdas_plan_s *p, const DevCand *dc, const uint32_t *count, int64_t ncol);
 // Trial value of plane row iz: the drift z(iz) of a template plan, the
 // acceleration trial alpha_iz of a time-domain plan.
 double row_value(const fdas_plan_s *p, int32_t iz);

@@ -10,12 +10,14 @@ namespace fdas {
 constexpr double kLn2 = 0.69314718055994530942;
 
 // m(k): block medians joined linearly between block centres, flat outside.
+// Bin numbers fit 32 bits (a spectrum has at most 2^25 bins), whose
+// conversions to and from FP64 are single instructions.
 __device__ __forceinline__ double median_curve(const double *__restrict__ med, int64_t nblk, int W,
                                                int64_t nb, int64_t g) {
-    const double c0 = 0.5 * double(min(int64_t(W), nb) - 1);
-    const int64_t wl = nb - (nblk - 1) * int64_t(W);
-    const double cl = double((nblk - 1) * int64_t(W)) + 0.5 * double(wl - 1);
-    const double x = double(g);
+    const double c0 = 0.5 * double(min(W, int(nb)) - 1);
+    const int w0 = int(nblk - 1) * W;  // first bin of the last block
+    const double cl = double(w0) + 0.5 * double(int(nb) - w0 - 1);
+    const double x = double(int(g));
     if (x <= c0 || nblk == 1) return med[0];
     if (x >= cl) return med[nblk - 1];
     // W is a power of two, so dividing by it is the exact multiply by 1 / W;
@@ -23,11 +25,23 @@ __device__ __forceinline__ double median_curve(const double *__restrict__ med, i
     // and its reciprocal width does not depend on g (computed once per
     // thread when inlined in a loop)
     const double inv_w = 1.0 / double(W);
-    const double inv_last = 1.0 / (cl - (c0 + double(nblk - 2) * double(W)));
-    const int64_t b = int64_t(floor((x - c0) * inv_w));
+    const double inv_last = 1.0 / (cl - (c0 + double(int(nblk) - 2) * double(W)));
+    const int b = int(floor((x - c0) * inv_w));
     const double cb = c0 + double(b) * double(W);
     const double f = (x - cb) * (b + 1 == nblk - 1 ? inv_last : inv_w);
     return med[b] + (med[b + 1] - med[b]) * f;
+}
+
+// The normalising factor sqrt(ln 2 / m) in FP64 (0 where m is not positive):
+// the hardware's reciprocal square root and two Newton steps, to a rounding or
+// two of the division and square root, which take three times as long.
+__device__ __forceinline__ double norm_scale(double m) {
+    if (!(m > 0.0)) return 0.0;
+    if (!(m > 1e-280 && m < 1e280)) return sqrt(kLn2 / m);
+    double r = __builtin_amdgcn_rsq(m);
+    r = fma(0.5 * r, fma(-m * r, r, 1.0), r);
+    r = fma(0.5 * r, fma(-m * r, r, 1.0), r);
+    return 0.83255461115769775635 * r;  // sqrt(ln 2)
 }
 
 // Screening code of a power: floor(P / delta) + 1, at most 255, with
@@ -54,56 +68,56 @@ __device__ __forceinline__ uint16_t block_codes4(float4 p, float code_inv) {
 }
 
 // Single-trial significance in FP64: log Q(n, s) of a sum of n unit-mean
-// exponential powers, log Phi_c of the Gaussian tail, and sigma from them.
+// exponential powers (n <= 16), and sigma with Phi_c(sigma) = Q(n, s).
+
+// Q(n, s) = exp(-s) sum_{i < n} s^i / i!, the sum as 1 + s (1 + s/2 (1 + ...)).
 __device__ inline double log_gamma_survival_d(int n, double s) {
     if (s <= 0.0) return 0.0;
-    const double ls = log(s);
-    double mx = -INFINITY, lf = 0.0;
-    for (int i = 0; i < n; ++i) {  // log(i!) accumulated exactly enough for i <= 16
-        if (i > 0) lf += log(double(i));
-        mx = fmax(mx, double(i) * ls - lf);
-    }
-    double acc = 0.0;
-    lf = 0.0;
-    for (int i = 0; i < n; ++i) {
-        if (i > 0) lf += log(double(i));
-        acc += exp(double(i) * ls - lf - mx);
-    }
-    return -s + mx + log(acc);
+    if (s > 1e18) return -s;  // the logarithm of the sum is below a rounding of s
+    double sum = 1.0;
+#pragma unroll
+    for (int i = 15; i >= 1; --i)
+        if (i < n) sum = fma(sum * s, 1.0 / double(i), 1.0);
+    return log(sum) - s;
 }
 
-__device__ inline double log_normal_tail_d(double sg) {
-    if (sg < 30.0) return log(0.5 * erfc(sg * 0.70710678118654752440));
-    const double s2 = 1.0 / (sg * sg);
-    const double series = 1.0 - s2 + 3.0 * s2 * s2 - 15.0 * s2 * s2 * s2 + 105.0 * s2 * s2 * s2 * s2;
-    return -0.5 * sg * sg - log(sg) - 0.91893853320467274178 + log(series);
-}
+__device__ inline double log_normal_tail_d(double sg) { return log(0.5 * erfc(sg * 0.70710678118654752440)); }
 
-// sigma with Phi_c(sigma) = Q(n, power): Newton's method on
-// f(sigma) = log Phi_c(sigma) - log Q, with f' = -phi(sigma) / Phi_c(sigma)
-// (f is decreasing and concave), inside a bracket that falls back to
-// bisection whenever a Newton step leaves it.
-__device__ inline double significance_d(double power, int n) {
-    const double target = log_gamma_survival_d(n, power);
-    double lo = -40.0, hi = 40.0;
-    if (log_normal_tail_d(lo) < target) return lo;
-    while (log_normal_tail_d(hi) > target && hi < 1e9) hi *= 2.0;
-    // start from the tail asymptote log Phi_c(x) ~ -x^2/2 - log(x sqrt(2 pi))
-    double x = sqrt(fmax(-2.0 * target, 1.0));
-    x = fmin(fmax(x, lo), hi);
+// sigma <= 0: Newton's method inside a bracket that falls back to bisection
+// whenever a step leaves it.
+__device__ inline double significance_low_d(double target) {
+    double lo = -40.0, hi = 1.0, x = 0.0;
     for (int it = 0; it < 100; ++it) {
         const double lt = log_normal_tail_d(x);
         const double f = lt - target;
         if (f > 0.0) lo = x; else hi = x;
         const double dlog = -exp(-0.5 * x * x - 0.91893853320467274178 - lt);  // d/dx log Phi_c
         double nx = x - f / dlog;
-        if (fabs(nx - x) <= 1e-12 * fmax(1.0, fabs(x))) {
-            x = nx;
-            break;
-        }
+        if (fabs(nx - x) <= 1e-12 * fmax(1.0, fabs(x))) return nx;
         if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
         x = nx;
         if (hi - lo <= 1e-12 * fmax(1.0, fabs(hi))) break;
+    }
+    return x;
+}
+
+// With E(x) = erfcx(x / sqrt 2): log Phi_c(x) = log(E / 2) - x^2 / 2 and its
+// derivative -sqrt(2 / pi) / E.  log Phi_c is concave and decreasing, so after
+// its first step Newton's method approaches the root from the right, and a
+// step below 1e-7 leaves an error of its square.
+__device__ inline double significance_d(double power, int n) {
+    const double target = log_gamma_survival_d(n, power);
+    if (!(target < -0.69314718055994530942)) return significance_low_d(target);
+    constexpr double kMost = 1342177280.0;  // reported from there on (powers past 9e17, infinite ones)
+    if (!(target > -0.5 * kMost * kMost)) return kMost;
+    const double t = -2.0 * target;
+    double x = sqrt(fmax(t - log(6.28318530717958647693 * t), 0.25));  // the tail's asymptote
+    for (int it = 0; it < 50; ++it) {
+        const double e = erfcx(x * 0.70710678118654752440);
+        const double f = log(0.5 * e) - 0.5 * x * x - target;
+        const double dx = f * e * 1.25331413731550025121;  // sqrt(pi / 2)
+        x += dx;
+        if (fabs(dx) <= 1e-7 * fmax(1.0, x)) break;
     }
     return x;
 }

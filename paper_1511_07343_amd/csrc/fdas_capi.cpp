@@ -116,6 +116,44 @@ int64_t candidate_bytes(const fdas_plan_s *p, const Geometry &g) {
            int64_t(harmsum_scratch_bytes(p->nz, g.ncol, p->hit_cap, p->group_cap)) + 64 + (p->corr ? g.nb * 4 : 0);
 }
 
+// Arguments of the finishing kernels, records to ws.final.
+FinishArgs finish_args(const fdas_plan_s *p, const DevCand *dc, const uint32_t *count, int64_t ncol) {
+    FinishArgs a{};
+    a.dc = dc;
+    a.count = count;
+    a.cap = p->cand_cap;
+    a.nz = p->nz;
+    a.nb = ncol;
+    a.cpb = cols_per_bin(p);
+    a.td = p->td;
+    a.zmax = p->zmax;
+    a.dz = p->dz;
+    a.out_cap = p->cand_cap;
+    return a;
+}
+
+static FinishArgs finish_args(const fdas_plan_s *p, const Workspace &ws, const DevCand *dc, const uint32_t *count,
+                              int64_t ncol, const DirectOut *direct) {
+    FinishArgs a = finish_args(p, dc, count, ncol);
+    a.out = direct ? direct->out : ws.final;
+    if (direct) a.out_cap = direct->cap;
+    a.count_dst = ws.d_h_count;
+    return a;
+}
+
+static hipError_t enqueue_finish(const fdas_plan_s *p, const Workspace &ws, const DevCand *dc, const uint32_t *count,
+                                 int64_t ncol, const DirectOut *direct, bool all, hipStream_t st) {
+    const FinishArgs a = finish_args(p, ws, dc, count, ncol, direct);
+    const hipError_t e = launch_finish_small(a, st);
+    return e == hipSuccess && all ? launch_finish_large(a, ws.sort, st) : e;
+}
+
+fdas_status finish_rest(fdas_plan_s *p, const Workspace &ws, int64_t nsamp, const DirectOut *direct, hipStream_t st) {
+    const int64_t ncol = nsamp / 2 * cols_per_bin(p);
+    const hipError_t e = launch_finish_large(finish_args(p, ws, ws.cands, ws.count, ncol, direct), ws.sort, st);
+    return e == hipSuccess ? FDAS_OK : hip_fail(p, e, "candidate sort");
+}
+
 // The time-domain resampling search on `st`: per trial, resample, real DFT,
 // block medians, normalised powers and codes into plane row iz; then the
 // harmonic sums along each row (izc < 0), peaks, candidates and their drift.
@@ -123,7 +161,7 @@ int64_t candidate_bytes(const fdas_plan_s *p, const Geometry &g) {
 // candidates (the others stay empty).
 static fdas_status enqueue_td_search(fdas_plan_s *p, const Workspace &ws, const Geometry &g, int32_t in_kind,
                                      const void *in_dev, float *plane, DevCand *dcands, uint32_t *dcount,
-                                     hipStream_t st, bool timed) {
+                                     hipStream_t st, bool timed, const DirectOut *direct) {
     if (in_kind != FDAS_IN_SERIES_F32) {
         set_error("a time-domain plan searches float32 series only");
         return FDAS_E_INVAL;
@@ -146,9 +184,7 @@ static fdas_status enqueue_td_search(fdas_plan_s *p, const Workspace &ws, const 
     if (e == hipSuccess)
         e = launch_harmsum(plane, ws.codes, p->nz, g.nb, 0, -1, p->opts.nharm_max, p->thr_f, p->code_thr, ws.hits,
                            p->hit_cap, p->group_cap, dcands, dcount, p->cand_cap, st);
-    if (e == hipSuccess)
-        e = launch_finish_candidates(dcands, dcount, p->cand_cap, ws.sort, p->nz, g.nb, 1, p->zmax, p->dz, ws.final, st);
-    if (e == hipSuccess) e = launch_td_drift(dcount, p->cand_cap, p->zmax, p->nz, ws.final, st);
+    if (e == hipSuccess) e = enqueue_finish(p, ws, dcands, dcount, g.nb, direct, finishes_all(p, timed), st);
     for (int i = 5; i <= FDAS_NSTAGES && e == hipSuccess; ++i) e = mark(i);
     if (e != hipSuccess) return hip_fail(p, e, "time-domain harmonic sums");
     return FDAS_OK;
@@ -167,7 +203,7 @@ fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &
                            const DirectOut *direct) {
     if (X_out) *X_out = nullptr;
     if (med_out) *med_out = nullptr;
-    if (p->td) return enqueue_td_search(p, ws, g, in_kind, in_dev, plane, dcands, dcount, st, timed);
+    if (p->td) return enqueue_td_search(p, ws, g, in_kind, in_dev, plane, dcands, dcount, st, timed, direct);
     hipError_t e;
     const float2 *X = nullptr;
     const double *med = nullptr;
@@ -194,7 +230,7 @@ fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &
     }
     if ((e = mark(2)) != hipSuccess) return hip_fail(p, e, "timing event");
     if (p->corr == FDAS_CORR_FFT_F32) {
-        e = launch_segfft(X, med, p->W, g.nb, p->log2s, p->h, g.nseg, ws.seg, st);
+        e = launch_segfft(X, med, p->W, g.nb, p->log2s, p->h, g.nseg, ws.seg, dcount, st);
         if (e != hipSuccess) return hip_fail(p, e, "segment DFT");
         if ((e = mark(3)) != hipSuccess) return hip_fail(p, e, "timing event");
         e = launch_correlate(ws.seg, p->d_bank, p->d_bank_half, p->nz, p->tpb, g.nb, p->log2s, p->h, g.nseg, plane,
@@ -203,26 +239,21 @@ fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &
         if (e != hipSuccess) return hip_fail(p, e, "correlate");
     } else {
         const bool bf16 = p->corr == FDAS_CORR_GEMM_BF16;
-        e = launch_lowp_spectrum(X, med, p->W, g.nb, bf16, ws.xl, st);
+        e = launch_lowp_spectrum(X, med, p->W, g.nb, bf16, ws.xl, dcount, st);
         if (e != hipSuccess) return hip_fail(p, e, "16-bit spectrum");
         if ((e = mark(3)) != hipSuccess) return hip_fail(p, e, "timing event");
         e = launch_corr_gemm(ws.xl, g.nb, p->h, p->d_gemm, p->nz, bf16, p->num_cu, plane, ws.codes, p->code_inv, st);
         if (e != hipSuccess) return hip_fail(p, e, "matrix correlate");
     }
     if ((e = mark(4)) != hipSuccess) return hip_fail(p, e, "timing event");
-    e = launch_zero_u32(dcount, 6, st);
-    if (e != hipSuccess) return hip_fail(p, e, "zero counter");
     e = launch_harmsum(plane, ws.codes, p->nz, g.ncol, p->opts.interbin ? g.nb : 0, p->izc, p->opts.nharm_max, p->thr_f, p->code_thr, ws.hits,
                        p->hit_cap, p->group_cap, dcands, dcount, p->cand_cap, st);
     if (e != hipSuccess) return hip_fail(p, e, "harmonic sum");
-    if (direct && (p->td || p->opts.refine_levels > 0)) {
+    if (direct && p->opts.refine_levels > 0) {
         set_error("records written to the host directly need a plan without refinement");
         return FDAS_E_INVAL;
     }
-    e = direct ? launch_finish_candidates(dcands, dcount, p->cand_cap, ws.sort, p->nz, g.ncol, cols_per_bin(p), p->zmax,
-                                          p->dz, direct->out, st, direct->cap, direct->count)
-               : launch_finish_candidates(dcands, dcount, p->cand_cap, ws.sort, p->nz, g.ncol, cols_per_bin(p), p->zmax,
-                                          p->dz, ws.final, st);
+    e = enqueue_finish(p, ws, dcands, dcount, g.ncol, direct, finishes_all(p, timed), st);
     if (e != hipSuccess) return hip_fail(p, e, "candidate sort");
     if ((e = mark(5)) != hipSuccess) return hip_fail(p, e, "timing event");
     if (p->opts.refine_levels > 0) {
@@ -337,7 +368,10 @@ fdas_status alloc_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp) {
     FDAS_ALLOC(ws.hits, harmsum_scratch_bytes(p->nz, g.ncol, p->hit_cap, p->group_cap));
     FDAS_ALLOC(ws.final, int64_t(p->cand_cap) * int64_t(sizeof(fdas_cand)));
 #undef FDAS_ALLOC
-    e = hipHostMalloc(reinterpret_cast<void **>(&ws.h_count), 64, hipHostMallocDefault);
+    e = hipHostMalloc(reinterpret_cast<void **>(&ws.h_count), 64 + kFinishSmall * sizeof(fdas_cand), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&ws.d_h_count), ws.h_count, 0);
+    ws.h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.h_count) + 64);
+    ws.d_h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.d_h_count) + 64);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_workspace(ws);
@@ -355,20 +389,16 @@ fdas_status collect(fdas_plan_s *p, Workspace &ws, fdas_cand *out, int64_t cap, 
                     hipStream_t st) {
     // Page-locked destination: one kernel writes the records and the counters
     // straight into host memory, with no round trip for the count in between.
-    void *dev_out = nullptr, *dev_cnt = nullptr;
-    if (cap > 0 && out && hipHostGetDevicePointer(&dev_out, out, 0) == hipSuccess && dev_out &&
-        hipHostGetDevicePointer(&dev_cnt, ws.h_count, 0) == hipSuccess && dev_cnt) {
+    void *dev_out = nullptr;
+    if (cap > 0 && out && hipHostGetDevicePointer(&dev_out, out, 0) == hipSuccess && dev_out) {
         const uint32_t c = uint32_t(std::min<int64_t>(cap, int64_t(p->cand_cap)));
-        hipError_t e = launch_copy_records(ws.final, ws.count, c, static_cast<fdas_cand *>(dev_out),
-                                           static_cast<uint32_t *>(dev_cnt), st);
+        hipError_t e = launch_copy_records(ws.final, ws.count, c, static_cast<fdas_cand *>(dev_out), ws.d_h_count, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return hip_fail(p, e, "copy candidates");
         return count_status(p, ws, cap, ncands);
     }
     (void)hipGetLastError();  // a pageable destination is not an error
-    hipError_t e = hipMemcpyAsync(ws.h_count, ws.count, 24, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return hip_fail(p, e, "copy candidate count");
-    e = hipStreamSynchronize(st);
+    const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(p, e, "search");
     return copy_candidates(p, ws, out, cap, ncands, st);
 }
@@ -783,17 +813,19 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
     plan->searched = false;
     plan->last_X = nullptr;
     plan->last_med = nullptr;
-    // Page-locked destination and nothing to post-process: the finishing
-    // kernel writes the records and the counters straight into host memory.
+    // Nothing to post-process: the finishing kernel writes the records straight
+    // into the caller's buffer where that is page-locked, else into the
+    // workspace's, from which they are copied here.
     DirectOut direct{};
-    bool use_direct = false;
-    if (cap > 0 && !plan->td && plan->opts.refine_levels == 0) {
-        void *dev_out = nullptr, *dev_cnt = nullptr;
-        if (hipHostGetDevicePointer(&dev_out, cands_host, 0) == hipSuccess && dev_out &&
-            hipHostGetDevicePointer(&dev_cnt, ws.h_count, 0) == hipSuccess && dev_cnt) {
-            direct = DirectOut{static_cast<fdas_cand *>(dev_out), uint32_t(std::min<int64_t>(cap, plan->cand_cap)),
-                               static_cast<uint32_t *>(dev_cnt)};
+    bool use_direct = false, staged = false;
+    if (plan->opts.refine_levels == 0) {
+        void *dev_out = nullptr;
+        if (cap > 0 && hipHostGetDevicePointer(&dev_out, cands_host, 0) == hipSuccess && dev_out) {
+            direct = DirectOut{static_cast<fdas_cand *>(dev_out), uint32_t(std::min<int64_t>(cap, plan->cand_cap))};
             use_direct = true;
+        } else if (!finishes_all(plan, timed)) {
+            direct = DirectOut{ws.d_h_final, kFinishSmall};
+            use_direct = staged = true;
         }
         (void)hipGetLastError();  // a pageable destination is not an error
     }
@@ -805,8 +837,22 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
     plan->last_nb = g.nb;
     plan->searched = true;
     if (use_direct) {
-        const hipError_t e = hipStreamSynchronize(st);
-        s = e != hipSuccess ? hip_fail(plan, e, "search") : count_status(plan, ws, cap, ncands);
+        hipError_t e = hipStreamSynchronize(st);
+        if (e != hipSuccess) {
+            s = hip_fail(plan, e, "search");
+        } else if (long_list(plan, ws) && !finishes_all(plan, timed)) {
+            s = finish_rest(plan, ws, plan->nsamp, staged ? nullptr : &direct, st);
+            if (s == FDAS_OK && staged) {
+                s = copy_candidates(plan, ws, cands_host, cap, ncands, st);
+            } else if (s == FDAS_OK) {
+                e = hipStreamSynchronize(st);
+                s = e != hipSuccess ? hip_fail(plan, e, "search") : count_status(plan, ws, cap, ncands);
+            }
+        } else {
+            const int64_t n = std::min<int64_t>(std::min<int64_t>(ws.h_count[0], plan->cand_cap), cap);
+            if (staged && n > 0) std::memcpy(cands_host, ws.h_final, size_t(n) * sizeof(fdas_cand));
+            s = count_status(plan, ws, cap, ncands);
+        }
     } else {
         s = collect(plan, ws, cands_host, cap, ncands, st);
     }

@@ -75,14 +75,16 @@ constexpr double gm_tap_scale(bool bf16) { return bf16 ? 1.0 : 16.0; }
 // Word k = (Re, Im) of Xhat[k] as two 16-bit floats, Re in the low half.
 template <bool BF16>
 __global__ __launch_bounds__(256) void k_lowp_spectrum(const float2 *__restrict__ X, const double *__restrict__ med,
-                                                       int W, int64_t nb, uint32_t *__restrict__ out) {
+                                                       int W, int64_t nb, uint32_t *__restrict__ out,
+                                                       uint32_t *__restrict__ counters) {
+    if (blockIdx.x == 0 && threadIdx.x < 6) counters[threadIdx.x] = 0u;
     const int64_t g = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (g >= nb) return;
     float2 x = X[g];
     if (med) {
         const int64_t nblk = (nb + W - 1) / W;
         const double mk = median_curve(med, nblk, W, nb, g);
-        const float sc = mk > 0.0 ? float(sqrt(kLn2 / mk)) : 0.f;
+        const float sc = float(norm_scale(mk));
         x = make_float2(x.x * sc, x.y * sc);
     }
     out[g] = uint32_t(to_half_bits<BF16>(x.x)) | (uint32_t(to_half_bits<BF16>(x.y)) << 16);
@@ -303,11 +305,11 @@ void build_gemm_bank(const double *taps, int nz, int h, bool bf16, void *out) {
 }
 
 hipError_t launch_lowp_spectrum(const float2 *X, const double *med, int W, int64_t nb, bool bf16, uint32_t *out,
-                                hipStream_t st) {
+                                uint32_t *counters, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
     const dim3 grid(unsigned((nb + 255) / 256));
-    if (bf16) hipLaunchKernelGGL(k_lowp_spectrum<true>, grid, dim3(256), 0, st, X, med, W, nb, out);
-    else hipLaunchKernelGGL(k_lowp_spectrum<false>, grid, dim3(256), 0, st, X, med, W, nb, out);
+    if (bf16) hipLaunchKernelGGL(k_lowp_spectrum<true>, grid, dim3(256), 0, st, X, med, W, nb, out, counters);
+    else hipLaunchKernelGGL(k_lowp_spectrum<false>, grid, dim3(256), 0, st, X, med, W, nb, out, counters);
     return hipGetLastError();
 }
 

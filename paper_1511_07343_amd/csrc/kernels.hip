@@ -8,6 +8,7 @@
 #include "fft_wg.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace fdas {
@@ -365,7 +366,7 @@ __device__ __forceinline__ void segfft_item(float2 *lds, int t, const float2 *__
             x = X[g];
             if (med) {
                 const double mk = median_curve(med, nblk, W, nb, g);
-                const float sc = mk > 0.0 ? float(sqrt(kLn2 / mk)) : 0.f;
+                const float sc = float(norm_scale(mk));
                 x = make_float2(x.x * sc, x.y * sc);
             }
         }
@@ -380,8 +381,10 @@ template <int LOG2S>
 __global__ __launch_bounds__(fft_threads(LOG2S)) void k_segfft(const float2 *__restrict__ X,
                                                                const double *__restrict__ med,
                                                                int W, int64_t nb, int h,
-                                                               float2 *__restrict__ segspec) {
+                                                               float2 *__restrict__ segspec,
+                                                               uint32_t *__restrict__ counters) {
     using Sh = FftShape<LOG2S, fft_threads(LOG2S)>;
+    if (blockIdx.x == 0 && threadIdx.x < 6) counters[threadIdx.x] = 0u;
     // From 8192 points the one-round exchange (S float2 of LDS) would hold a
     // compute unit to two workgroups, fewer than its registers allow, and
     // the 527 segments of a 2^23-sample series would take two rounds of
@@ -399,7 +402,7 @@ __global__ __launch_bounds__(256) void k_normalise(const float2 *__restrict__ X,
     if (g >= nb) return;
     const int64_t nblk = (nb + W - 1) / W;
     const double mk = median_curve(med, nblk, W, nb, g);
-    const float sc = mk > 0.0 ? float(sqrt(kLn2 / mk)) : 0.f;
+    const float sc = float(norm_scale(mk));
     const float2 x = X[g];
     out[g] = make_float2(x.x * sc, x.y * sc);
 }
@@ -1355,10 +1358,11 @@ hipError_t launch_median(const float2 *X, int64_t nb, double *med, int W, hipStr
 }
 
 hipError_t launch_segfft(const float2 *X, const double *med, int W, int64_t nb, int log2s, int h,
-                         int64_t nseg, float2 *segspec, hipStream_t st) {
-    if (nseg <= 0) return hipSuccess;
+                         int64_t nseg, float2 *segspec, uint32_t *counters, hipStream_t st) {
+    if (nseg <= 0) return hipErrorInvalidValue;
 #define CALL(L) \
-    hipLaunchKernelGGL((k_segfft<L>), dim3(unsigned(nseg)), dim3(fft_threads(L)), 0, st, X, med, W, nb, h, segspec);
+    hipLaunchKernelGGL((k_segfft<L>), dim3(unsigned(nseg)), dim3(fft_threads(L)), 0, st, X, med, W, nb, h, segspec, \
+                       counters);
     FDAS_SWITCH_LOG2(log2s, CALL)
 #undef CALL
     return hipGetLastError();
@@ -1428,7 +1432,9 @@ hipError_t launch_harmsum(const float *plane, const uint8_t *codes, int nz, int6
     uint32_t *group_map = reinterpret_cast<uint32_t *>(blocks + cell_cap / 2);
     const int64_t rows = SC_TZ, cols = int64_t(SC_WAVE_COLS) * SC_WAVES;
     const dim3 grid1(unsigned((nb + cols - 1) / cols), unsigned((nz + rows - 1) / rows));
-    const unsigned grid2 = 2048;
+    // a step of the exact sums and the neighbour test for every 2^14 plane
+    // cells, so that a small plane's launches are small too
+    const unsigned grid2 = unsigned(std::min<int64_t>(2048, std::max<int64_t>(64, (int64_t(nz) * nb) >> 14)));
 #define CALL(LV)                                                                                                   \
     hipLaunchKernelGGL((k_screen<LV>), grid1, dim3(64 * SC_WAVES), 0, st, codes, nz, nb, izc, T, groups, blocks,    \
                        group_map, count, group_cap, cell_cap);                                                     \

@@ -38,9 +38,9 @@ hipError_t launch_median(const float2 *X, int64_t nb, double *med, int W, hipStr
 // Segment spectra: seg s = DFT_S of Xhat[s L - h + n], n in [0, S), where
 // L = (S - 2h) rounded down to a multiple of 4, Xhat = X sqrt(ln2 / m(k)) (m
 // interpolated between block medians in FP64; med == nullptr means X is
-// already normalised); zero outside [0, nb).
+// already normalised); zero outside [0, nb).  Also clears counters[0..5].
 hipError_t launch_segfft(const float2 *X, const double *med, int W, int64_t nb, int log2s, int h,
-                         int64_t nseg, float2 *segspec, hipStream_t st);
+                         int64_t nseg, float2 *segspec, uint32_t *counters, hipStream_t st);
 
 // Xhat = X sqrt(ln2 / m(k)) into out (inspection; the search fuses it).
 hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t nb, float2 *out, hipStream_t st);
@@ -70,8 +70,9 @@ int gemm_ksteps(int h);
 size_t gemm_bank_bytes(int nz, int h);
 void build_gemm_bank(const double *taps, int nz, int h, bool bf16, void *out);
 // Xhat = X sqrt(ln2 / m(k)) (or X when med is NULL) as 16-bit (Re, Im) pairs.
+// Also clears counters[0..5].
 hipError_t launch_lowp_spectrum(const float2 *X, const double *med, int W, int64_t nb, bool bf16, uint32_t *out,
-                                hipStream_t st);
+                                uint32_t *counters, hipStream_t st);
 // plane[iz][k] = |sum_q Xhat[k - q] T_iz[q]|^2 and its block screening codes
 // (as launch_correlate), over `workgroups` persistent workgroups.  nb % 512 == 0.
 hipError_t launch_corr_gemm(const uint32_t *xl, int64_t nb, int h, const void *bank, int nz, bool bf16,
@@ -108,14 +109,30 @@ hipError_t launch_copy_records(const fdas_cand *src, const uint32_t *count, uint
 // Candidate finishing: sort the first min(*count, cap) records by
 // (nharm, k, iz) (k < nb plane columns, iz < nz) and write the first
 // min(*count, cap, out_cap) of them as public records (r = k / (nharm cpb)
-// with cpb plane columns per bin, z, FP64 significance) to out; with
-// count_dst, also count[0..5] there (out and count_dst may be device aliases
-// of page-locked host memory).
+// with cpb plane columns per bin; z = (-zmax + iz dz) / nharm, or for the
+// time-domain search alpha r with alpha = -zmax + iz dz, 0 for one trial; FP64
+// significance) to out; with count_dst, also count[0..5] there (out and
+// count_dst may be device aliases of page-locked host memory).
+struct FinishArgs {
+    const DevCand *dc;
+    const uint32_t *count;
+    uint32_t cap;
+    int nz;
+    int64_t nb;
+    int cpb;
+    bool td;
+    double zmax, dz;
+    fdas_cand *out;
+    uint32_t out_cap;
+    uint32_t *count_dst;
+};
+// Lists of at most this many records are finished by launch_finish_small;
+// launch_finish_large does the longer ones, and nothing for the others.
 // scratch: cand_sort_scratch_bytes(cap) bytes.
+constexpr uint32_t kFinishSmall = 4096;
 size_t cand_sort_scratch_bytes(uint32_t cap);
-hipError_t launch_finish_candidates(const DevCand *dc, const uint32_t *count, uint32_t cap, void *scratch, int nz,
-                                    int64_t nb, int cpb, double zmax, double dz, fdas_cand *out, hipStream_t st,
-                                    uint32_t out_cap = 0xffffffffu, uint32_t *count_dst = nullptr);
+hipError_t launch_finish_small(const FinishArgs &a, hipStream_t st);
+hipError_t launch_finish_large(const FinishArgs &a, void *scratch, hipStream_t st);
 
 // De-dispersion: out[i][t] = sum_c fil[c][t + d[i][c]] for t < nout
 // (channel-major 8-bit filterbank, nchan x nsamp; exact integer sums stored
@@ -129,13 +146,10 @@ hipError_t launch_dedisperse(const uint8_t *fil, int nchan, int64_t nsamp, doubl
 // Time-domain resampling search: y = x resampled for drift alpha (relative
 // to the mean frequency; linear interpolation, FP64 positions); normalised
 // powers |X|^2 ln2 / m(k) of one trial into a plane row with their 2-bin
-// codes (nb % 4 == 0); candidate drift z = alpha(iz) r with alpha(iz) =
-// -alpha_max + iz 2 alpha_max / (nalpha - 1).
+// codes (nb % 4 == 0).
 hipError_t launch_td_resample(const float *x, int64_t nsamp, double alpha, float *y, hipStream_t st);
 hipError_t launch_td_power(const float2 *X, const double *med, int W, int64_t nb, float *row, uint8_t *qrow,
                            float code_inv, hipStream_t st);
-hipError_t launch_td_drift(const uint32_t *count, uint32_t cap, double alpha_max, int nalpha, fdas_cand *cands,
-                           hipStream_t st);
 
 // Candidate refinement (Fourier interpolation off the grid): for each of the
 // first min(*count, cap) public records, a pattern search over the

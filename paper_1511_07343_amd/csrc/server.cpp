@@ -173,8 +173,12 @@ static void scheduler(fdas_server_s *sv) {
                             res.error = "page-locked result buffer allocation failed";
                             finished = true;
                         } else {
-                            e = hipMemcpyAsync(sl.out.p, ws.final, size_t(sl.n) * sizeof(fdas_cand),
-                                               hipMemcpyDeviceToHost, sl.stream);
+                            if (long_list(sv->core, ws) && !finishes_all(sv->core, false) &&
+                                finish_rest(sv->core, ws, sl.req.nsamp, nullptr, sl.stream) != FDAS_OK)
+                                e = hipErrorUnknown;
+                            if (e == hipSuccess)
+                                e = hipMemcpyAsync(sl.out.p, ws.final, size_t(sl.n) * sizeof(fdas_cand),
+                                                   hipMemcpyDeviceToHost, sl.stream);
                         }
                     }
                     if (!finished) {
@@ -305,7 +309,6 @@ static void scheduler(fdas_server_s *sv) {
                                                  cols_per_bin(sv->core));
                 s = enqueue_search(sv->core, buf->ws, g, FDAS_IN_SERIES_F32, buf->series, buf->ws.plane,
                                    buf->ws.cands, buf->ws.count, st);
-                if (s == FDAS_OK) e = hipMemcpyAsync(buf->ws.h_count, buf->ws.count, 24, hipMemcpyDeviceToHost, st);
             }
             if (e == hipSuccess && s == FDAS_OK) e = hipEventRecord(free_slot->done, st);
             if (e != hipSuccess || s != FDAS_OK) {

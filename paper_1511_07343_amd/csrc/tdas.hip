@@ -1,8 +1,8 @@
 // Time-domain resampling acceleration search (the other method of Sec. 1:
 // resample the series for each acceleration trial, then one long DFT each).
 // The DFT, the block medians and the harmonic sums are the FDAS kernels; this
-// file holds the resampling, the normalised powers with their screening codes
-// and the drift of the reported candidates.
+// file holds the resampling and the normalised powers with their screening
+// codes.
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -61,20 +61,6 @@ __global__ __launch_bounds__(256) void k_td_power(const float2 *__restrict__ X, 
     }
 }
 
-// Candidate drift of a time-domain search: z = alpha(iz) r, alpha(iz) =
-// -alpha_max + iz d (0 for a single trial).
-__global__ __launch_bounds__(256) void k_td_drift(const uint32_t *__restrict__ count, uint32_t cap, double alpha_max,
-                                                  double d, int single, fdas_cand *__restrict__ cands) {
-    // -alpha_max + d iz with two roundings, as the trials are formed (a fused
-    // multiply-add would round once and can differ in the last bit)
-#pragma clang fp contract(off)
-    const uint32_t n = min(*count, cap);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const double a = single ? 0.0 : -alpha_max + d * double(cands[i].iz);
-        cands[i].z = a * cands[i].r;
-    }
-}
-
 unsigned grid_for(int64_t items) {
     const int64_t g = (items + 255) / 256;
     return unsigned(g < 4096 ? (g > 0 ? g : 1) : 4096);
@@ -92,15 +78,6 @@ hipError_t launch_td_power(const float2 *X, const double *med, int W, int64_t nb
                            float code_inv, hipStream_t st) {
     if (nb <= 0 || nb % 4 != 0 || W <= 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_td_power, dim3(grid_for(nb / 4)), dim3(256), 0, st, X, med, W, nb, row, qrow, code_inv);
-    return hipGetLastError();
-}
-
-hipError_t launch_td_drift(const uint32_t *count, uint32_t cap, double alpha_max, int nalpha, fdas_cand *cands,
-                           hipStream_t st) {
-    if (cap == 0) return hipSuccess;
-    const double d = nalpha > 1 ? 2.0 * alpha_max / double(nalpha - 1) : 0.0;
-    hipLaunchKernelGGL(k_td_drift, dim3(grid_for(cap)), dim3(256), 0, st, count, cap, alpha_max, d, nalpha == 1 ? 1 : 0,
-                       cands);
     return hipGetLastError();
 }
 
