@@ -129,7 +129,7 @@ extern "C" fdas_status fdas_autotune(const fdas_bank *bank, int64_t nsamp, const
         st = fdas_plan(bank, nsamp, seg, &o, &p);
         if (st != FDAS_OK) continue;
         for (int32_t tpb : tpbs) {
-            p->tpb = tpb;
+            p->tpb = p->opts.templates_per_block = tpb;
             double score = INFINITY;
             if (persistent) {
                 score = persistent_score(p, dx, nsamp);

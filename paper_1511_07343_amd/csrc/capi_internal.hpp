@@ -50,7 +50,10 @@ struct Workspace {
     uint32_t *h_count = nullptr, *d_h_count = nullptr;
     fdas_cand *h_final = nullptr, *d_h_final = nullptr;
     float *series = nullptr;      // graph input: the trial is copied here first (batched path)
-    float *resampled = nullptr;   // time-domain search: the series resampled for one trial
+    // Time-domain search: trials whose spectra are formed together (Z, work, X
+    // and med hold so many), and the series resampled for each.
+    int td_batch = 1;
+    float *resampled = nullptr;
 };
 
 }  // namespace fdas
@@ -164,8 +167,8 @@ fdas_status make_plan_core(const fdas_bank_s *bank, int64_t nsamp, int32_t seg, 
                            fdas_plan_s **out);
 fdas_status collect(fdas_plan_s *p, Workspace &ws, fdas_cand *out, int64_t cap, int64_t *ncands, hipStream_t st);
 
-// Templates per correlation workgroup: about 13, with the number of template
-// blocks rounded up to a multiple of the 8 XCDs.
+// Templates per correlation tile of the persistent batch: about 13, with the
+// number of template blocks rounded up to a multiple of the 8 XCDs.
 inline int32_t default_tpb(int32_t nz) {
     int64_t nzb = (nz + 12) / 13;
     nzb = ((nzb + 7) / 8) * 8;

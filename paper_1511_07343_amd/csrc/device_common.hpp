@@ -11,25 +11,26 @@ constexpr double kLn2 = 0.69314718055994530942;
 
 // m(k): block medians joined linearly between block centres, flat outside.
 // Bin numbers fit 32 bits (a spectrum has at most 2^25 bins), whose
-// conversions to and from FP64 are single instructions.
+// conversions to and from FP64 are single instructions; no branches, so that
+// the loads of several bins are in flight together.
 __device__ __forceinline__ double median_curve(const double *__restrict__ med, int64_t nblk, int W,
                                                int64_t nb, int64_t g) {
+    const int last = int(nblk) - 1;
     const double c0 = 0.5 * double(min(W, int(nb)) - 1);
-    const int w0 = int(nblk - 1) * W;  // first bin of the last block
+    const int w0 = last * W;  // first bin of the last block
     const double cl = double(w0) + 0.5 * double(int(nb) - w0 - 1);
     const double x = double(int(g));
-    if (x <= c0 || nblk == 1) return med[0];
-    if (x >= cl) return med[nblk - 1];
     // W is a power of two, so dividing by it is the exact multiply by 1 / W;
     // the last interval (to the centre of a partial last block) is shorter,
     // and its reciprocal width does not depend on g (computed once per
     // thread when inlined in a loop)
     const double inv_w = 1.0 / double(W);
-    const double inv_last = 1.0 / (cl - (c0 + double(int(nblk) - 2) * double(W)));
-    const int b = int(floor((x - c0) * inv_w));
+    const double inv_last = 1.0 / (cl - (c0 + double(last - 1) * double(W)));
+    const int b = max(0, min(int(floor((x - c0) * inv_w)), last - 1));
+    const double lo = med[b], hi = med[min(b + 1, last)];
     const double cb = c0 + double(b) * double(W);
-    const double f = (x - cb) * (b + 1 == nblk - 1 ? inv_last : inv_w);
-    return med[b] + (med[b + 1] - med[b]) * f;
+    const double f = (x - cb) * (b + 1 == last ? inv_last : inv_w);
+    return x <= c0 ? lo : x >= cl ? hi : lo + (hi - lo) * f;
 }
 
 // The normalising factor sqrt(ln 2 / m) in FP64 (0 where m is not positive):

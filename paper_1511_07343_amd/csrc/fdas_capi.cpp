@@ -169,14 +169,12 @@ static fdas_status enqueue_td_search(fdas_plan_s *p, const Workspace &ws, const 
     auto mark = [&](int i) -> hipError_t { return timed ? hipEventRecord(p->tev[size_t(i)], st) : hipSuccess; };
     hipError_t e = mark(0);
     const float *x = static_cast<const float *>(in_dev);
-    for (int32_t iz = 0; iz < p->nz && e == hipSuccess; ++iz) {
-        const double alpha = row_value(p, iz);
-        e = launch_td_resample(x, g.nsamp, alpha, ws.resampled, st);
-        if (e == hipSuccess) e = launch_r2c_packed(ws.resampled, g.nsamp, ws.Z, ws.work, st);
-        if (e == hipSuccess) e = launch_unpack_median(ws.Z, g.nsamp, ws.X, ws.med, p->W, st);
-        if (e == hipSuccess)
-            e = launch_td_power(ws.X, ws.med, p->W, g.nb, plane + int64_t(iz) * g.nb, ws.codes + int64_t(iz) * (g.nb / 2),
-                                p->code_inv, st);
+    for (int32_t iz = 0; iz < p->nz && e == hipSuccess; iz += ws.td_batch) {
+        const int n = std::min(ws.td_batch, p->nz - iz);
+        e = launch_td_resample(x, g.nsamp, p->zmax, p->dz, p->nz, iz, n, ws.resampled, st);
+        if (e == hipSuccess) e = launch_r2c_packed(ws.resampled, g.nsamp, ws.Z, ws.work, st, n);
+        if (e == hipSuccess) e = launch_unpack_median(ws.Z, g.nsamp, ws.X, ws.med, p->W, st, n);
+        if (e == hipSuccess) e = launch_td_power(ws.X, ws.med, p->W, g.nb, iz, n, plane, ws.codes, p->code_inv, st);
     }
     if (e != hipSuccess) return hip_fail(p, e, "time-domain spectra");
     for (int i = 1; i <= 4 && e == hipSuccess; ++i) e = mark(i);
@@ -233,7 +231,7 @@ fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &
         e = launch_segfft(X, med, p->W, g.nb, p->log2s, p->h, g.nseg, ws.seg, dcount, st);
         if (e != hipSuccess) return hip_fail(p, e, "segment DFT");
         if ((e = mark(3)) != hipSuccess) return hip_fail(p, e, "timing event");
-        e = launch_correlate(ws.seg, p->d_bank, p->d_bank_half, p->nz, p->tpb, g.nb, p->log2s, p->h, g.nseg, plane,
+        e = launch_correlate(ws.seg, p->d_bank, p->d_bank_half, p->nz, p->opts.templates_per_block, g.nb, p->log2s, p->h, g.nseg, plane,
                              ws.codes,
                              p->code_inv, st);
         if (e != hipSuccess) return hip_fail(p, e, "correlate");
@@ -339,7 +337,22 @@ static void free_workspace(Workspace &ws) {
     ws = Workspace{};
 }
 
+// Trials of a time-domain search whose spectra are formed together: enough
+// to fill the GPU (2^24 samples), and no more than 16 (2^20 samples: 36 us a
+// trial one at a time, 13 us sixteen at a time).
+static int td_trials_together(const fdas_plan_s *p, int64_t nsamp) {
+    return int(std::min<int64_t>(p->nz, std::max<int64_t>(1, std::min<int64_t>(16, (int64_t(1) << 24) / nsamp))));
+}
+
+static fdas_status try_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp, int together);
+
 fdas_status alloc_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp) {
+    const int together = p->td ? td_trials_together(p, nsamp) : 1;
+    const fdas_status s = try_workspace(p, ws, nsamp, together);
+    return s == FDAS_E_NOMEM && together > 1 ? try_workspace(p, ws, nsamp, 1) : s;
+}
+
+static fdas_status try_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp, int together) {
     const Geometry g = make_geometry(nsamp, p->S, p->h, p->W, cols_per_bin(p));
     const int64_t M = g.nb;
     hipError_t e;
@@ -353,11 +366,12 @@ fdas_status alloc_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp) {
             return FDAS_E_NOMEM;                                                    \
         }                                                                           \
     } while (0)
-    FDAS_ALLOC(ws.Z, M * 8);
-    FDAS_ALLOC(ws.work, M * 8);
-    FDAS_ALLOC(ws.X, M * 8);
-    FDAS_ALLOC(ws.med, g.nblk * 8);
-    if (p->td) FDAS_ALLOC(ws.resampled, nsamp * 4);
+    ws.td_batch = together;
+    FDAS_ALLOC(ws.Z, M * 8 * together);
+    FDAS_ALLOC(ws.work, M * 8 * together);
+    FDAS_ALLOC(ws.X, M * 8 * together);
+    FDAS_ALLOC(ws.med, g.nblk * 8 * together);
+    if (p->td) FDAS_ALLOC(ws.resampled, nsamp * 4 * together);
     else FDAS_ALLOC(ws.seg, g.nseg * int64_t(p->S) * 8);
     FDAS_ALLOC(ws.plane, int64_t(p->nz) * g.ncol * 4);
     FDAS_ALLOC(ws.codes, int64_t(p->nz) * (g.ncol / 2));
@@ -742,7 +756,8 @@ int64_t fdas_plan_device_bytes(const fdas_plan_t *plan) {
         if (ws.nsamp) {
             const Geometry g = make_geometry(ws.nsamp, plan->S, plan->h, plan->W, cols_per_bin(plan));
             b += series_bytes(g, plan->S, plan->nz) + candidate_bytes(plan, g);
-            if (plan->td) b += ws.nsamp * 4;  // the resampled series
+            if (plan->td)  // the resampled series, and the buffers of trials formed together
+                b += ws.td_batch * ws.nsamp * 4 + (ws.td_batch - 1) * (3 * g.nb * 8 + g.nblk * 8);
         }
     }
     return b;

@@ -79,6 +79,7 @@ __global__ __launch_bounds__(fft_threads(LOG2S)) void k_dft(const float2 *__rest
 
 // ------------------------------------------------------- real input DFT
 // z[n] = x[2n] + i x[2n+1] is read as float2 directly from the series.
+// blockIdx.y numbers series of M points laid out one after the other.
 
 // M = 2^LOG2M <= 8192: one workgroup.
 template <int LOG2M>
@@ -87,6 +88,8 @@ __global__ __launch_bounds__(fft_threads(LOG2M)) void k_r2c_small(const float2 *
     using Sh = FftShape<LOG2M, fft_threads(LOG2M)>;
     __shared__ float2 lds[Sh::LDS_FLOAT2];
     const int t = threadIdx.x;
+    z += int64_t(blockIdx.y) << LOG2M;
+    Z += int64_t(blockIdx.y) << LOG2M;
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
@@ -117,6 +120,8 @@ __global__ __launch_bounds__(fft_threads(LOG2M1)) void k_r2c_cols(const float2 *
     const int64_t M2 = int64_t(1) << log2m2;
     const int64_t M = M2 << LOG2M1;
     const int64_t n2 = xcd_spread(blockIdx.x, gridDim.x);  // adjacent columns share lines
+    z += int64_t(blockIdx.y) * M;
+    work += int64_t(blockIdx.y) * M;
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
@@ -143,6 +148,8 @@ __global__ __launch_bounds__(fft_threads(LOG2M2)) void k_r2c_rows(const float2 *
     __shared__ float2 lds[Sh::LDS_FLOAT2];
     const int t = threadIdx.x;
     const int64_t k1 = xcd_spread(blockIdx.x, gridDim.x);  // adjacent rows' outputs share lines
+    work += int64_t(blockIdx.y) << (LOG2M2 + log2m1);
+    Z += int64_t(blockIdx.y) << (LOG2M2 + log2m1);
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
@@ -176,6 +183,8 @@ __global__ __launch_bounds__(fft_threads(LOG2M1) * kR2cGroup) void k_r2c_cols4(c
     const int64_t M2 = int64_t(1) << log2m2;
     const int64_t M = M2 << LOG2M1;
     const int64_t n2 = xcd_spread(blockIdx.x, gridDim.x) * kR2cGroup + c;  // adjacent groups share lines
+    z += int64_t(blockIdx.y) * M;
+    work += int64_t(blockIdx.y) * M;
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
@@ -202,6 +211,8 @@ __global__ __launch_bounds__(fft_threads(LOG2M2) * kR2cGroup) void k_r2c_rows4(c
     const int c = threadIdx.x & (kR2cGroup - 1);
     const int t = threadIdx.x / kR2cGroup;
     const int64_t k1 = xcd_spread(blockIdx.x, gridDim.x) * kR2cGroup + c;
+    work += int64_t(blockIdx.y) << (LOG2M2 + log2m1);
+    Z += int64_t(blockIdx.y) << (LOG2M2 + log2m1);
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
@@ -300,7 +311,7 @@ __device__ double median_select(const uint32_t *u, int n, SelectScratch &sc) {
 constexpr int kMaxW = 8192;
 
 // One workgroup per block of W bins: X[k] from Z[k] and Z[M - k], then the
-// block's median power.
+// block's median power.  blockIdx.y numbers spectra laid out one after the other.
 __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__restrict__ Z,
                                                                int64_t M, float2 *__restrict__ X,
                                                                double *__restrict__ med, int W) {
@@ -309,6 +320,9 @@ __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__r
     const int t = threadIdx.x;
     const int64_t b0 = int64_t(blockIdx.x) * W;
     const int w = int(min(int64_t(W), M - b0));
+    Z += int64_t(blockIdx.y) * M;
+    X += int64_t(blockIdx.y) * M;
+    med += int64_t(blockIdx.y) * gridDim.x;
     const double inv_n = 1.0 / double(2 * M);
     for (int i = t; i < w; i += kMedThreads) {
         const int64_t k = b0 + i;
@@ -352,33 +366,47 @@ __device__ __forceinline__ void segfft_item(float2 *lds, int t, const float2 *__
                                             const double *__restrict__ med, int W, int64_t nb, int h, int64_t s,
                                             float2 *__restrict__ segspec) {
     using Sh = FftShape<LOG2S, fft_threads(LOG2S)>;
-    const int64_t L = seg_valid(Sh::S, h);
-    const int64_t g0 = s * L - h;
+    const int g0 = int(s * seg_valid(Sh::S, h)) - h;
     const int64_t nblk = (nb + W - 1) / W;
-    Twiddles<Sh, -1> tw;
-    tw.init(t);
+    // The normalising factors first, in batches whose FP64 temporaries bound
+    // the registers; then all the points' loads go out before the first is
+    // used (bins before or past the spectrum are outside the buffer and read 0).
+    const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(X, int(8 * nb));
+    float sc[Sh::R];
+    if (med) {
+        constexpr int BATCH = Sh::R < 8 ? Sh::R : 8;
+        static_for<0, Sh::R / BATCH>([&](auto hc) {
+            constexpr int m0 = decltype(hc)::value * BATCH;
+            int tb = t;
+            asm volatile("" : "+v"(tb));  // no batch's addresses are formed ahead
+#pragma unroll
+            for (int m = m0; m < m0 + BATCH; ++m) {
+                const int g = g0 + tb + Sh::NT * m;
+                const float f = float(norm_scale(median_curve(med, nblk, W, nb, max(0, min(g, int(nb) - 1)))));
+                sc[m] = g >= 0 && g < nb ? f : 0.f;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    } else {
+#pragma unroll
+        for (int m = 0; m < Sh::R; ++m) sc[m] = 1.f;
+    }
     float2 v[Sh::R];
 #pragma unroll
-    for (int m = 0; m < Sh::R; ++m) {
-        const int64_t g = g0 + t + Sh::NT * m;
-        float2 x = make_float2(0.f, 0.f);
-        if (g >= 0 && g < nb) {
-            x = X[g];
-            if (med) {
-                const double mk = median_curve(med, nblk, W, nb, g);
-                const float sc = float(norm_scale(mk));
-                x = make_float2(x.x * sc, x.y * sc);
-            }
-        }
-        v[m] = x;
-    }
+    for (int m = 0; m < Sh::R; ++m) v[m] = buffer_load_f2(rx, g0 + t + Sh::NT * m, 0);
+#pragma unroll
+    for (int m = 0; m < Sh::R; ++m) v[m] = make_float2(v[m].x * sc[m], v[m].y * sc[m]);
+    int tw_t = t;
+    asm volatile("" : "+v"(tw_t));  // the twiddles take their registers after the scaling has left its own
+    Twiddles<Sh, -1> tw;
+    tw.init(tw_t);
     fft_wg<Sh, -1, SPLIT>(v, lds, tw, t);
 #pragma unroll
     for (int m = 0; m < Sh::R; ++m) segspec[s * Sh::S + t + Sh::NT * m] = v[m];
 }
 
 template <int LOG2S>
-__global__ __launch_bounds__(fft_threads(LOG2S)) void k_segfft(const float2 *__restrict__ X,
+__global__ __launch_bounds__(fft_threads(LOG2S), LOG2S == 13 ? 3 : 2) void k_segfft(const float2 *__restrict__ X,
                                                                const double *__restrict__ med,
                                                                int W, int64_t nb, int h,
                                                                float2 *__restrict__ segspec,
@@ -1302,13 +1330,13 @@ hipError_t launch_dft(int log2n, int dir, int64_t batch, const float2 *in, float
     return hipGetLastError();
 }
 
-hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st) {
+hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch) {
     const float2 *z = reinterpret_cast<const float2 *>(x);
     int log2m = 0;
     while ((int64_t(1) << log2m) < nsamp / 2) ++log2m;
-    if ((int64_t(1) << log2m) != nsamp / 2 || log2m < 6 || log2m > 26) return hipErrorInvalidValue;
+    if ((int64_t(1) << log2m) != nsamp / 2 || log2m < 6 || log2m > 26 || batch < 1) return hipErrorInvalidValue;
     if (log2m <= 13) {
-#define CALL(L) hipLaunchKernelGGL((k_r2c_small<L>), dim3(1), dim3(fft_threads(L)), 0, st, z, Z);
+#define CALL(L) hipLaunchKernelGGL((k_r2c_small<L>), dim3(1, unsigned(batch)), dim3(fft_threads(L)), 0, st, z, Z);
         FDAS_SWITCH_LOG2(log2m, CALL)
 #undef CALL
         return hipGetLastError();
@@ -1316,35 +1344,36 @@ hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *w
     const int l1 = (log2m + 1) / 2, l2 = log2m / 2;  // 7 <= l2 <= l1 <= 13
     const unsigned ncols = 1u << l2, nrows = 1u << l1;
     if (l1 <= 11) {  // four columns per workgroup (ncols is a multiple of 4)
-#define CALL(L) hipLaunchKernelGGL((k_r2c_cols4<L>), dim3(ncols / kR2cGroup), dim3(fft_threads(L) * kR2cGroup), 0, st, \
+#define CALL(L) hipLaunchKernelGGL((k_r2c_cols4<L>), dim3(ncols / kR2cGroup, unsigned(batch)), dim3(fft_threads(L) * kR2cGroup), 0, st, \
                            z, work, l2);
         FDAS_SWITCH_LOG2_GROUPED(l1, CALL)
 #undef CALL
     } else {
-#define CALL(L) hipLaunchKernelGGL((k_r2c_cols<L>), dim3(ncols), dim3(fft_threads(L)), 0, st, z, work, l2);
+#define CALL(L) hipLaunchKernelGGL((k_r2c_cols<L>), dim3(ncols, unsigned(batch)), dim3(fft_threads(L)), 0, st, z, work, l2);
         FDAS_SWITCH_LOG2(l1, CALL)
 #undef CALL
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (l2 <= 11) {
-#define CALL(L) hipLaunchKernelGGL((k_r2c_rows4<L>), dim3(nrows / kR2cGroup), dim3(fft_threads(L) * kR2cGroup), 0, st, \
+#define CALL(L) hipLaunchKernelGGL((k_r2c_rows4<L>), dim3(nrows / kR2cGroup, unsigned(batch)), dim3(fft_threads(L) * kR2cGroup), 0, st, \
                            work, Z, l1);
         FDAS_SWITCH_LOG2_GROUPED(l2, CALL)
 #undef CALL
     } else {
-#define CALL(L) hipLaunchKernelGGL((k_r2c_rows<L>), dim3(nrows), dim3(fft_threads(L)), 0, st, work, Z, l1);
+#define CALL(L) hipLaunchKernelGGL((k_r2c_rows<L>), dim3(nrows, unsigned(batch)), dim3(fft_threads(L)), 0, st, work, Z, l1);
         FDAS_SWITCH_LOG2(l2, CALL)
 #undef CALL
     }
     return hipGetLastError();
 }
 
-hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st) {
+hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st,
+                                int batch) {
     const int64_t M = nsamp / 2;
-    if (W < 2 || W > kMaxW || (W & (W - 1))) return hipErrorInvalidValue;
+    if (W < 2 || W > kMaxW || (W & (W - 1)) || batch < 1) return hipErrorInvalidValue;
     const int64_t nblk = (M + W - 1) / W;
-    hipLaunchKernelGGL(k_unpack_median, dim3(unsigned(nblk)), dim3(kMedThreads), size_t(W) * sizeof(uint32_t), st, Z,
+    hipLaunchKernelGGL(k_unpack_median, dim3(unsigned(nblk), unsigned(batch)), dim3(kMedThreads), size_t(W) * sizeof(uint32_t), st, Z,
                        M, X, med, W);
     return hipGetLastError();
 }
@@ -1380,11 +1409,40 @@ hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t n
     return hipGetLastError();
 }
 
+// Templates per workgroup of the correlation, chosen for the launch.  Long
+// launches take about 13, with the number of template blocks a multiple of the
+// 8 XCDs.  Launches of less than 32 templates and segments for every
+// workgroup that runs at once take what a model of them says is fastest: a
+// workgroup's time is that of its templates and about half of one more (its
+// twiddles and segment), and the last workgroups run with half the GPU idle.
+// 2^17 samples, 101 templates, 2048 points: 2 instead of 13, 20 us against
+// 42; 2^18, 51, 8192: 2 instead of 7, 23 against 45; 2^20, 201, 2048: 6, 171
+// against 174; 2^22, 201, 2048 would take 7: 636 against 617 with 13.
+static int auto_tpb(int log2s, int nz, int64_t nseg) {
+    int64_t nzb = (int64_t(nz) + 12) / 13;
+    nzb = ((nzb + 7) / 8) * 8;
+    const int most = int((nz + nzb - 1) / nzb);
+    const int64_t at_once = 256 * (log2s >= 13 ? 2 : log2s == 12 ? 4 : log2s == 11 ? 8 : 16);
+    if (nseg * nz >= 32 * at_once) return most;
+    int best = most;
+    double least = INFINITY;
+    for (int tpb = 1; tpb <= std::max(most, 13); ++tpb) {
+        const double rounds = double(nseg * ((nz + tpb - 1) / tpb)) / double(at_once);
+        const double cost = (rounds <= 1.0 ? 1.0 : rounds + 0.5) * (tpb + 0.5);
+        if (cost < least) {
+            least = cost;
+            best = tpb;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_correlate(const float2 *segspec, const float2 *bank, const float2 *bank_half, int nz, int tpb,
                             int64_t nb, int log2s, int h, int64_t nseg, float *plane, uint8_t *codes, float code_inv,
                             hipStream_t st) {
     if (nseg <= 0 || nz <= 0) return hipSuccess;
-    if (tpb <= 0) return hipErrorInvalidValue;
+    if (tpb < 0) return hipErrorInvalidValue;
+    if (tpb == 0) tpb = auto_tpb(log2s, nz, nseg);
     const int64_t nzb = (nz + tpb - 1) / tpb;
     const int64_t total = nzb * nseg;
     const int64_t per = (total + kXcds - 1) / kXcds;

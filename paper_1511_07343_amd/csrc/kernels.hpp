@@ -25,12 +25,14 @@ hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t st);
 hipError_t launch_dft(int log2n, int dir, int64_t batch, const float2 *in, float2 *out, hipStream_t st);
 
 // Complex DFT of z[n] = x[2n] + i x[2n+1] (M = N/2 points) into Z, natural
-// order.  work: M float2 scratch (used when M > 8192).
-hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st);
+// order.  work: M float2 scratch (used when M > 8192).  batch: so many series
+// laid out one after the other, in x, Z and work.
+hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch = 1);
 
 // Unpack Z into the real-input spectrum X[k], k in [0, M) (X[0] = 0), and the
-// median of |X|^2 over each block of W bins (FP64 out).
-hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st);
+// median of |X|^2 over each block of W bins (FP64 out); batch as above.
+hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st,
+                                int batch = 1);
 
 // Block medians of |X|^2 of a given spectrum.
 hipError_t launch_median(const float2 *X, int64_t nb, double *med, int W, hipStream_t st);
@@ -54,6 +56,7 @@ hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t n
 // floats, the bins k from bank in [0, nb) and the points k + 1/2 from
 // bank_half in [nb, 2 nb), and the nz x nb codes cover the pairs
 // (k, k + 1/2): codes[iz][k] = max of the two points' codes.
+// tpb: templates per workgroup, 0 to have it chosen for the launch.
 hipError_t launch_correlate(const float2 *segspec, const float2 *bank, const float2 *bank_half, int nz, int tpb,
                             int64_t nb, int log2s, int h, int64_t nseg, float *plane, uint8_t *codes, float code_inv,
                             hipStream_t st);
@@ -143,13 +146,15 @@ constexpr double kDispersion = 4.148808e3;  // s MHz^2 pc^-1 cm^3
 hipError_t launch_dedisperse(const uint8_t *fil, int nchan, int64_t nsamp, double f_top, double foff, double tsamp,
                              const double *dms, int ndm, int64_t nout, float *out, hipStream_t st);
 
-// Time-domain resampling search: y = x resampled for drift alpha (relative
-// to the mean frequency; linear interpolation, FP64 positions); normalised
-// powers |X|^2 ln2 / m(k) of one trial into a plane row with their 2-bin
-// codes (nb % 4 == 0).
-hipError_t launch_td_resample(const float *x, int64_t nsamp, double alpha, float *y, hipStream_t st);
-hipError_t launch_td_power(const float2 *X, const double *med, int W, int64_t nb, float *row, uint8_t *qrow,
-                           float code_inv, hipStream_t st);
+// Time-domain resampling search, trials iz0 .. iz0 + count - 1, trial iz of
+// drift alpha = -zmax + iz dz (0 for one trial), each in its own part of y, X
+// and med: the series resampled for the drift (relative to the mean
+// frequency; linear interpolation, FP64 positions); the normalised powers
+// |X|^2 ln2 / m(k) into plane rows iz with their 2-bin codes (nb % 4 == 0).
+hipError_t launch_td_resample(const float *x, int64_t nsamp, double zmax, double dz, int nz, int iz0, int count,
+                              float *y, hipStream_t st);
+hipError_t launch_td_power(const float2 *X, const double *med, int W, int64_t nb, int iz0, int count, float *plane,
+                           uint8_t *codes, float code_inv, hipStream_t st);
 
 // Candidate refinement (Fourier interpolation off the grid): for each of the
 // first min(*count, cap) public records, a pattern search over the
