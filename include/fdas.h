@@ -335,8 +335,8 @@ fdas_status fdas_interp_power(fdas_plan_t *plan, int64_t n, const double *r, con
  * the candidates they keep (e.g. the most significant after sifting)
  * rather than every record of the search.  For input kind
  * FDAS_IN_SPECTRUM_C64_NORMALISED the caller's spectrum buffer must still
- * hold that spectrum.  Synchronous; allocates 40 n + 4 bytes of device
- * memory for the call.  INVAL if no search has completed on the plan, n < 0,
+ * hold that spectrum.  Synchronous; allocates 40 n + 512 bytes of device
+ * memory for the call, and 2096 n more for up to 2048 records.  INVAL if no search has completed on the plan, n < 0,
  * levels out of range or a record's nharm is not 1, 2, 4, 8 or 16; NOMEM if
  * the buffer cannot be allocated. */
 fdas_status fdas_refine(fdas_plan_t *plan, fdas_cand *cands, int64_t n, int32_t levels, void *hip_stream);

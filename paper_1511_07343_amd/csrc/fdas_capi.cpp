@@ -1083,21 +1083,31 @@ static fdas_status check_refine_args(const fdas_plan_t *plan, const fdas_cand *c
     return FDAS_OK;
 }
 
-// Records dc and count dn on the device (either buffer the caller provides):
-// copy in, refine, copy back, wait.
-static hipError_t refine_on_device(fdas_plan_t *plan, fdas_cand *cands, int64_t n, int32_t levels, fdas_cand *dc,
-                                   uint32_t *dn, const uint32_t *nn_host, hipStream_t st) {
+// Layout of a refinement's device buffer: the records, their count at the
+// next multiple of 256 bytes, 256 bytes further the levels' scratch.
+static size_t refine_count_at(int64_t n) { return (size_t(n) * sizeof(fdas_cand) + 255) & ~size_t(255); }
+static size_t refine_buffer_bytes(int64_t n) {
+    return refine_count_at(n) + 256 + (n <= kRefineLevelsMost ? refine_level_scratch_bytes(n) : 0);
+}
+
+// Copy the records in, refine, copy back, wait.
+static hipError_t refine_on_device(fdas_plan_t *plan, fdas_cand *cands, int64_t n, int32_t levels, void *buf,
+                                   const uint32_t *nn_host, hipStream_t st) {
     const size_t bytes = size_t(n) * sizeof(fdas_cand);
-    hipError_t e;
-    if ((e = hipMemcpyAsync(dc, cands, bytes, hipMemcpyHostToDevice, st)) == hipSuccess &&
-        (e = hipMemcpyAsync(dn, nn_host, sizeof(uint32_t), hipMemcpyHostToDevice, st)) == hipSuccess &&
-        (e = launch_refine(plan->last_X, plan->last_med, plan->W, plan->last_nb, plan->h, plan->izc, plan->dz,
-                           plan->zmax, cols_per_bin(plan), levels, dn, uint32_t(n), dc, 4 * plan->num_cu, st)) ==
-            hipSuccess &&
-        (e = hipMemcpyAsync(cands, dc, bytes, hipMemcpyDeviceToHost, st)) == hipSuccess) {
-        e = hipStreamSynchronize(st);
+    fdas_cand *dc = static_cast<fdas_cand *>(buf);
+    uint32_t *dn = reinterpret_cast<uint32_t *>(static_cast<char *>(buf) + refine_count_at(n));
+    hipError_t e = hipMemcpyAsync(dc, cands, bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && n <= kRefineLevelsMost) {
+        e = launch_refine_levels(plan->last_X, plan->last_med, plan->W, plan->last_nb, plan->h, plan->izc, plan->dz,
+                                 plan->zmax, cols_per_bin(plan), levels, n, dc, reinterpret_cast<char *>(dn) + 256, st);
+    } else if (e == hipSuccess) {
+        e = hipMemcpyAsync(dn, nn_host, sizeof(uint32_t), hipMemcpyHostToDevice, st);
+        if (e == hipSuccess)
+            e = launch_refine(plan->last_X, plan->last_med, plan->W, plan->last_nb, plan->h, plan->izc, plan->dz,
+                              plan->zmax, cols_per_bin(plan), levels, dn, uint32_t(n), dc, 4 * plan->num_cu, st);
     }
-    return e;
+    if (e == hipSuccess) e = hipMemcpyAsync(cands, dc, bytes, hipMemcpyDeviceToHost, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
 }
 
 fdas_status fdas_refine_noalloc(fdas_plan_t *plan, fdas_cand *cands, int64_t n, int32_t levels, void *hip_stream) {
@@ -1119,15 +1129,12 @@ fdas_status fdas_refine_noalloc(fdas_plan_t *plan, fdas_cand *cands, int64_t n, 
     size_t scr_bytes = 0;
     e = refine_noalloc_scratch(&scr, &scr_bytes);
     if (e != hipSuccess) return hip_fail(plan, e, "fdas_refine_noalloc: scratch address");
-    fdas_cand *dc = static_cast<fdas_cand *>(scr);
-    uint32_t *dn = reinterpret_cast<uint32_t *>(static_cast<char *>(scr) + size_t(FDAS_REFINE_NOALLOC_MAX) *
-                                                                              sizeof(fdas_cand));
-    if (size_t(FDAS_REFINE_NOALLOC_MAX) * sizeof(fdas_cand) + sizeof(uint32_t) > scr_bytes) {
+    if (refine_buffer_bytes(n) > scr_bytes) {
         set_error("fdas_refine_noalloc: scratch array too small");
         return FDAS_E_DEVICE;
     }
     const uint32_t nn = uint32_t(n);
-    e = refine_on_device(plan, cands, n, levels, dc, dn, &nn, static_cast<hipStream_t>(hip_stream));
+    e = refine_on_device(plan, cands, n, levels, scr, &nn, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return hip_fail(plan, e, "refine");
     return FDAS_OK;
 }
@@ -1137,18 +1144,15 @@ fdas_status fdas_refine(fdas_plan_t *plan, fdas_cand *cands, int64_t n, int32_t 
     if (s != FDAS_OK) return s;
     if (n == 0) return FDAS_OK;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const size_t bytes = size_t(n) * sizeof(fdas_cand);
     char *buf = nullptr;
-    hipError_t e = hipMalloc(&buf, bytes + sizeof(uint32_t));
+    hipError_t e = hipMalloc(&buf, refine_buffer_bytes(n));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         set_error("fdas_refine: device allocation failed");
         return FDAS_E_NOMEM;
     }
-    fdas_cand *dc = reinterpret_cast<fdas_cand *>(buf);
-    uint32_t *dn = reinterpret_cast<uint32_t *>(buf + bytes);
     const uint32_t nn = uint32_t(n);
-    e = refine_on_device(plan, cands, n, levels, dc, dn, &nn, st);
+    e = refine_on_device(plan, cands, n, levels, buf, &nn, st);
     const hipError_t ef = hipFree(buf);
     if (e != hipSuccess) return hip_fail(plan, e, "refine");
     if (ef != hipSuccess) return hip_fail(plan, ef, "free");

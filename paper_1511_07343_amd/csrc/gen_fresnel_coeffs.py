@@ -6,10 +6,12 @@ integrals F(x) = C(x) + i S(x), C(x) = int_0^x cos(pi t^2 / 2) dt.
   c_n = (-1)^n (pi/2)^(2n) / ((2n)! (4n + 1)),
   s_n = (-1)^n (pi/2)^(2n+1) / ((2n + 1)! (4n + 3)),
   13 terms (the last below 2e-21 at |x| = 1).
-x >= 1: the auxiliary functions f, g of F(x) = (1 + i)/2 - (g + i f) exp(i pi x^2 / 2)
-  as Chebyshev expansions in u = 1 / x^2 of the smooth, bounded functions
-  phi_f(u) = pi x f(x) and phi_g(u) = pi^2 x^3 g(x) (both -> 1 as u -> 0), on
-  the u intervals below, fitted at Chebyshev nodes from 40-digit values.
+x >= 0: the auxiliary functions f, g of F(x) = (1 + i)/2 - (g + i f) exp(i pi x^2 / 2),
+  smooth on [0, inf), as polynomials of a variable t in [-1, 1] (Chebyshev fits
+  at 40 digits, written out in powers of t):
+  x < 3: of f and g themselves in t = 2 x / 3 - 1;
+  x >= 3: of phi_f = pi x f and phi_g = pi^2 x^3 g (both -> 1 as x -> inf) in
+  t = 18 / x^2 - 1.
 
 Run: python gen_fresnel_coeffs.py  (needs mpmath; the output is committed).
 """
@@ -19,9 +21,8 @@ import mpmath as mp
 
 mp.mp.dps = 40
 
-# (u_lo, u_hi, degree), i.e. x in [4, inf), [2, 4), [sqrt 2, 2), [1, sqrt 2); the
-# degrees keep every fit within 1e-14 of the 40-digit values (checked below).
-INTERVALS = [(0.0, 1.0 / 16.0, 12), (1.0 / 16.0, 1.0 / 4.0, 18), (1.0 / 4.0, 1.0 / 2.0, 14), (1.0 / 2.0, 1.0, 16)]
+SPLIT = 3  # x at which the two fits meet: few bins of a response lie below it
+SMALL_DEGREE, TAIL_DEGREE = 28, 14  # fits within 1e-15 of the 40-digit values (checked below)
 SERIES_TERMS = 13
 
 
@@ -35,36 +36,42 @@ def fg(x):
     return f, g
 
 
-def phis(u):
+def tail(t):
+    u = (mp.mpf(t) + 1) / (2 * SPLIT ** 2)
     if u == 0:
         return mp.mpf(1), mp.mpf(1)
-    x = 1 / mp.sqrt(mp.mpf(u))
+    x = 1 / mp.sqrt(u)
     f, g = fg(x)
     return mp.pi * x * f, mp.pi ** 2 * x ** 3 * g
 
 
-def cheb(a, b, deg):
-    """Chebyshev coefficients (first-kind, on [a, b]) of phi_f and phi_g."""
+def small(t):
+    return fg((mp.mpf(t) + 1) * SPLIT / 2)
+
+
+def powers(fun, deg):
+    """Coefficients in powers of t of the Chebyshev fits of fun's two values."""
     n = deg + 1
     th = [mp.pi * (k + mp.mpf(1) / 2) / n for k in range(n)]
-    vals = [phis(mp.mpf(a) + (mp.mpf(b) - a) * (mp.cos(t) + 1) / 2) for t in th]
+    vals = [fun(mp.cos(t)) for t in th]
     out = []
     for which in (0, 1):
-        cs = []
-        for j in range(n):
-            acc = mp.fsum(v[which] * mp.cos(j * t) for v, t in zip(vals, th))
-            cs.append(2 * acc / n)
-        cs[0] /= 2
-        out.append([float(v) for v in cs])
+        total = [mp.mpf(0)] * n
+        prev, cur = [mp.mpf(1)] + [mp.mpf(0)] * deg, [mp.mpf(0), mp.mpf(1)] + [mp.mpf(0)] * (deg - 1)
+        for j in range(n):  # prev holds T_j, cur T_(j+1)
+            c = 2 * mp.fsum(v[which] * mp.cos(j * t) for v, t in zip(vals, th)) / n
+            c = c / 2 if j == 0 else c
+            total = [a + c * b for a, b in zip(total, prev)]
+            prev, cur = cur, [2 * a - b for a, b in zip([mp.mpf(0)] + cur[:-1], prev)]
+        out.append([float(v) for v in total])
     return out
 
 
-def clenshaw(cs, a, b, u):
-    t = (2 * u - (b + a)) / (b - a)
-    b1 = b2 = 0.0
-    for c in reversed(cs[1:]):
-        b1, b2 = 2 * t * b1 - b2 + c, b1
-    return t * b1 - b2 + cs[0]
+def horner(cs, t):
+    r = cs[-1]
+    for c in reversed(cs[:-1]):
+        r = r * t + c
+    return r
 
 
 def main():
@@ -73,35 +80,31 @@ def main():
                 for n in range(SERIES_TERMS)]
     series_s = [float((-1) ** n * (mp.pi / 2) ** (2 * n + 1) / (mp.factorial(2 * n + 1) * (4 * n + 3)))
                 for n in range(SERIES_TERMS)]
-    fits = [(a, b, cheb(a, b, d)) for a, b, d in INTERVALS]
+    fits = [("Small", small, powers(small, SMALL_DEGREE)), ("Tail", tail, powers(tail, TAIL_DEGREE))]
     worst = 0.0
-    for a, b, (cf, cg) in fits:
-        for i in range(1, 60):
-            u = a + (b - a) * i / 60
-            ef, eg = phis(u)
-            worst = max(worst, abs(clenshaw(cf, a, b, u) - float(ef)), abs(clenshaw(cg, a, b, u) - float(eg)))
-    assert worst < 1e-14, worst
+    for _, fun, coeffs in fits:
+        for i in range(0, 200):
+            t = -1 + 2 * (i + 0.37) / 200
+            for c, e in zip(coeffs, fun(t)):
+                worst = max(worst, abs(horner(c, t) - float(e)))
+    assert worst < 1e-15, worst
     lines = ["// Generated by gen_fresnel_coeffs.py: polynomial data of the device Fresnel",
-             "// integrals (power series below 1, Chebyshev expansions of the auxiliary",
-             f"// functions above; max fit error {worst:.1e} of phi ~ 1).  Do not edit.",
+             "// integrals (power series below 1; polynomials of the auxiliary functions",
+             f"// everywhere, max error in FP64 {worst:.1e} of values up to 1).  Do not edit.",
              "#pragma once", "", "#include <hip/hip_runtime.h>", "", "namespace fdas {",
-             "namespace fresnel_data {", "",
-             f"constexpr int kSeriesTerms = {SERIES_TERMS};"]
+             "namespace fresnel_data {", ""]
     fmt = lambda v: repr(float(v))  # noqa: E731  (round-trip exact)
     # coefficient arrays live in constant memory: read with uniform indices
-    # they become scalar loads instead of constants held in vector registers
-    lines.append("__constant__ double kSeriesC[kSeriesTerms] = {" + ", ".join(fmt(v) for v in series_c) + "};")
-    lines.append("__constant__ double kSeriesS[kSeriesTerms] = {" + ", ".join(fmt(v) for v in series_s) + "};")
-    lines.append(f"constexpr int kIntervals = {len(fits)};")
-    lines.append("constexpr double kULo[kIntervals] = {" + ", ".join(fmt(a) for a, _, _ in fits) + "};")
-    lines.append("constexpr double kUHi[kIntervals] = {" + ", ".join(fmt(b) for _, b, _ in fits) + "};")
-    for i, (a, b, (cf, cg)) in enumerate(fits):
-        lines.append(f"__constant__ double kPhiF{i}[{len(cf)}] = {{" + ", ".join(fmt(v) for v in cf) + "};")
-        lines.append(f"__constant__ double kPhiG{i}[{len(cg)}] = {{" + ", ".join(fmt(v) for v in cg) + "};")
+    # they become scalar loads, of both functions' coefficients together
+    lines.append(f"constexpr double kSplit = {SPLIT}.0;")
+    for name, first, second in ([("Series", series_c, series_s)] +
+                                [(name, cf, cg) for name, _, (cf, cg) in fits]):
+        lines.append(f"__constant__ double k{name}[{len(first)}][2] = {{" +
+                     ", ".join(f"{{{fmt(a)}, {fmt(b)}}}" for a, b in zip(first, second)) + "};")
     lines += ["", "}  // namespace fresnel_data", "}  // namespace fdas", ""]
     with open(os.path.join(here, "fresnel_coeffs.hpp"), "w") as f:
         f.write("\n".join(lines))
-    print("max fit error", worst)
+    print("max error", worst)
 
 
 if __name__ == "__main__":

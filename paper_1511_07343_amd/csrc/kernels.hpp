@@ -171,6 +171,15 @@ hipError_t refine_noalloc_scratch(void **out, size_t *bytes);
 hipError_t launch_refine(const float2 *X, const double *med, int W, int64_t nb, int h, int izc, double dz,
                          double zmax, int cpb, int levels, const uint32_t *count, uint32_t cap, fdas_cand *cands,
                          int workgroups, hipStream_t st);
+// The same, bit for bit, for n <= kRefineLevelsMost records, one launch per
+// level: faster while the records alone do not fill the GPU evenly (256
+// records, 6 levels: 658 us against 915; one: 171 against 875).  scratch_dev:
+// refine_level_scratch_bytes(n) bytes.
+constexpr int64_t kRefineLevelsMost = 2048;
+size_t refine_level_scratch_bytes(int64_t n);
+hipError_t launch_refine_levels(const float2 *X, const double *med, int W, int64_t nb, int h, int izc, double dz,
+                                double zmax, int cpb, int levels, int64_t n, fdas_cand *cands, void *scratch_dev,
+                                hipStream_t st);
 // out[i] = S(r[i], z[i]) with nh[i] harmonics (NaN when nh[i] is not in 1..16),
 // device arrays of n entries.
 hipError_t launch_interp_points(const float2 *X, const double *med, int W, int64_t nb, int h, const double *r,
