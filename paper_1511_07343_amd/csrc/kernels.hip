@@ -107,6 +107,26 @@ __device__ __forceinline__ int64_t xcd_spread(int64_t i, int64_t n) {
     return (n % kXcds == 0) ? (i % kXcds) * (n / kXcds) + i / kXcds : i;
 }
 
+// work[n2 + M2 k1] = v[m] exp(-2 pi i n2 k1 / M), k1 = t + NT m: the first
+// factor and the rotation from one to the next in FP64 (at most 15 of them, a
+// few 1e-16 each), two sines and cosines instead of one for each point (2^22
+// points: 26 us against 33).
+template <class Sh>
+__device__ __forceinline__ void r2c_twist(const float2 (&v)[Sh::R], float2 *__restrict__ work, int64_t n2, int t,
+                                          int64_t M2, int64_t M) {
+    const double inv = -2.0 / double(M);  // M is a power of two
+    double c, s, dc, ds;
+    sincospi(inv * double((n2 * t) & (M - 1)), &s, &c);
+    sincospi(inv * double((n2 * Sh::NT) & (M - 1)), &ds, &dc);
+#pragma unroll
+    for (int m = 0; m < Sh::R; ++m) {
+        work[n2 + M2 * (t + Sh::NT * m)] = cmul(v[m], make_float2(float(c), float(s)));
+        const double c1 = fma(c, dc, -(s * ds));
+        s = fma(c, ds, s * dc);
+        c = c1;
+    }
+}
+
 // Four-step M = M1 * M2 (n = n2 + M2 n1, k = k1 + M1 k2).
 // Pass A, one workgroup per column n2: DFT over n1, times exp(-2 pi i n2 k1 / M),
 // stored at work[n2 + M2 k1].
@@ -128,15 +148,7 @@ __global__ __launch_bounds__(fft_threads(LOG2M1)) void k_r2c_cols(const float2 *
 #pragma unroll
     for (int m = 0; m < Sh::R; ++m) v[m] = z[n2 + M2 * (t + Sh::NT * m)];
     fft_wg<Sh, -1>(v, lds, tw, t);
-#pragma unroll
-    for (int m = 0; m < Sh::R; ++m) {
-        const int64_t k1 = t + Sh::NT * m;
-        const int64_t idx = (n2 * k1) & (M - 1);
-        double s, c;
-        sincospi(-2.0 * double(idx) / double(M), &s, &c);
-        const float2 w = make_float2(float(c), float(s));
-        work[n2 + M2 * k1] = cmul(v[m], w);
-    }
+    r2c_twist<Sh>(v, work, n2, t, M2, M);
 }
 
 // Pass B, one workgroup per row k1: DFT over n2 -> Z[k1 + M1 k2].
@@ -191,15 +203,7 @@ __global__ __launch_bounds__(fft_threads(LOG2M1) * kR2cGroup) void k_r2c_cols4(c
 #pragma unroll
     for (int m = 0; m < Sh::R; ++m) v[m] = z[n2 + M2 * (t + Sh::NT * m)];
     fft_wg<Sh, -1>(v, lds + c * r2c_region<Sh>(), tw, t);
-#pragma unroll
-    for (int m = 0; m < Sh::R; ++m) {
-        const int64_t k1 = t + Sh::NT * m;
-        const int64_t idx = (n2 * k1) & (M - 1);
-        double s, co;
-        sincospi(-2.0 * double(idx) / double(M), &s, &co);
-        const float2 w = make_float2(float(co), float(s));
-        work[n2 + M2 * k1] = cmul(v[m], w);
-    }
+    r2c_twist<Sh>(v, work, n2, t, M2, M);
 }
 
 template <int LOG2M2>
@@ -224,49 +228,88 @@ __global__ __launch_bounds__(fft_threads(LOG2M2) * kR2cGroup) void k_r2c_rows4(c
 }
 
 // ------------------------------------------------------ medians of |X|^2
-// Order statistics of W powers in LDS by radix selection on their bit
-// patterns (non-negative floats and +inf order as their unsigned bits): four
-// passes of 8 bits, each a 256-bucket histogram and a scan that finds the
-// bucket holding the wanted rank.  The result is the exact rank-r value, as
-// a sort would give.
+// Order statistics of W powers in LDS on their bit patterns (non-negative
+// floats and +inf order as their unsigned bits; the result is the exact value
+// of a rank, as a sort would give).  One histogram of the exponents and the
+// leading three mantissa bits finds the bucket that holds the wanted rank, at
+// most 4 % of the powers of noise; its keys are listed and ranked by counting,
+// four threads to a key.  (Eight bits at a time, the exponents of 256 powers
+// fall in some five buckets, whose LDS atomics run one after the other, and
+// the other 24 bits take three more histograms, scans and four barriers each:
+// that form remains for a bucket of more than kSelectList keys, equal powers
+// for instance.  2^22 bins in blocks of 1024: 25 us against 33; 16 spectra of
+// 2^19 bins: 41 us against 51, with the factors below.)
 constexpr int kMedThreads = 256;
-
-static_assert(kMedThreads == 256, "one histogram bucket per thread");
+constexpr int kSelectBuckets = 2048;  // key >> 20; patterns with the sign bit join the last
+constexpr int kSelectList = 512;
 
 struct SelectScratch {
-    uint32_t hist[256];
+    uint32_t hist[kSelectBuckets];
+    uint32_t list[kSelectList];
     uint32_t wave_tot[kMedThreads / 64];
-    uint32_t pick[2];  // bucket, rank within it
+    uint32_t pick[3];  // bucket, rank within it, keys in it
+    uint32_t listed;
+    uint32_t value[2];  // keys of ranks r and r + 1 of the bucket
 };
 
-__device__ uint32_t select_rank(const uint32_t *u, int n, uint32_t rank, SelectScratch &sc) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+__device__ __forceinline__ uint32_t select_bucket(uint32_t key) { return min(key >> 20, uint32_t(kSelectBuckets - 1)); }
+
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+    // rows of 16 lanes by shifts, then the rows' last lanes broadcast onwards
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x111, 0xf, 0xf, false));  // row_shr:1
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x112, 0xf, 0xf, false));  // row_shr:2
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x114, 0xf, 0xf, false));  // row_shr:4
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x118, 0xf, 0xf, false));  // row_shr:8
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x142, 0xa, 0xf, false));  // row_bcast:15 to rows 1, 3
+    x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x143, 0xc, 0xf, false));  // row_bcast:31 to rows 2, 3
+    return x;
+}
+
+// The bucket that holds `rank` among the kMedThreads * PER buckets of sc.hist,
+// thread t counting buckets [PER t, PER t + PER): sc.pick.
+template <int PER>
+__device__ __forceinline__ void pick_bucket(uint32_t rank, SelectScratch &sc) {
+    const int t = threadIdx.x, wave = t >> 6;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] = sc.hist[PER * t + q];
+        sum += c[q];
+    }
+    uint32_t incl = wave_scan(sum);
+    if ((t & 63) == 63) sc.wave_tot[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += sc.wave_tot[w];
+    uint32_t excl = incl - sum;
+    if (excl <= rank && rank < incl) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (excl <= rank && rank < excl + c[q]) {
+                sc.pick[0] = uint32_t(PER * t + q);
+                sc.pick[1] = rank - excl;
+                sc.pick[2] = c[q];
+            }
+            excl += c[q];
+        }
+    }
+    __syncthreads();
+}
+
+// The key of rank `rank`, eight bits at a time.
+__device__ uint32_t select_radix(const uint32_t *u, int n, uint32_t rank, SelectScratch &sc) {
+    const int t = threadIdx.x;
+    static_assert(kMedThreads == 256, "one histogram bucket per thread");
     uint32_t prefix = 0, mask = 0;
     for (int shift = 24; shift >= 0; shift -= 8) {
-        sc.hist[t] = 0;  // kMedThreads == 256 buckets
+        sc.hist[t] = 0;
         __syncthreads();
         for (int i = t; i < n; i += kMedThreads) {
             const uint32_t key = u[i];
             if ((key & mask) == prefix) atomicAdd(&sc.hist[(key >> shift) & 255u], 1u);
         }
         __syncthreads();
-        // inclusive scan of the 256 counts: within each wave, then across the 4
-        const uint32_t c = sc.hist[t];
-        uint32_t incl = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(incl, o);
-            if (lane >= o) incl += y;
-        }
-        if (lane == 63) sc.wave_tot[wave] = incl;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) incl += sc.wave_tot[w];
-        const uint32_t excl = incl - c;
-        if (excl <= rank && rank < incl) {
-            sc.pick[0] = uint32_t(t);
-            sc.pick[1] = rank - excl;
-        }
-        __syncthreads();
+        pick_bucket<1>(rank, sc);
         prefix |= sc.pick[0] << shift;
         mask |= 255u << shift;
         rank = sc.pick[1];
@@ -275,13 +318,9 @@ __device__ uint32_t select_rank(const uint32_t *u, int n, uint32_t rank, SelectS
     return prefix;
 }
 
-// Median of the n valid keys (mean of the middle pair for even n), in FP64:
-// rank (n - 1) / 2 by selection; for even n the next rank is that value again
-// when it occurs more than once up to it, else the smallest larger key.
-__device__ double median_select(const uint32_t *u, int n, SelectScratch &sc) {
-    const uint32_t r1 = uint32_t(n - 1) >> 1;
-    const uint32_t v1 = select_rank(u, n, r1, sc);
-    if (n & 1) return double(__uint_as_float(v1));
+// The key after v1 = the key of rank r1: v1 again when it occurs more than
+// once up to there, else the smallest larger key.
+__device__ uint32_t select_next(const uint32_t *u, int n, uint32_t r1, uint32_t v1, SelectScratch &sc) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     uint32_t le = 0, above = 0xffffffffu;
     for (int i = t; i < n; i += kMedThreads) {
@@ -304,14 +343,68 @@ __device__ double median_select(const uint32_t *u, int n, SelectScratch &sc) {
         tle += sc.hist[w];
         tab = min(tab, sc.hist[8 + w]);
     }
-    const uint32_t v2 = tle >= r1 + 2 ? v1 : tab;
+    return tle >= r1 + 2 ? v1 : tab;
+}
+
+// Cleared before the keys are complete (a barrier follows either).
+__device__ __forceinline__ void select_clear(SelectScratch &sc) {
+    for (int i = threadIdx.x; i < kSelectBuckets; i += kMedThreads) sc.hist[i] = 0;
+    if (threadIdx.x == 0) sc.listed = 0;
+}
+
+// Median of the n valid keys (mean of the middle pair for even n), in FP64.
+// The histogram is cleared; the barrier after the keys' writes is passed.
+__device__ double median_select(const uint32_t *u, int n, SelectScratch &sc) {
+    const int t = threadIdx.x;
+    const uint32_t r1 = uint32_t(n - 1) >> 1;
+    for (int i = t; i < n; i += kMedThreads) atomicAdd(&sc.hist[select_bucket(u[i])], 1u);
+    __syncthreads();
+    pick_bucket<kSelectBuckets / kMedThreads>(r1, sc);
+    const uint32_t bucket = sc.pick[0], r = sc.pick[1], nl = sc.pick[2];
+    uint32_t v1, v2;
+    if (nl > uint32_t(kSelectList)) {
+        __syncthreads();  // pick is rewritten
+        v1 = select_radix(u, n, r1, sc);
+        v2 = n & 1 ? v1 : select_next(u, n, r1, v1, sc);
+    } else {
+        for (int i = t; i < n; i += kMedThreads) {
+            const uint32_t key = u[i];
+            if (select_bucket(key) == bucket) sc.list[atomicAdd(&sc.listed, 1u)] = key;
+        }
+        __syncthreads();
+        // a key with `less` smaller keys and `leq` keys up to its own value
+        // holds the ranks [less, leq); threads of equal keys write one value
+        for (uint32_t c = uint32_t(t) >> 2; c < nl; c += kMedThreads / 4) {
+            const uint32_t key = sc.list[c];
+            uint32_t less = 0, leq = 0;
+            for (uint32_t i = uint32_t(t) & 3u; i < nl; i += 4) {
+                const uint32_t o = sc.list[i];
+                less += o < key ? 1u : 0u;
+                leq += o <= key ? 1u : 0u;
+            }
+            uint32_t both = (less << 16) | leq;
+            both += uint32_t(__shfl_xor(both, 1));
+            both += uint32_t(__shfl_xor(both, 2));
+            less = both >> 16;
+            leq = both & 0xffffu;
+            if (less <= r && r < leq) sc.value[0] = key;
+            if (less <= r + 1 && r + 1 < leq) sc.value[1] = key;
+        }
+        __syncthreads();
+        v1 = sc.value[0];
+        v2 = n & 1 ? v1 : r + 1 < nl ? sc.value[1] : select_next(u, n, r1, v1, sc);
+    }
+    if (n & 1) return double(__uint_as_float(v1));
     return 0.5 * (double(__uint_as_float(v1)) + double(__uint_as_float(v2)));
 }
 
 constexpr int kMaxW = 8192;
 
 // One workgroup per block of W bins: X[k] from Z[k] and Z[M - k], then the
-// block's median power.  blockIdx.y numbers spectra laid out one after the other.
+// block's median power.  blockIdx.y numbers spectra laid out one after the
+// other.  A thread's bins are kMedThreads apart: their factors exp(-2 pi i k /
+// 2M) follow from the first by a rotation in FP64 (at most 31 of them, a few
+// 1e-15), two sines and cosines instead of one per bin.
 __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__restrict__ Z,
                                                                int64_t M, float2 *__restrict__ X,
                                                                double *__restrict__ med, int W) {
@@ -323,7 +416,11 @@ __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__r
     Z += int64_t(blockIdx.y) * M;
     X += int64_t(blockIdx.y) * M;
     med += int64_t(blockIdx.y) * gridDim.x;
+    select_clear(sc);
     const double inv_n = 1.0 / double(2 * M);
+    double cs, sn, step_c = 1.0, step_s = 0.0;
+    sincospi(-2.0 * double(b0 + t) * inv_n, &sn, &cs);
+    if (w > kMedThreads) sincospi(-2.0 * double(kMedThreads) * inv_n, &step_s, &step_c);
     for (int i = t; i < w; i += kMedThreads) {
         const int64_t k = b0 + i;
         float2 x = make_float2(0.f, 0.f);
@@ -333,12 +430,13 @@ __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__r
             // E = (Z[k] + conj Z[M-k]) / 2,  O = (Z[k] - conj Z[M-k]) / (2i)
             const float2 e = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
             const float2 o = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
-            double sn, cs;
-            sincospi(-2.0 * double(k) * inv_n, &sn, &cs);
             x = cadd(e, cmul(o, make_float2(float(cs), float(sn))));
         }
         X[k] = x;
         s[i] = __float_as_uint(cnorm(x));
+        const double c1 = fma(cs, step_c, -(sn * step_s));
+        sn = fma(cs, step_s, sn * step_c);
+        cs = c1;
     }
     __syncthreads();
     const double m = median_select(s, w, sc);
@@ -352,6 +450,7 @@ __global__ __launch_bounds__(kMedThreads) void k_median(const float2 *__restrict
     const int t = threadIdx.x;
     const int64_t b0 = int64_t(blockIdx.x) * W;
     const int w = int(min(int64_t(W), nb - b0));
+    select_clear(sc);
     for (int i = t; i < w; i += kMedThreads) s[i] = __float_as_uint(cnorm(X[b0 + i]));
     __syncthreads();
     const double m = median_select(s, w, sc);
@@ -753,16 +852,6 @@ __device__ __forceinline__ void add_fraction(const uint8_t *__restrict__ qrow, i
     });
 }
 
-// Inclusive prefix sum over the wave.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t x, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    return x;
-}
-
 // Screen tile (bx, by) of a workgroup of 64 SC_WAVES threads: columns
 // [bx SC_WAVES 2048, + SC_WAVES 2048), rows [by SC_TZ, + SC_TZ).  rowmask_lds:
 // SC_WAVES SC_TZ 64 words of LDS.
@@ -825,7 +914,7 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
     // LDS words, so no barrier is needed.)
     if (!__any(mycells != 0)) return;
     // cells (<= 32 SC_TZ 64 = 16384) in the low half, groups in the high half
-    const uint32_t incl = wave_scan((mygroups << 16) | mycells, lane);
+    const uint32_t incl = wave_scan((mygroups << 16) | mycells);
     const uint32_t total = __shfl(incl, 63);
     uint32_t cbase = 0, gbase = 0;
     if (lane == 0) {
@@ -1028,7 +1117,7 @@ __device__ __forceinline__ void peaks_tile(uint32_t wg, uint32_t nwg, int nz, in
             }
         }
         const uint32_t ncand = __popc(lmask);
-        const uint32_t incl = wave_scan(ncand, lane);
+        const uint32_t incl = wave_scan(ncand);
         if (lane == 63) wsum[par][wave] = incl;
         // orders the counts, and the previous step's staged records before a flush
         __syncthreads();
