@@ -50,10 +50,9 @@ struct Workspace {
     uint32_t *h_count = nullptr, *d_h_count = nullptr;
     fdas_cand *h_final = nullptr, *d_h_final = nullptr;
     float *series = nullptr;      // graph input: the trial is copied here first (batched path)
-    // Time-domain search: trials whose spectra are formed together (Z, work, X
-    // and med hold so many), and the series resampled for each.
+    // Time-domain search: trials whose spectra are formed together (Z, work
+    // and med hold so many; it needs no X).
     int td_batch = 1;
-    float *resampled = nullptr;
 };
 
 }  // namespace fdas

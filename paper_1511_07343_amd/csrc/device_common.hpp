@@ -55,6 +55,33 @@ __device__ __forceinline__ uint32_t put_code(float pw, float code_inv, int b, ui
     return __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaf(pw, code_inv, 1.f), 255.f), uint32_t(b), w);
 }
 
+// exp(-2 pi i k / 2M), which separates the spectrum of a real series of 2M
+// samples from the M-point DFT of its even and odd samples, and its rotation
+// by a step of bins (real_factor_step); FP64.
+struct RealFactor {
+    double c, s;
+    __device__ __forceinline__ RealFactor(int64_t k, int64_t M) { sincospi(-double(k) / double(M), &s, &c); }
+    __device__ __forceinline__ void rotate(double2 step) {
+        const double c1 = fma(c, step.x, -(s * step.y));
+        s = fma(c, step.y, s * step.x);
+        c = c1;
+    }
+};
+
+inline double2 real_factor_step(int bins, int64_t M) {
+    const double a = -3.14159265358979323846 * double(bins) / double(M);
+    return make_double2(cos(a), sin(a));
+}
+
+// X[k] = E + exp(-2 pi i k / 2M) O of the real series' spectrum,
+// E = (Z[k] + conj Z[M-k]) / 2, O = (Z[k] - conj Z[M-k]) / (2i), 0 < k < M.
+__device__ __forceinline__ float2 unpack_bin(float2 zk, float2 zm, const RealFactor &f) {
+    const float2 e = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
+    const float2 o = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
+    const float c = float(f.c), s = float(f.s);
+    return make_float2(e.x + fmaf(-o.y, s, o.x * c), e.y + fmaf(o.y, c, o.x * s));
+}
+
 // The larger power of a 2-bin block, a NaN if either is one: powers are
 // non-negative (or NaN), and non-negative floats, with NaN above +inf, order
 // as their unsigned bit patterns, so one integer maximum picks the larger

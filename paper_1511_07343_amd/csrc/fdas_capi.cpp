@@ -171,10 +171,9 @@ static fdas_status enqueue_td_search(fdas_plan_s *p, const Workspace &ws, const 
     const float *x = static_cast<const float *>(in_dev);
     for (int32_t iz = 0; iz < p->nz && e == hipSuccess; iz += ws.td_batch) {
         const int n = std::min(ws.td_batch, p->nz - iz);
-        e = launch_td_resample(x, g.nsamp, p->zmax, p->dz, p->nz, iz, n, ws.resampled, st);
-        if (e == hipSuccess) e = launch_r2c_packed(ws.resampled, g.nsamp, ws.Z, ws.work, st, n);
-        if (e == hipSuccess) e = launch_unpack_median(ws.Z, g.nsamp, ws.X, ws.med, p->W, st, n);
-        if (e == hipSuccess) e = launch_td_power(ws.X, ws.med, p->W, g.nb, iz, n, plane, ws.codes, p->code_inv, st);
+        e = launch_r2c_resampled(x, g.nsamp, p->zmax, p->dz, p->nz, iz, n, ws.Z, ws.work, st);
+        if (e == hipSuccess) e = launch_unpack_median(ws.Z, g.nsamp, nullptr, ws.med, p->W, st, n);
+        if (e == hipSuccess) e = launch_td_power(ws.Z, ws.med, p->W, g.nb, iz, n, plane, ws.codes, p->code_inv, st);
     }
     if (e != hipSuccess) return hip_fail(p, e, "time-domain spectra");
     for (int i = 1; i <= 4 && e == hipSuccess; ++i) e = mark(i);
@@ -319,7 +318,6 @@ fdas_status copy_candidates(const fdas_plan_s *p, const Workspace &ws, fdas_cand
 
 static void free_workspace(Workspace &ws) {
     if (ws.Z) (void)hipFree(ws.Z);
-    if (ws.resampled) (void)hipFree(ws.resampled);
     if (ws.work) (void)hipFree(ws.work);
     if (ws.X) (void)hipFree(ws.X);
     if (ws.med) (void)hipFree(ws.med);
@@ -369,10 +367,9 @@ static fdas_status try_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp, i
     ws.td_batch = together;
     FDAS_ALLOC(ws.Z, M * 8 * together);
     FDAS_ALLOC(ws.work, M * 8 * together);
-    FDAS_ALLOC(ws.X, M * 8 * together);
+    if (!p->td) FDAS_ALLOC(ws.X, M * 8);
     FDAS_ALLOC(ws.med, g.nblk * 8 * together);
-    if (p->td) FDAS_ALLOC(ws.resampled, nsamp * 4 * together);
-    else FDAS_ALLOC(ws.seg, g.nseg * int64_t(p->S) * 8);
+    if (!p->td) FDAS_ALLOC(ws.seg, g.nseg * int64_t(p->S) * 8);
     FDAS_ALLOC(ws.plane, int64_t(p->nz) * g.ncol * 4);
     FDAS_ALLOC(ws.codes, int64_t(p->nz) * (g.ncol / 2));
     if (p->corr != FDAS_CORR_FFT_F32) FDAS_ALLOC(ws.xl, g.nb * 4);
@@ -756,8 +753,8 @@ int64_t fdas_plan_device_bytes(const fdas_plan_t *plan) {
         if (ws.nsamp) {
             const Geometry g = make_geometry(ws.nsamp, plan->S, plan->h, plan->W, cols_per_bin(plan));
             b += series_bytes(g, plan->S, plan->nz) + candidate_bytes(plan, g);
-            if (plan->td)  // the resampled series, and the buffers of trials formed together
-                b += ws.td_batch * ws.nsamp * 4 + (ws.td_batch - 1) * (3 * g.nb * 8 + g.nblk * 8);
+            if (plan->td)  // no spectrum buffer, and those of trials formed together
+                b += (ws.td_batch - 1) * (2 * g.nb * 8 + g.nblk * 8) - g.nb * 8;
         }
     }
     return b;

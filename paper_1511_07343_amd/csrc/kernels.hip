@@ -78,23 +78,87 @@ __global__ __launch_bounds__(fft_threads(LOG2S)) void k_dft(const float2 *__rest
 }
 
 // ------------------------------------------------------- real input DFT
-// z[n] = x[2n] + i x[2n+1] is read as float2 directly from the series.
-// blockIdx.y numbers series of M points laid out one after the other.
+// z[n] = x[2n] + i x[2n+1]; blockIdx.y numbers series of M points.  Where the
+// first pass takes its points from:
+
+// series laid out one after the other, read as float2
+struct PackedSeries {
+    const float2 *__restrict__ z;
+    __device__ __forceinline__ void select(int b, int64_t M) { z += b * M; }
+    __device__ __forceinline__ float2 operator()(int64_t i) const { return z[i]; }
+};
+
+// Trials of the time-domain search: y[m] = x at position s_m = N (v_m + 1/2),
+// v_m + alpha v_m^2 / 2 = tau_m = m / N - 1/2, the time axis on which a tone
+// drifting by alpha (relative to its mean frequency) keeps one frequency.
+// Linear interpolation between the neighbouring samples (x[N] = 0), zero
+// outside the series.  The position is formed in FP64 (it needs ~24 bits of
+// integer part plus the fraction): two Newton steps from the FP32 root
+// v = 2 tau / (1 + sqrt(q)), q = 1 + 2 alpha tau in [1/2, 3/2], whose slope
+// 1 + alpha v is sqrt(q), so no FP64 root or division is taken; the first
+// leaves about 1e-14, the second a rounding.  Forming the samples here rather
+// than in a pass of their own saves a write and a read of the series, and the
+// instructions hide under the pass's loads and stores (sixteen trials of 2^20
+// samples: 44 us, against 36 us and 28 us in two passes).
+struct ResampledSeries {
+    const float *__restrict__ x;
+    int n;
+    double zmax, dz;
+    int nz, iz0;
+    double h, inv_n;  // alpha / 2, 1 / N
+    __device__ __forceinline__ void select(int b, int64_t) {
+        // -alpha_max + d iz with two roundings, as the trials are defined
+#pragma clang fp contract(off)
+        const double alpha = nz == 1 ? 0.0 : -zmax + dz * double(iz0 + b);
+        h = 0.5 * alpha;
+        inv_n = 1.0 / double(n);  // exact: n is a power of two
+    }
+    __device__ __forceinline__ double newton(double v, double inv, double tau) const {
+        return fma(tau - v * fma(h, v, 1.0), inv, v);
+    }
+    __device__ __forceinline__ float sample(double v) const {
+        const double nd = double(n);
+        const double s = fma(nd, v, 0.5 * nd);
+        const double fl = floor(s);
+        const int i = int(fl);
+        // both neighbours in one load that stays inside the series
+        struct __attribute__((packed, aligned(4))) Pair {
+            float a, b;
+        };
+        const Pair q = *reinterpret_cast<const Pair *>(x + min(max(i, 0), n - 2));
+        const bool last = i == n - 1;
+        const double f = s - fl;
+        const double a = double(last ? q.b : q.a);
+        const double b = double(last ? 0.f : q.b);
+        return uint32_t(i) < uint32_t(n) ? float(a * (1.0 - f) + b * f) : 0.f;
+    }
+    __device__ __forceinline__ float2 operator()(int64_t i) const {
+        const double tau0 = fma(double(int(2 * i)), inv_n, -0.5), tau1 = tau0 + inv_n;  // exact
+        const float tf = float(tau0);
+        const float q = fmaf(4.f * float(h), tf, 1.f);
+        const float r = __builtin_amdgcn_rsqf(q);
+        const double inv = double(r);
+        double v = double(2.f * tf * __builtin_amdgcn_rcpf(fmaf(q, r, 1.f)));
+        v = newton(newton(v, inv, tau0), inv, tau0);
+        double w = fma(inv_n, inv, v);
+        w = newton(newton(w, inv, tau1), inv, tau1);
+        return make_float2(sample(v), sample(w));
+    }
+};
 
 // M = 2^LOG2M <= 8192: one workgroup.
-template <int LOG2M>
-__global__ __launch_bounds__(fft_threads(LOG2M)) void k_r2c_small(const float2 *__restrict__ z,
-                                                                  float2 *__restrict__ Z) {
+template <int LOG2M, class In>
+__global__ __launch_bounds__(fft_threads(LOG2M)) void k_r2c_small(In z, float2 *__restrict__ Z) {
     using Sh = FftShape<LOG2M, fft_threads(LOG2M)>;
     __shared__ float2 lds[Sh::LDS_FLOAT2];
     const int t = threadIdx.x;
-    z += int64_t(blockIdx.y) << LOG2M;
+    z.select(blockIdx.y, Sh::S);
     Z += int64_t(blockIdx.y) << LOG2M;
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
 #pragma unroll
-    for (int m = 0; m < Sh::R; ++m) v[m] = z[t + Sh::NT * m];
+    for (int m = 0; m < Sh::R; ++m) v[m] = z(t + Sh::NT * m);
     fft_wg<Sh, -1>(v, lds, tw, t);
 #pragma unroll
     for (int m = 0; m < Sh::R; ++m) Z[t + Sh::NT * m] = v[m];
@@ -130,23 +194,21 @@ __device__ __forceinline__ void r2c_twist(const float2 (&v)[Sh::R], float2 *__re
 // Four-step M = M1 * M2 (n = n2 + M2 n1, k = k1 + M1 k2).
 // Pass A, one workgroup per column n2: DFT over n1, times exp(-2 pi i n2 k1 / M),
 // stored at work[n2 + M2 k1].
-template <int LOG2M1>
-__global__ __launch_bounds__(fft_threads(LOG2M1)) void k_r2c_cols(const float2 *__restrict__ z,
-                                                                  float2 *__restrict__ work,
-                                                                  int log2m2) {
+template <int LOG2M1, class In>
+__global__ __launch_bounds__(fft_threads(LOG2M1)) void k_r2c_cols(In z, float2 *__restrict__ work, int log2m2) {
     using Sh = FftShape<LOG2M1, fft_threads(LOG2M1)>;
     __shared__ float2 lds[Sh::LDS_FLOAT2];
     const int t = threadIdx.x;
     const int64_t M2 = int64_t(1) << log2m2;
     const int64_t M = M2 << LOG2M1;
     const int64_t n2 = xcd_spread(blockIdx.x, gridDim.x);  // adjacent columns share lines
-    z += int64_t(blockIdx.y) * M;
+    z.select(blockIdx.y, M);
     work += int64_t(blockIdx.y) * M;
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
 #pragma unroll
-    for (int m = 0; m < Sh::R; ++m) v[m] = z[n2 + M2 * (t + Sh::NT * m)];
+    for (int m = 0; m < Sh::R; ++m) v[m] = z(n2 + M2 * (t + Sh::NT * m));
     fft_wg<Sh, -1>(v, lds, tw, t);
     r2c_twist<Sh>(v, work, n2, t, M2, M);
 }
@@ -184,9 +246,8 @@ constexpr int r2c_region() {
     return Sh::LDS_FLOAT2 + 8;
 }
 
-template <int LOG2M1>
-__global__ __launch_bounds__(fft_threads(LOG2M1) * kR2cGroup) void k_r2c_cols4(const float2 *__restrict__ z,
-                                                                                float2 *__restrict__ work,
+template <int LOG2M1, class In>
+__global__ __launch_bounds__(fft_threads(LOG2M1) * kR2cGroup) void k_r2c_cols4(In z, float2 *__restrict__ work,
                                                                                 int log2m2) {
     using Sh = FftShape<LOG2M1, fft_threads(LOG2M1)>;
     __shared__ float2 lds[kR2cGroup * r2c_region<Sh>()];
@@ -195,13 +256,13 @@ __global__ __launch_bounds__(fft_threads(LOG2M1) * kR2cGroup) void k_r2c_cols4(c
     const int64_t M2 = int64_t(1) << log2m2;
     const int64_t M = M2 << LOG2M1;
     const int64_t n2 = xcd_spread(blockIdx.x, gridDim.x) * kR2cGroup + c;  // adjacent groups share lines
-    z += int64_t(blockIdx.y) * M;
+    z.select(blockIdx.y, M);
     work += int64_t(blockIdx.y) * M;
     Twiddles<Sh, -1> tw;
     tw.init(t);
     float2 v[Sh::R];
 #pragma unroll
-    for (int m = 0; m < Sh::R; ++m) v[m] = z[n2 + M2 * (t + Sh::NT * m)];
+    for (int m = 0; m < Sh::R; ++m) v[m] = z(n2 + M2 * (t + Sh::NT * m));
     fft_wg<Sh, -1>(v, lds + c * r2c_region<Sh>(), tw, t);
     r2c_twist<Sh>(v, work, n2, t, M2, M);
 }
@@ -400,13 +461,14 @@ __device__ double median_select(const uint32_t *u, int n, SelectScratch &sc) {
 
 constexpr int kMaxW = 8192;
 
-// One workgroup per block of W bins: X[k] from Z[k] and Z[M - k], then the
-// block's median power.  blockIdx.y numbers spectra laid out one after the
-// other.  A thread's bins are kMedThreads apart: their factors exp(-2 pi i k /
-// 2M) follow from the first by a rotation in FP64 (at most 31 of them, a few
-// 1e-15), two sines and cosines instead of one per bin.
+// One workgroup per block of W bins: X[k] from Z[k] and Z[M - k] (written
+// unless X is null), then the block's median power.  blockIdx.y numbers
+// spectra laid out one after the other.  A thread's bins are kMedThreads
+// apart: their factors exp(-2 pi i k / 2M) follow from the first by a rotation
+// in FP64 (`step`; at most 31 of them, a few 1e-15), one sine and cosine
+// instead of one per bin.
 __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__restrict__ Z,
-                                                               int64_t M, float2 *__restrict__ X,
+                                                               int64_t M, double2 step, float2 *__restrict__ X,
                                                                double *__restrict__ med, int W) {
     extern __shared__ uint32_t s[];  // W keys (dynamic: the block's size only)
     __shared__ SelectScratch sc;
@@ -414,29 +476,15 @@ __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__r
     const int64_t b0 = int64_t(blockIdx.x) * W;
     const int w = int(min(int64_t(W), M - b0));
     Z += int64_t(blockIdx.y) * M;
-    X += int64_t(blockIdx.y) * M;
     med += int64_t(blockIdx.y) * gridDim.x;
     select_clear(sc);
-    const double inv_n = 1.0 / double(2 * M);
-    double cs, sn, step_c = 1.0, step_s = 0.0;
-    sincospi(-2.0 * double(b0 + t) * inv_n, &sn, &cs);
-    if (w > kMedThreads) sincospi(-2.0 * double(kMedThreads) * inv_n, &step_s, &step_c);
+    RealFactor f(b0 + t, M);
     for (int i = t; i < w; i += kMedThreads) {
         const int64_t k = b0 + i;
-        float2 x = make_float2(0.f, 0.f);
-        if (k > 0) {
-            const float2 zk = Z[k];
-            const float2 zm = Z[M - k];
-            // E = (Z[k] + conj Z[M-k]) / 2,  O = (Z[k] - conj Z[M-k]) / (2i)
-            const float2 e = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
-            const float2 o = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
-            x = cadd(e, cmul(o, make_float2(float(cs), float(sn))));
-        }
-        X[k] = x;
+        const float2 x = k > 0 ? unpack_bin(Z[k], Z[M - k], f) : make_float2(0.f, 0.f);
+        if (X) X[int64_t(blockIdx.y) * M + k] = x;
         s[i] = __float_as_uint(cnorm(x));
-        const double c1 = fma(cs, step_c, -(sn * step_s));
-        sn = fma(cs, step_s, sn * step_c);
-        cs = c1;
+        f.rotate(step);
     }
     __syncthreads();
     const double m = median_select(s, w, sc);
@@ -1419,13 +1467,13 @@ hipError_t launch_dft(int log2n, int dir, int64_t batch, const float2 *in, float
     return hipGetLastError();
 }
 
-hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch) {
-    const float2 *z = reinterpret_cast<const float2 *>(x);
+template <class In>
+static hipError_t launch_r2c(const In &z, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch) {
     int log2m = 0;
     while ((int64_t(1) << log2m) < nsamp / 2) ++log2m;
     if ((int64_t(1) << log2m) != nsamp / 2 || log2m < 6 || log2m > 26 || batch < 1) return hipErrorInvalidValue;
     if (log2m <= 13) {
-#define CALL(L) hipLaunchKernelGGL((k_r2c_small<L>), dim3(1, unsigned(batch)), dim3(fft_threads(L)), 0, st, z, Z);
+#define CALL(L) hipLaunchKernelGGL((k_r2c_small<L, In>), dim3(1, unsigned(batch)), dim3(fft_threads(L)), 0, st, z, Z);
         FDAS_SWITCH_LOG2(log2m, CALL)
 #undef CALL
         return hipGetLastError();
@@ -1433,12 +1481,12 @@ hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *w
     const int l1 = (log2m + 1) / 2, l2 = log2m / 2;  // 7 <= l2 <= l1 <= 13
     const unsigned ncols = 1u << l2, nrows = 1u << l1;
     if (l1 <= 11) {  // four columns per workgroup (ncols is a multiple of 4)
-#define CALL(L) hipLaunchKernelGGL((k_r2c_cols4<L>), dim3(ncols / kR2cGroup, unsigned(batch)), dim3(fft_threads(L) * kR2cGroup), 0, st, \
+#define CALL(L) hipLaunchKernelGGL((k_r2c_cols4<L, In>), dim3(ncols / kR2cGroup, unsigned(batch)), dim3(fft_threads(L) * kR2cGroup), 0, st, \
                            z, work, l2);
         FDAS_SWITCH_LOG2_GROUPED(l1, CALL)
 #undef CALL
     } else {
-#define CALL(L) hipLaunchKernelGGL((k_r2c_cols<L>), dim3(ncols, unsigned(batch)), dim3(fft_threads(L)), 0, st, z, work, l2);
+#define CALL(L) hipLaunchKernelGGL((k_r2c_cols<L, In>), dim3(ncols, unsigned(batch)), dim3(fft_threads(L)), 0, st, z, work, l2);
         FDAS_SWITCH_LOG2(l1, CALL)
 #undef CALL
     }
@@ -1457,13 +1505,23 @@ hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *w
     return hipGetLastError();
 }
 
+hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch) {
+    return launch_r2c(PackedSeries{reinterpret_cast<const float2 *>(x)}, nsamp, Z, work, st, batch);
+}
+
+hipError_t launch_r2c_resampled(const float *x, int64_t nsamp, double zmax, double dz, int nz, int iz0, int count,
+                                float2 *Z, float2 *work, hipStream_t st) {
+    if (nsamp < 2 || nsamp > (int64_t(1) << 26) || count < 1 || count > 65535) return hipErrorInvalidValue;
+    return launch_r2c(ResampledSeries{x, int(nsamp), zmax, dz, nz, iz0, 0.0, 0.0}, nsamp, Z, work, st, count);
+}
+
 hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st,
                                 int batch) {
     const int64_t M = nsamp / 2;
     if (W < 2 || W > kMaxW || (W & (W - 1)) || batch < 1) return hipErrorInvalidValue;
     const int64_t nblk = (M + W - 1) / W;
-    hipLaunchKernelGGL(k_unpack_median, dim3(unsigned(nblk), unsigned(batch)), dim3(kMedThreads), size_t(W) * sizeof(uint32_t), st, Z,
-                       M, X, med, W);
+    hipLaunchKernelGGL(k_unpack_median, dim3(unsigned(nblk), unsigned(batch)), dim3(kMedThreads),
+                       size_t(W) * sizeof(uint32_t), st, Z, M, real_factor_step(kMedThreads, M), X, med, W);
     return hipGetLastError();
 }
 

@@ -29,8 +29,9 @@ hipError_t launch_dft(int log2n, int dir, int64_t batch, const float2 *in, float
 // laid out one after the other, in x, Z and work.
 hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch = 1);
 
-// Unpack Z into the real-input spectrum X[k], k in [0, M) (X[0] = 0), and the
-// median of |X|^2 over each block of W bins (FP64 out); batch as above.
+// Unpack Z into the real-input spectrum X[k], k in [0, M) (X[0] = 0; not
+// stored if X is null), and the median of |X|^2 over each block of W bins
+// (FP64 out); batch as above.
 hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st,
                                 int batch = 1);
 
@@ -147,13 +148,14 @@ hipError_t launch_dedisperse(const uint8_t *fil, int nchan, int64_t nsamp, doubl
                              const double *dms, int ndm, int64_t nout, float *out, hipStream_t st);
 
 // Time-domain resampling search, trials iz0 .. iz0 + count - 1, trial iz of
-// drift alpha = -zmax + iz dz (0 for one trial), each in its own part of y, X
-// and med: the series resampled for the drift (relative to the mean
-// frequency; linear interpolation, FP64 positions); the normalised powers
-// |X|^2 ln2 / m(k) into plane rows iz with their 2-bin codes (nb % 4 == 0).
-hipError_t launch_td_resample(const float *x, int64_t nsamp, double zmax, double dz, int nz, int iz0, int count,
-                              float *y, hipStream_t st);
-hipError_t launch_td_power(const float2 *X, const double *med, int W, int64_t nb, int iz0, int count, float *plane,
+// drift alpha = -zmax + iz dz (0 for one trial; |alpha| <= 1/2), each in its
+// own part of Z, work and med: launch_r2c_packed of the series resampled for
+// the drift (relative to the mean frequency; linear interpolation, FP64
+// positions); and the normalised powers |X|^2 ln2 / m(k) of the spectra X that
+// Z unpacks to, into plane rows iz with their 2-bin codes (nb % 8 == 0).
+hipError_t launch_r2c_resampled(const float *x, int64_t nsamp, double zmax, double dz, int nz, int iz0, int count,
+                                float2 *Z, float2 *work, hipStream_t st);
+hipError_t launch_td_power(const float2 *Z, const double *med, int W, int64_t nb, int iz0, int count, float *plane,
                            uint8_t *codes, float code_inv, hipStream_t st);
 
 // Candidate refinement (Fourier interpolation off the grid): for each of the
