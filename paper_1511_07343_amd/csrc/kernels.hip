@@ -809,19 +809,37 @@ __device__ __forceinline__ void cell_sums(const float *__restrict__ P, int64_t n
 // A lane owns the 16 blocks 16 m + beta (32 columns) of a row.  Fraction j of
 // bin 2 (16 m + beta) + i lies in block j m + floor((2 j beta + j i + 8) / 32):
 // the 16 blocks' codes of fraction j sit in bytes [j m, j m + span) of row r_j
-// at compile-time offsets.  Blocks 2p and 2p+1 share one 32-bit register
-// (p < 8), one per 16-bit half: a sum of at most 16 codes (<= 4080) never
-// carries into the upper half, and a half reaches level l iff
-// sum + 0x8000 - T_l sets its bit 15.  All loads of a row are independent of
-// each other and issued together.
-constexpr int SC_TZ = 8;      // rows per wave
+// at compile-time offsets.  Blocks p and p + 8 share one 32-bit register
+// (p < 8), one per 16-bit half (they straddle two blocks of an even fraction
+// together, which saves a maximum against neighbours): a sum of at most 16
+// codes (<= 4080) never carries into the upper half, and a half reaches level
+// l iff sum + 0x8000 - T_l sets its bit 15.  All loads of a row are
+// independent of each other and issued together.
+//
+// Some 300 vector instructions for 2048 cells of 16 harmonics, half of them
+// byte gathers, and 25 loads, whose lines keep the L1 as busy: 2^22 columns x
+// 201 rows, 16 harmonics 388 us (2.2e12 cells/s; with the masks formed for
+// every row and neighbouring blocks paired 410), 2^21 half bins x 201 rows, 8
+// harmonics 101 us (121).  Sums on the i8 matrix cores take the same bytes as
+// operands with fewer vector instructions, but 16 bytes of every fraction
+// where these loads take what is used, and came to 435 us; keeping the bounds
+// of the fractions whose row of codes does not change from one row to the next
+// costs more in waves per SIMD than it saves (413 us and more); tiles of 16
+// rows (402) and columns before rows (397) gain nothing.
+constexpr int SC_TZ = 8;      // most rows per wave
 constexpr int SC_WAVES = 4;   // waves per workgroup
 constexpr int SC_COLS = 32;   // columns per lane (one group)
 constexpr int SC_WAVE_COLS = 64 * SC_COLS;
 
+// 0x8000 - T_0, then T_(l-1) - T_l, times 0x10001 modulo 2^32: added level by
+// level to the sums of both halves, which stay below 2^16 throughout.
 struct ScreenThr {
-    uint32_t k[5];  // (0x8000 - T_l) in both 16-bit halves
+    uint32_t k[5];
 };
+
+inline uint32_t screen_step(const uint32_t *code_thr, int l) {
+    return ((l == 0 ? 0x8000u : code_thr[l - 1]) - code_thr[l]) * 0x10001u;
+}
 
 struct Group {
     int32_t m;         // columns 32 m .. 32 m + 31
@@ -861,96 +879,115 @@ __device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b) {
                               __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
-// Bytes A and C of the aligned words w (C >> 2 is A >> 2 or one more) in the
-// low bytes of the two 16-bit halves of the result.
+// Bytes A and C of the aligned words w in the low bytes of the two 16-bit
+// halves of the result.
 template <int A, int C, int NW>
 __device__ __forceinline__ uint32_t gather2(const uint32_t (&w)[NW]) {
     constexpr int wa = A >> 2, wc = C >> 2;
-    static_assert(wc == wa || wc == wa + 1, "bytes in adjacent words");
     // v_perm_b32 selector bytes: 0-3 pick bytes of the second source, 4-7
     // bytes of the first, 0x0c gives zero.
     constexpr uint32_t sel = uint32_t(A & 3) | 0x0c00u | (uint32_t((wc == wa ? 0 : 4) + (C & 3)) << 16) | 0x0c000000u;
     return __builtin_amdgcn_perm(w[wc], w[wa], sel);
 }
 
-// Add fraction J's bounds of the lane's 8 block pairs (group m of row qrow) to acc.
+// The words that hold fraction J's codes of group m, and adding its bounds of
+// the 8 block pairs.
 template <int J>
-__device__ __forceinline__ void add_fraction(const uint8_t *__restrict__ qrow, int64_t m, uint32_t (&acc)[8]) {
+struct FracWords {
     using FB = FracBlocks<J>;
-    const int64_t b = int64_t(J) * m;  // first byte
-    const uint32_t *__restrict__ src = reinterpret_cast<const uint32_t *>(qrow + (b & ~int64_t(3)));
     uint32_t d[FB::nd];
+    __device__ __forceinline__ void load(const uint8_t *__restrict__ qrow, uint32_t m) {
+        const uint32_t *__restrict__ src = reinterpret_cast<const uint32_t *>(qrow + (J * m & ~3u));
 #pragma unroll
-    for (int q = 0; q < FB::nd; ++q) d[q] = src[q];
-    uint32_t w[FB::nw];
-    if constexpr (FB::maxshift == 0) {
-#pragma unroll
-        for (int q = 0; q < FB::nw; ++q) w[q] = d[q];
-    } else {
-        const uint32_t sh = uint32_t(b & 3);
-#pragma unroll
-        for (int q = 0; q < FB::nw; ++q) w[q] = __builtin_amdgcn_alignbyte(d[q + 1 < FB::nd ? q + 1 : q], d[q], sh);
+        for (int q = 0; q < FB::nd; ++q) d[q] = src[q];
     }
-    static_for<0, 8>([&](auto pc) {
-        constexpr int p = decltype(pc)::value;
-        constexpr int l0 = FB::lo(2 * p), l1 = FB::lo(2 * p + 1), h0 = FB::hi(2 * p), h1 = FB::hi(2 * p + 1);
-        uint32_t v = gather2<l0, l1>(w);
-        if constexpr (h0 != l0 || h1 != l1) v = max_u16x2(v, gather2<h0, h1>(w));
-        acc[p] += v;
-    });
-}
+    __device__ __forceinline__ void add(uint32_t m, uint32_t (&acc)[8]) const {
+        uint32_t w[FB::nw];
+        if constexpr (FB::maxshift == 0) {
+#pragma unroll
+            for (int q = 0; q < FB::nw; ++q) w[q] = d[q];
+        } else {
+            const uint32_t sh = J * m & 3u;
+#pragma unroll
+            for (int q = 0; q < FB::nw; ++q) w[q] = __builtin_amdgcn_alignbyte(d[q + 1 < FB::nd ? q + 1 : q], d[q], sh);
+        }
+        static_for<0, 8>([&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            constexpr int l0 = FB::lo(p), l1 = FB::lo(p + 8), h0 = FB::hi(p), h1 = FB::hi(p + 8);
+            uint32_t v = gather2<l0, l1>(w);
+            if constexpr (h0 != l0 || h1 != l1) v = max_u16x2(v, gather2<h0, h1>(w));
+            acc[p] += v;
+        });
+    }
+};
+
+template <class Seq>
+struct FracSet;
+template <int... I>
+struct FracSet<std::integer_sequence<int, I...>> : FracWords<I + 1>... {
+    template <int J>
+    __device__ __forceinline__ FracWords<J> &at() {
+        return *this;
+    }
+};
+using FracAll = FracSet<std::make_integer_sequence<int, 16>>;
 
 // Screen tile (bx, by) of a workgroup of 64 SC_WAVES threads: columns
-// [bx SC_WAVES 2048, + SC_WAVES 2048), rows [by SC_TZ, + SC_TZ).  rowmask_lds:
-// SC_WAVES SC_TZ 64 words of LDS.
+// [bx SC_WAVES 2048, + SC_WAVES 2048), rows [by tile_rows, + tile_rows),
+// tile_rows <= SC_TZ.  rowmask_lds: SC_WAVES SC_TZ 64 words of LDS.
 template <int LEVELS>
-__device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, int by, const uint8_t *__restrict__ Q,
+__device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, int by, int tile_rows,
+                                            const uint8_t *__restrict__ Q,
                                             int nz, int64_t nb, int izc, const ScreenThr &T,
                                             Group *__restrict__ groups, uint2 *__restrict__ blocks,
                                             uint32_t *__restrict__ group_map, uint32_t *__restrict__ cnt,
                                             uint32_t group_cap, uint32_t cell_cap) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    // a workgroup covers SC_WAVES * 2048 columns and SC_TZ rows
+    // a workgroup covers SC_WAVES * 2048 columns
     const int64_t m = (bx * SC_WAVES + wave) * 64 + lane;  // column group
-    const int iz0 = by * SC_TZ;
+    const int iz0 = by * tile_rows, rows = min(tile_rows, nz - iz0);
     const int64_t ngr = nb / SC_COLS;
     const int64_t qlen = nb / 2;  // codes per row
     const bool valid = m < ngr;
-    if (!__any(valid) || iz0 >= nz) return;
-    const int64_t mm = valid ? m : 0;  // lanes past the end read group 0 and report nothing
+    if (!__any(valid) || rows <= 0) return;
+    const uint32_t mm = valid ? uint32_t(m) : 0u;  // lanes past the end read group 0 and report nothing
     uint32_t *__restrict__ rowmask = rowmask_lds + wave * (SC_TZ * 64) + lane;  // row r at rowmask[64 r]
     uint32_t mycells = 0, mygroups = 0;
 #pragma unroll 1
-    for (int r = 0; r < SC_TZ; ++r) {
+    for (int r = 0; r < rows; ++r) {
         const int iz = iz0 + r;
-        rowmask[64 * r] = 0;
-        if (iz >= nz) continue;
         const int d = iz - izc;
-        uint32_t G[LEVELS + 1][8];
-#pragma unroll
-        for (int l = 0; l <= LEVELS; ++l)
-#pragma unroll
-            for (int p = 0; p < 8; ++p) G[l][p] = 0u;
+        FracAll fs;
         static_for<1, 17>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
             if constexpr (frac_used<LEVELS>(j))
-                add_fraction<j>(Q + int64_t(frac_row(izc, d, j)) * qlen, mm, G[frac_level(j)]);
+                fs.template at<j>().load(Q + int64_t(frac_row(izc, d, j)) * qlen, mm);
         });
+        uint32_t sm[LEVELS + 1][8], any = 0;  // sums + 0x8000 - T_l
+        static_for<0, LEVELS + 1>([&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+#pragma unroll
+            for (int p = 0; p < 8; ++p) sm[l][p] = l == 0 ? T.k[0] : sm[l > 0 ? l - 1 : 0][p] + T.k[l];
+            static_for<1, 17>([&](auto jc) {
+                constexpr int j = 17 - decltype(jc)::value;
+                if constexpr (frac_level(j) == l) fs.template at<j>().add(mm, sm[l]);
+            });
+#pragma unroll
+            for (int p = 0; p < 8; ++p) any |= sm[l][p];
+        });
+        // which blocks, only when there are any
         uint32_t mask = 0;
+        if (__any((any & 0x80008000u) != 0u)) {
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            uint32_t sm = G[0][p];
-            uint32_t fl = sm + T.k[0];
+            for (int p = 0; p < 8; ++p) {
+                uint32_t fl = 0;
 #pragma unroll
-            for (int l = 1; l <= LEVELS; ++l) {
-                sm += G[l][p];
-                fl |= sm + T.k[l];
+                for (int l = 0; l <= LEVELS; ++l) fl |= sm[l][p];
+                mask |= ((fl >> 15) & 0x10001u) << p;
             }
-            mask |= ((fl >> 15) & 1u) << (2 * p);
-            mask |= (fl >> 31) << (2 * p + 1);
+            mask = valid ? (mask & 0xffu) | (mask >> 8) : 0u;
         }
-        if (!valid) mask = 0;
         rowmask[64 * r] = mask;
         mycells += 2u * __popc(mask);
         mygroups += mask != 0 ? 1u : 0u;
@@ -976,7 +1013,7 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
     uint32_t first = __shfl(cbase, 0) + (incl & 0xffffu) - mycells;
     uint32_t g = __shfl(gbase, 0) + (incl >> 16) - mygroups;
 #pragma unroll 1
-    for (int r = 0; r < SC_TZ; ++r) {
+    for (int r = 0; r < rows; ++r) {
         const uint32_t mask = rowmask[64 * r];
         if (mask == 0) continue;
         const uint32_t ncell = 2u * __popc(mask);
@@ -999,14 +1036,14 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
 }
 
 template <int LEVELS>
-__global__ __launch_bounds__(64 * SC_WAVES) void k_screen(const uint8_t *__restrict__ Q, int nz, int64_t nb,
-                                                          int izc, ScreenThr T, Group *__restrict__ groups,
+__global__ __launch_bounds__(64 * SC_WAVES, 3) void k_screen(const uint8_t *__restrict__ Q, int nz, int64_t nb,
+                                                          int tile_rows, int izc, ScreenThr T, Group *__restrict__ groups,
                                                           uint2 *__restrict__ blocks, uint32_t *__restrict__ group_map,
                                                           uint32_t *__restrict__ cnt, uint32_t group_cap,
                                                           uint32_t cell_cap) {
     // Row masks of the waves, kept until their records are written.
     __shared__ uint32_t rowmask_lds[SC_WAVES * SC_TZ * 64];
-    screen_tile<LEVELS>(rowmask_lds, blockIdx.x, blockIdx.y, Q, nz, nb, izc, T, groups, blocks, group_map, cnt,
+    screen_tile<LEVELS>(rowmask_lds, blockIdx.x, blockIdx.y, tile_rows, Q, nz, nb, izc, T, groups, blocks, group_map, cnt,
                         group_cap, cell_cap);
 }
 
@@ -1405,7 +1442,7 @@ __global__ __launch_bounds__(256, 2) void k_batch(BatchArgs a) {
             const HarmLists hl = harm_lists(tr.hits, a.cell_cap, a.group_cap);
             if (stage == BST_SCREEN) {
                 const int64_t ncolt = (tr.nb + int64_t(SC_WAVE_COLS) * SC_WAVES - 1) / (int64_t(SC_WAVE_COLS) * SC_WAVES);
-                screen_tile<LEVELS>(reinterpret_cast<uint32_t *>(lds), int64_t(idx) % ncolt, int(int64_t(idx) / ncolt),
+                screen_tile<LEVELS>(reinterpret_cast<uint32_t *>(lds), int64_t(idx) % ncolt, int(int64_t(idx) / ncolt), SC_TZ,
                                     tr.codes, a.nz, tr.nb, a.izc, a.T, hl.groups, hl.blocks, hl.group_map, tr.cnt,
                                     a.group_cap, a.cell_cap);
             } else if (stage == BST_EXACT) {
@@ -1628,20 +1665,24 @@ hipError_t launch_harmsum(const float *plane, const uint8_t *codes, int nz, int6
     for (int l = 0; l <= levels; ++l) {
         if (code_thr[l] > 0x8000u) return hipErrorInvalidValue;
         thr.v[l] = thr_host[l];
-        T.k[l] = (0x8000u - code_thr[l]) * 0x10001u;
+        T.k[l] = screen_step(code_thr, l);
     }
     cell_cap &= ~1u;  // whole blocks
     Group *groups = static_cast<Group *>(scratch);
     float *sums = reinterpret_cast<float *>(groups + group_cap);
     uint2 *blocks = reinterpret_cast<uint2 *>(sums + size_t(cell_cap) * SUM_STRIDE);
     uint32_t *group_map = reinterpret_cast<uint32_t *>(blocks + cell_cap / 2);
-    const int64_t rows = SC_TZ, cols = int64_t(SC_WAVE_COLS) * SC_WAVES;
-    const dim3 grid1(unsigned((nb + cols - 1) / cols), unsigned((nz + rows - 1) / rows));
+    // rows per tile: SC_TZ, fewer when that leaves less than 2048 workgroups
+    // (2^14 columns x 21 rows, 4 harmonics: 5.2 us a row at a time, 12.1 us
+    // eight; 2^19 columns x 160 rows, 8 harmonics: 24 us five at a time)
+    const int64_t cols = int64_t(SC_WAVE_COLS) * SC_WAVES, ncolt = (nb + cols - 1) / cols;
+    const int rows = int(std::max<int64_t>(1, std::min<int64_t>(SC_TZ, ncolt * nz / 2048)));
+    const dim3 grid1(unsigned(ncolt), unsigned((nz + rows - 1) / rows));
     // a step of the exact sums and the neighbour test for every 2^14 plane
     // cells, so that a small plane's launches are small too
     const unsigned grid2 = unsigned(std::min<int64_t>(2048, std::max<int64_t>(64, (int64_t(nz) * nb) >> 14)));
 #define CALL(LV)                                                                                                   \
-    hipLaunchKernelGGL((k_screen<LV>), grid1, dim3(64 * SC_WAVES), 0, st, codes, nz, nb, izc, T, groups, blocks,    \
+    hipLaunchKernelGGL((k_screen<LV>), grid1, dim3(64 * SC_WAVES), 0, st, codes, nz, nb, rows, izc, T, groups, blocks, \
                        group_map, count, group_cap, cell_cap);                                                     \
     hipLaunchKernelGGL((k_exact<LV>), dim3(grid2), dim3(256), 0, st, plane, nz, nb, split, izc, blocks, count,      \
                        cell_cap, sums);                                                                            \
@@ -1713,7 +1754,7 @@ hipError_t launch_batch_persistent(int log2s, int nharm_max, const BatchTrial *t
     for (int l = 0; l <= levels; ++l) {
         if (code_thr[l] > 0x8000u) return hipErrorInvalidValue;
         a.thr.v[l] = thr_host[l];
-        a.T.k[l] = (0x8000u - code_thr[l]) * 0x10001u;
+        a.T.k[l] = screen_step(code_thr, l);
     }
 #define CALL(LS, LV)                                                                                     \
     if (log2s == LS && levels == LV)                                                                     \
