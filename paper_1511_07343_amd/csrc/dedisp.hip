@@ -68,10 +68,9 @@ __device__ __forceinline__ i32x4 one_at(int at) {
 // bytes of sample block n of channel q.  The samples' top bits are flipped
 // (b - 128 as a signed byte) and 128 per channel added back at the end.
 
-// Lane l's sums of a tile are samples 16 (l % 16) + 4 (l / 16) .. + 3; those
-// before `first` belong to another span.
-__device__ __forceinline__ void store_tile(float *__restrict__ o, int64_t tile0, int64_t first, int lane, i32x4 sum) {
-    const int64_t t = tile0 + 16 * (lane & 15) + 4 * (lane >> 4);
+// A lane's four sums of a tile, samples t .. t + 3; those before `first` belong
+// to another span.
+__device__ __forceinline__ void store_sums(float *__restrict__ o, int64_t t, int64_t first, i32x4 sum) {
     const f32x4u v = {float(sum[0]), float(sum[1]), float(sum[2]), float(sum[3])};
     if (t >= first) {
         __builtin_nontemporal_store(v, reinterpret_cast<f32x4u *>(o + t));
@@ -90,28 +89,33 @@ __device__ __forceinline__ int64_t span_start(int64_t first, int span, int64_t n
 }
 
 // ---------------------------------------------------------- through LDS
-// A workgroup adds one span of 1024 samples for DL_GROUP consecutive DM
+// A workgroup adds one span of 1280 samples for DL_GROUP consecutive DM
 // trials, DL_DMS per wave.  In stages of DL_CH channels, each channel's bytes
 // that any of the trials needs (the span and the spread of their delays,
 // `row` bytes) are staged in LDS once, two stages in turn, and read from
 // there by every trial.  LDS reads of 16 bytes run at full rate only when
-// aligned, so a trial reads, per channel and block of 16 samples, the two
-// aligned pieces that hold them, and the matrix A does the byte shift: for a
-// trial whose samples start at byte s of a piece, row i of A has its one at
-// byte i + s of the 32 (two channels per product instead of four).  Bound by
-// the LDS reads (8 aligned 16-byte reads per 4 channels, 1024 samples and
-// trial): 64 channels to 256 trials of 2^23 samples in 5.35 ms (1.4e11 bytes
-// added, 25 TB/s), against 7.3 ms with unaligned LDS reads and byte
-// alignments in registers, 12.0 ms for the direct form and 14.2 ms for sums
-// of 16-bit fields on the vector units.
+// aligned, so a trial reads the aligned pieces that hold its samples and the
+// matrix A does the byte shift: for samples that start at byte s of a piece,
+// row i of A has its one at byte i + s of two pieces, and a block of 16
+// samples takes two products, one with each.  A lane's blocks follow one
+// another (block i of lane n is 5 n + i), so that the second piece of a block
+// is the first of the next: 6 reads for 5 blocks of 4 channels, where blocks
+// side by side in the lanes take 2 for each.  Five, because lanes 80 bytes
+// apart fall on different banks.  64 channels to 256 trials of 2^23 samples in
+// 4.99 ms (1.4e11 bytes added, 28 TB/s; LDS busy 58 % of the time, vector ALU
+// 53 %, matrix cores 37 %: four waves a SIMD wait for one another's stages),
+// against 5.39 ms with two reads a block, 7.3 ms with unaligned LDS reads and
+// byte alignments in registers, 12.0 ms for the direct form and 14.2 ms for
+// sums of 16-bit fields on the vector units.  Three blocks a lane take 6.0 ms,
+// seven 5.8 (registers), both trials' reads together 5.7.
 constexpr int DL_WAVES = 8;
 constexpr int DL_DMS = 2;
 constexpr int DL_GROUP = DL_WAVES * DL_DMS;
 constexpr int DL_CH = 16;
-constexpr int DL_TILES = 4;
+constexpr int DL_TILES = 5;
 constexpr int DL_SPAN = 256 * DL_TILES;
-constexpr int DL_MAX_ROW = 2048;
-constexpr int DL_LOADS = DL_MAX_ROW / 512;  // 16-byte pieces per thread and stage
+constexpr int DL_MAX_ROW = 2304;
+constexpr int DL_LOADS = (DL_MAX_ROW + 511) / 512;  // 16-byte pieces per thread and stage
 
 static_assert(DL_CH * 32 == DL_WAVES * 64, "32 threads stage a channel");
 static_assert(DL_DMS + 1 <= 4, "a wave evaluates its trials' and the smallest delays in one go");
@@ -189,32 +193,46 @@ __global__ __launch_bounds__(64 * DL_WAVES, 4) void k_dedisperse_lds(const uint8
     for (int c0 = 0; c0 < nchan; c0 += DL_CH, cur ^= 1) {
         const int now = at;
         if (c0 + DL_CH < nchan) fetch(c0 + DL_CH);
-        const uint8_t *__restrict__ buf = stage + cur * buf_bytes + 16 * ((lane & 15) + (q & 1));
+        const uint8_t *__restrict__ buf = stage + cur * buf_bytes + 16 * DL_TILES * (lane & 15);
+        // four channels at a time; the rows past the last channel are zero
 #pragma unroll 1
-        for (int g = 0; g < min(DL_CH, nchan - c0); g += 2) {
+        for (int g = 0; g < min(DL_CH, nchan - c0); g += 4) {
 #pragma unroll
             for (int k = 0; k < DL_DMS; ++k) {
-                const int o = __shfl(now, 16 * k + g + (q >> 1));
+                const int o = __shfl(now, 16 * k + g + q);
                 const uint8_t *__restrict__ p = buf + (o & ~15);
-                i32x4 w[DL_TILES];
+                i32x4 w[DL_TILES + 1];
 #pragma unroll
-                for (int i = 0; i < DL_TILES; ++i) w[i] = *reinterpret_cast<const i32x4 *>(p + 256 * i);
-                const i32x4 a = one_at((lane & 15) + (o & 15) - 16 * (q & 1));
+                for (int i = 0; i <= DL_TILES; ++i) w[i] = *reinterpret_cast<const i32x4 *>(p + 16 * i);
+                const int x = (lane & 15) + (o & 15);
+                const i32x4 lo = one_at(x), hi = one_at(x - 16);
 #pragma unroll
                 for (int i = 0; i < DL_TILES; ++i)
-                    acc[k][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, w[i], acc[k][i], 0, 0, 0);
+                    acc[k][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(lo, w[i], acc[k][i], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < DL_TILES; ++i)
+                    acc[k][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hi, w[i + 1], acc[k][i], 0, 0, 0);
             }
         }
         // the other buffer was last read before the previous barrier
         if (c0 + DL_CH < nchan) put(stage + (cur ^ 1) * buf_bytes);
         __syncthreads();
     }
+    // Through LDS, a region of the stage for each wave, so that a store covers
+    // 256 consecutive samples (a lane's own blocks are 64 bytes each, 320
+    // bytes apart: half lines of memory).
+    static_assert(4 * DL_WAVES * DL_SPAN <= 2 * DL_CH * (DL_SPAN + 16), "the sums fit the smallest stage");
+    i32x4 *const mem = reinterpret_cast<i32x4 *>(stage) + wave * (DL_SPAN / 4);
 #pragma unroll
     for (int k = 0; k < DL_DMS; ++k) {
         if (mine + k >= dm1) break;
         float *__restrict__ o = out + int64_t(mine + k) * nout;
 #pragma unroll
-        for (int i = 0; i < DL_TILES; ++i) store_tile(o, t0 + 256 * i, first, lane, acc[k][i] + 128 * nchan);
+        for (int i = 0; i < DL_TILES; ++i) mem[4 * (DL_TILES * (lane & 15) + i) + q] = acc[k][i] + 128 * nchan;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int i = 0; i < DL_TILES; ++i) store_sums(o, t0 + 256 * i + 4 * lane, first, mem[64 * i + lane]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -306,7 +324,8 @@ __global__ __launch_bounds__(64 * DD_WAVES) void k_dedisperse(const uint8_t *__r
     }
     float *__restrict__ o = out + int64_t(dm) * nout;
 #pragma unroll
-    for (int i = 0; i < TILES; ++i) store_tile(o, t0 + 256 * i, first, lane, s.acc[i] + 128 * nchan);
+    for (int i = 0; i < TILES; ++i)
+        store_sums(o, t0 + 256 * i + 16 * (lane & 15) + 4 * (lane >> 4), first, s.acc[i] + 128 * nchan);
 }
 
 // A series shorter than the smallest span: one thread per output sample.
@@ -332,7 +351,6 @@ hipError_t launch_spans(const uint8_t *fil, int nchan, int64_t nsamp, const Disp
     return hipGetLastError();
 }
 
-// Row bytes of the LDS form for these trials: the span, the largest spread of
 // Row bytes of the LDS form for these trials: the span and one more piece, the
 // largest spread of a group's delays (at most two samples above that at the
 // lowest channel, whose delays differ most) and the bytes before the first
@@ -355,13 +373,13 @@ hipError_t launch_trials(const uint8_t *fil, int nchan, int64_t nsamp, const Dis
         return hipGetLastError();
     }
     // The LDS form from about half a group of trials (64 channels, 2^22
-    // samples: 8 trials 182 us against 209, 4 trials 175 against 101) and one
-    // workgroup per compute unit on (64 channels, 2^16 samples, 64 trials:
-    // 256 workgroups, 36 us against 44; 64 workgroups, 34 against 26), while
-    // the trials are close enough together for its rows.
+    // samples: 8 trials 176 us against 209, 4 trials 175 against 101) and 2^18
+    // samples of groups on (64 channels, 2^16 samples, 64 trials: 208
+    // workgroups, 36 us against 44; 52 workgroups, 34 against 26), while the
+    // trials are close enough together for its rows.
     const int64_t total = (nout + DL_SPAN - 1) / DL_SPAN * ((ndm + DL_GROUP - 1) / DL_GROUP);
     const int64_t row = lds_row(disp, nchan, ndm);
-    if (nout >= DL_SPAN && total >= 256 && row <= DL_MAX_ROW && ndm >= 7) {
+    if (nout >= DL_SPAN && total >= 205 && row <= DL_MAX_ROW && ndm >= 7) {
         const int64_t per = (total + kDdXcds - 1) / kDdXcds;
         if (per * kDdXcds > 0x7fffffff) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_dedisperse_lds, dim3(unsigned(per * kDdXcds)), dim3(64 * DL_WAVES),
