@@ -79,7 +79,7 @@ __device__ __forceinline__ float2 unpack_bin(float2 zk, float2 zm, const RealFac
     const float2 e = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
     const float2 o = make_float2(0.5f * (zk.y + zm.y), -0.5f * (zk.x - zm.x));
     const float c = float(f.c), s = float(f.s);
-    return make_float2(e.x + fmaf(-o.y, s, o.x * c), e.y + fmaf(o.y, c, o.x * s));
+    return make_float2(e.x + fmaf(o.x, c, -(o.y * s)), e.y + fmaf(o.x, s, o.y * c));  // as cmul
 }
 
 // The larger power of a 2-bin block, a NaN if either is one: powers are
