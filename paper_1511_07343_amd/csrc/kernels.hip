@@ -298,13 +298,13 @@ __global__ __launch_bounds__(fft_threads(LOG2M2) * kR2cGroup) void k_r2c_rows4(c
 // fall in some five buckets, whose LDS atomics run one after the other, and
 // the other 24 bits take three more histograms, scans and four barriers each:
 // that form remains for a bucket of more than kSelectList keys, equal powers
-// for instance.  2^22 bins in blocks of 1024: 25 us against 33; 16 spectra of
-// 2^19 bins: 41 us against 51, with the factors below.)
+// for instance.  2^22 bins in blocks of 1024: 24 us against 33; 16 spectra of
+// 2^19 bins: 41 us against 51, and 32 where X is not stored.)
 constexpr int kMedThreads = 256;
 constexpr int kSelectBuckets = 2048;  // key >> 20; patterns with the sign bit join the last
 constexpr int kSelectList = 512;
 
-struct SelectScratch {
+struct alignas(16) SelectScratch {
     uint32_t hist[kSelectBuckets];
     uint32_t list[kSelectList];
     uint32_t wave_tot[kMedThreads / 64];
@@ -407,18 +407,23 @@ __device__ uint32_t select_next(const uint32_t *u, int n, uint32_t r1, uint32_t 
     return tle >= r1 + 2 ? v1 : tab;
 }
 
-// Cleared before the keys are complete (a barrier follows either).
+// Before the keys; each key is then counted as it is written.
 __device__ __forceinline__ void select_clear(SelectScratch &sc) {
-    for (int i = threadIdx.x; i < kSelectBuckets; i += kMedThreads) sc.hist[i] = 0;
+    uint4 *h = reinterpret_cast<uint4 *>(sc.hist);
+    for (int i = threadIdx.x; i < kSelectBuckets / 4; i += kMedThreads) h[i] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) sc.listed = 0;
+    __syncthreads();
+}
+__device__ __forceinline__ void select_key(uint32_t *u, int i, uint32_t key, SelectScratch &sc) {
+    u[i] = key;
+    atomicAdd(&sc.hist[select_bucket(key)], 1u);
 }
 
-// Median of the n valid keys (mean of the middle pair for even n), in FP64.
-// The histogram is cleared; the barrier after the keys' writes is passed.
+// Median of the n keys written by select_key (mean of the middle pair for even
+// n), in FP64.
 __device__ double median_select(const uint32_t *u, int n, SelectScratch &sc) {
     const int t = threadIdx.x;
     const uint32_t r1 = uint32_t(n - 1) >> 1;
-    for (int i = t; i < n; i += kMedThreads) atomicAdd(&sc.hist[select_bucket(u[i])], 1u);
     __syncthreads();
     pick_bucket<kSelectBuckets / kMedThreads>(r1, sc);
     const uint32_t bucket = sc.pick[0], r = sc.pick[1], nl = sc.pick[2];
@@ -483,10 +488,9 @@ __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__r
         const int64_t k = b0 + i;
         const float2 x = k > 0 ? unpack_bin(Z[k], Z[M - k], f) : make_float2(0.f, 0.f);
         if (X) X[int64_t(blockIdx.y) * M + k] = x;
-        s[i] = __float_as_uint(cnorm(x));
+        select_key(s, i, __float_as_uint(cnorm(x)), sc);
         f.rotate(step);
     }
-    __syncthreads();
     const double m = median_select(s, w, sc);
     if (t == 0) med[blockIdx.x] = m;
 }
@@ -499,8 +503,7 @@ __global__ __launch_bounds__(kMedThreads) void k_median(const float2 *__restrict
     const int64_t b0 = int64_t(blockIdx.x) * W;
     const int w = int(min(int64_t(W), nb - b0));
     select_clear(sc);
-    for (int i = t; i < w; i += kMedThreads) s[i] = __float_as_uint(cnorm(X[b0 + i]));
-    __syncthreads();
+    for (int i = t; i < w; i += kMedThreads) select_key(s, i, __float_as_uint(cnorm(X[b0 + i])), sc);
     const double m = median_select(s, w, sc);
     if (t == 0) med[blockIdx.x] = m;
 }
