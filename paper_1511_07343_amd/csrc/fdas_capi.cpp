@@ -336,7 +336,7 @@ static void free_workspace(Workspace &ws) {
 }
 
 // Trials of a time-domain search whose spectra are formed together: enough
-// to fill the GPU (2^24 samples), and no more than 16 (2^20 samples: 8.6 us a
+// to fill the GPU (2^24 samples), and no more than 16 (2^20 samples: 7.6 us a
 // trial sixteen at a time; with the resampling still a pass of its own 13 us,
 // against 36 us one at a time).
 static int td_trials_together(const fdas_plan_s *p, int64_t nsamp) {

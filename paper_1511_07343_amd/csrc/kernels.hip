@@ -99,7 +99,7 @@ struct PackedSeries {
 // leaves about 1e-14, the second a rounding.  Forming the samples here rather
 // than in a pass of their own saves a write and a read of the series, and the
 // instructions hide under the pass's loads and stores (sixteen trials of 2^20
-// samples: 44 us, against 36 us and 28 us in two passes).
+// samples: 38 us, against 36 us and 28 us in two passes).
 struct ResampledSeries {
     const float *__restrict__ x;
     int n;
@@ -125,12 +125,15 @@ struct ResampledSeries {
         struct __attribute__((packed, aligned(4))) Pair {
             float a, b;
         };
-        const Pair q = *reinterpret_cast<const Pair *>(x + min(max(i, 0), n - 2));
+        const uint32_t at = 4u * min(uint32_t(i), uint32_t(n - 2));
+        const Pair q = *reinterpret_cast<const Pair *>(reinterpret_cast<const char *>(x) + at);
         const bool last = i == n - 1;
         const double f = s - fl;
         const double a = double(last ? q.b : q.a);
         const double b = double(last ? 0.f : q.b);
-        return uint32_t(i) < uint32_t(n) ? float(a * (1.0 - f) + b * f) : 0.f;
+        int keep = uint32_t(i) < uint32_t(n) ? -1 : 0;
+        asm("" : "+v"(keep));  // a mask, so that no branch is put around the load
+        return __int_as_float(__float_as_int(float(a * (1.0 - f) + b * f)) & keep);
     }
     __device__ __forceinline__ float2 operator()(int64_t i) const {
         const double tau0 = fma(double(int(2 * i)), inv_n, -0.5), tau1 = tau0 + inv_n;  // exact
@@ -299,7 +302,8 @@ __global__ __launch_bounds__(fft_threads(LOG2M2) * kR2cGroup) void k_r2c_rows4(c
 // the other 24 bits take three more histograms, scans and four barriers each:
 // that form remains for a bucket of more than kSelectList keys, equal powers
 // for instance.  2^22 bins in blocks of 1024: 24 us against 33; 16 spectra of
-// 2^19 bins: 41 us against 51, and 32 where X is not stored.)
+// 2^19 bins: 41 us against 51, and 29 where X is not stored and the loads of
+// four bins go out together.)
 constexpr int kMedThreads = 256;
 constexpr int kSelectBuckets = 2048;  // key >> 20; patterns with the sign bit join the last
 constexpr int kSelectList = 512;
@@ -484,12 +488,27 @@ __global__ __launch_bounds__(kMedThreads) void k_unpack_median(const float2 *__r
     med += int64_t(blockIdx.y) * gridDim.x;
     select_clear(sc);
     RealFactor f(b0 + t, M);
-    for (int i = t; i < w; i += kMedThreads) {
-        const int64_t k = b0 + i;
-        const float2 x = k > 0 ? unpack_bin(Z[k], Z[M - k], f) : make_float2(0.f, 0.f);
-        if (X) X[int64_t(blockIdx.y) * M + k] = x;
-        select_key(s, i, __float_as_uint(cnorm(x)), sc);
-        f.rotate(step);
+    constexpr int UNR = 4;  // bins per thread whose loads go out together
+    for (int i0 = t; i0 < w; i0 += UNR * kMedThreads) {
+        float2 zk[UNR], zm[UNR];
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) {
+            const int64_t k = b0 + min(i0 + kMedThreads * j, w - 1);
+            zk[j] = Z[k];
+            zm[j] = Z[(M - k) & (M - 1)];  // M is a power of two
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) {
+            const int i = i0 + kMedThreads * j;
+            if (i < w) {
+                float2 x = unpack_bin(zk[j], zm[j], f);
+                if (b0 + i == 0) x = make_float2(0.f, 0.f);
+                if (X) X[int64_t(blockIdx.y) * M + b0 + i] = x;
+                select_key(s, i, __float_as_uint(cnorm(x)), sc);
+            }
+            f.rotate(step);
+        }
     }
     const double m = median_select(s, w, sc);
     if (t == 0) med[blockIdx.x] = m;
@@ -503,7 +522,16 @@ __global__ __launch_bounds__(kMedThreads) void k_median(const float2 *__restrict
     const int64_t b0 = int64_t(blockIdx.x) * W;
     const int w = int(min(int64_t(W), nb - b0));
     select_clear(sc);
-    for (int i = t; i < w; i += kMedThreads) select_key(s, i, __float_as_uint(cnorm(X[b0 + i])), sc);
+    constexpr int UNR = 4;  // bins per thread whose loads go out together
+    for (int i0 = t; i0 < w; i0 += UNR * kMedThreads) {
+        float2 x[UNR];
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) x[j] = X[b0 + min(i0 + kMedThreads * j, w - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < UNR; ++j)
+            if (i0 + kMedThreads * j < w) select_key(s, i0 + kMedThreads * j, __float_as_uint(cnorm(x[j])), sc);
+    }
     const double m = median_select(s, w, sc);
     if (t == 0) med[blockIdx.x] = m;
 }
