@@ -30,19 +30,23 @@ __device__ __forceinline__ double median_curve(const double *__restrict__ med, i
     const double lo = med[b], hi = med[min(b + 1, last)];
     const double cb = c0 + double(b) * double(W);
     const double f = (x - cb) * (b + 1 == last ? inv_last : inv_w);
-    return x <= c0 ? lo : x >= cl ? hi : lo + (hi - lo) * f;
+    double mid = lo + (hi - lo) * f;
+    asm("" : "+v"(mid));  // selected, not formed behind a branch that the loads are waited for at
+    return x <= c0 ? lo : x >= cl ? hi : mid;
 }
 
-// The normalising factor sqrt(ln 2 / m) in FP64 (0 where m is not positive):
-// the hardware's reciprocal square root and two Newton steps, to a rounding or
-// two of the division and square root, which take three times as long.
+// The normalising factor sqrt(ln 2 / m) in FP64 (0 where m is not positive, or
+// infinite): the hardware's reciprocal square root and two Newton steps, to a
+// rounding or two of the division and square root, which take three times as
+// long.  m lies between medians of single-precision powers, well inside the
+// range of the steps; no branches, as above.
 __device__ __forceinline__ double norm_scale(double m) {
-    if (!(m > 0.0)) return 0.0;
-    if (!(m > 1e-280 && m < 1e280)) return sqrt(kLn2 / m);
     double r = __builtin_amdgcn_rsq(m);
     r = fma(0.5 * r, fma(-m * r, r, 1.0), r);
     r = fma(0.5 * r, fma(-m * r, r, 1.0), r);
-    return 0.83255461115769775635 * r;  // sqrt(ln 2)
+    r *= 0.83255461115769775635;  // sqrt(ln 2)
+    asm("" : "+v"(r));
+    return m > 0.0 && m < __builtin_inf() ? r : 0.0;
 }
 
 // Screening code of a power: floor(P / delta) + 1, at most 255, with
