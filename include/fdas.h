@@ -346,8 +346,9 @@ fdas_status fdas_refine(fdas_plan_t *plan, fdas_cand *cands, int64_t n, int32_t 
  * that forbid hipMalloc).  Same arguments, refinement and results as
  * fdas_refine (bit-identical: the same kernels), but the records and their
  * count are staged in a fixed device array that the library holds for the
- * life of the process, FDAS_REFINE_NOALLOC_MAX records large (one array per
- * GPU), instead of a per-call allocation; nothing is allocated or freed.
+ * life of the process, FDAS_REFINE_NOALLOC_MAX records and the scratch of
+ * 2048 large (4.9 MB, one array per GPU), instead of a per-call allocation;
+ * nothing is allocated or freed.
  * INVAL when n > FDAS_REFINE_NOALLOC_MAX or when the current device is not
  * the plan's, besides fdas_refine's own INVAL cases.  Every call on one GPU
  * uses that GPU's one array: calls that overlap on a GPU (from several
