@@ -29,7 +29,8 @@ hipError_t launch_dft(int log2n, int dir, int64_t batch, const float2 *in, float
 // laid out one after the other, in x, Z and work.
 hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *work, hipStream_t st, int batch = 1);
 
-// Unpack Z into the real-input spectrum X[k], k in [0, M) (X[0] = 0; not
+// Unpack Z into the real-input spectrum X[k], k in [0, M), M = nsamp / 2 a
+// power of two (X[0] = 0; not
 // stored if X is null), and the median of |X|^2 over each block of W bins
 // (FP64 out); batch as above.
 hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st,
