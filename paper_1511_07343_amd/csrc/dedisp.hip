@@ -2,6 +2,7 @@
 // dispersion-measure trial): the channels of a channel-major 8-bit
 // filterbank shifted by their per-DM sample delays and added, in exact
 // integer arithmetic on the matrix cores.
+#include "delays.hpp"
 #include "kernels.hpp"
 
 #include <algorithm>
@@ -16,42 +17,7 @@ typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // rows start at any float
 
 constexpr int kDdXcds = 8;
-constexpr int DD_LAUNCH_DMS = 256;  // DM trials per launch (passed by value)
 constexpr int kFlip = int(0x80808080u);  // b -> b - 128 as signed bytes
-
-// What the delays are formed from; kdm[i] is the dispersion constant times DM i.
-struct Dispersion {
-    double f_top, foff, inv_top2, tsamp, inv_tsamp;  // inv_top2 = 1 / f_top^2
-    double kdm[DD_LAUNCH_DMS];
-};
-
-// Delay of channel c: floor(kdm (1 / f_c^2 - 1 / f_top^2) / tsamp + 1/2), each
-// operation rounded by itself, the same on the host and the device.
-__host__ __device__ inline int32_t delay_of(const Dispersion &p, double kdm, int c) {
-#pragma clang fp contract(off)
-    const double f = p.f_top - p.foff * double(c);
-    const double raw = kdm * (1.0 / (f * f) - p.inv_top2) / p.tsamp;
-    return int32_t(floor(raw + 0.5));
-}
-
-// The same without its divisions, which take most of its time: two Newton
-// steps on the reciprocal of f^2 and a product with 1 / tsamp differ from the
-// rounded operations by less than 2^-46 of kdm / (f^2 tsamp); a sum closer
-// than that to a whole number (as with DM 0) is formed by delay_of.
-__device__ __forceinline__ int32_t delay_fast(const Dispersion &p, double kdm, int c) {
-    const double f = p.f_top - p.foff * double(c);
-    const double f2 = f * f;
-    double y = __builtin_amdgcn_rcp(f2);
-    y = fma(fma(-f2, y, 1.0), y, y);
-    y = fma(fma(-f2, y, 1.0), y, y);
-    const double scale = kdm * p.inv_tsamp;
-    const double x = fma(scale, y - p.inv_top2, 0.5);
-    const double fl = floor(x), off = x - fl;
-    const double slack = scale * y * 0x1p-46 + 0x1p-46;
-    int32_t d = int32_t(fl);
-    if (__any(off < slack || off > 1.0 - slack)) d = delay_of(p, kdm, c);
-    return d;
-}
 
 // 16 bytes, all 0 but a 1 at byte `at` (none outside 0 .. 15).
 __device__ __forceinline__ i32x4 one_at(int at) {
