@@ -58,9 +58,11 @@ __host__ __device__ __forceinline__ bool any_lane(bool yes) {
 }
 
 // The same without its divisions, which take most of its time: of the same
-// f^2, two Newton steps on its reciprocal and a product with 1 / tsamp differ from the
-// rounded operations by less than 2^-46 of kdm / (f^2 tsamp); a sum closer
-// than that to a whole number (as with DM 0) is formed by delay_of.
+// f^2, two Newton steps on its reciprocal and a product with 1 / tsamp differ
+// from the rounded operations by less than 2^-46 of kdm / (f^2 tsamp) (2^-1016
+// of kdm / tsamp where 1 / f^2 is not a normal number).  A sum closer than
+// that to a whole number (as with DM 0) is formed by delay_of, and so is one
+// for which the comparison fails: factors may overflow though the delay is 0.
 __host__ __device__ __forceinline__ int32_t delay_fast(const Dispersion &p, double kdm, int c) {
     const double f2 = squared_frequency(p, c);
     double y = short_reciprocal(f2);
@@ -69,9 +71,10 @@ __host__ __device__ __forceinline__ int32_t delay_fast(const Dispersion &p, doub
     const double scale = kdm * p.inv_tsamp;
     const double x = fma(scale, y - p.inv_top2, 0.5);
     const double fl = floor(x), off = x - fl;
-    const double slack = scale * y * 0x1p-46 + 0x1p-46;
-    int32_t d = int32_t(fl);
-    if (any_lane(off < slack || off > 1.0 - slack)) d = delay_of(p, kdm, c);
+    const double slack = scale * (y + 0x1p-970) * 0x1p-46 + 0x1p-46;
+    int32_t d = 0;
+    if (any_lane(!(off >= slack && off <= 1.0 - slack))) d = delay_of(p, kdm, c);
+    else d = int32_t(fl);
     return d;
 }
 

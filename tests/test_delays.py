@@ -77,3 +77,22 @@ def test_delays_match_the_oracle(delays):
     for i, dm in enumerate(dms):
         fast, exact = delays(f_top, foff, tsamp, np.full(nchan, 4.148808e3 * dm), np.arange(nchan))
         assert np.array_equal(fast, want[i]) and np.array_equal(exact, want[i])
+
+
+@pytest.mark.parametrize("f_top,foff,tsamp,dms,nchan", [
+    (1500.0, 0.0, 1e-310, [0.0, 10.0, 3e5], 8),    # 1 / tsamp overflows; every channel at f_top, every delay 0
+    (1500.0, 0.0, 1e-300, [1.0, 1e9], 8),          # k DM / tsamp overflows
+    (1500.0, 10.0, 1e-310, [0.0], 8),
+    (1e160, 0.0, 1e-3, [0.0, 50.0], 3),            # f^2 overflows
+    (1e160, 1e157, 1e-3, [0.0, 50.0], 3),
+    (1e-152, 0.0, 1e-3, [0.0, 50.0], 3),           # f^2 has no finite square of its reciprocal
+    (9.9e153, 0.0, 1e-300, [1e3], 3),              # 1 / f^2 is subnormal
+    (1500.0, 10.0, float("inf"), [0.0, 50.0], 8),
+])
+def test_delays_at_the_ends_of_the_range(delays, f_top, foff, tsamp, dms, nchan):
+    """Accepted inputs (every delay 0) where a factor overflows or vanishes."""
+    c = np.arange(nchan)
+    for dm in dms:
+        fast, exact = delays(f_top, foff, tsamp, np.full(nchan, 4.148808e3 * dm), c)
+        assert np.all(exact == 0)
+        assert np.array_equal(fast, exact)
