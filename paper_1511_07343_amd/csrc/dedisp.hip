@@ -17,6 +17,32 @@ typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // rows start at any float
 
 constexpr int kDdXcds = 8;
+
+// The work items of one launch: workgroup i takes item
+// first + (i mod 8) per + i div 8 if that lies below end, so that neighbouring
+// items share an XCD's L2.
+struct Items {
+    int64_t first, end, per;
+    __device__ __forceinline__ int64_t mine() const {
+        return first + int64_t(blockIdx.x % kDdXcds) * per + blockIdx.x / kDdXcds;
+    }
+};
+
+// launch(grid, items) for all of `total` work items, a workgroup of `threads`
+// threads each, in as few launches as the runtime takes (a grid has less than
+// 2^32 threads).
+template <class Launch>
+hipError_t launch_items(int64_t total, int threads, Launch launch) {
+    const int64_t most = int64_t(0xffffffffu) / threads / kDdXcds * kDdXcds;
+    for (int64_t first = 0; first < total; first += most) {
+        const int64_t n = std::min(most, total - first), per = (n + kDdXcds - 1) / kDdXcds;
+        launch(unsigned(per * kDdXcds), Items{first, first + n, per});
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 constexpr int kFlip = int(0x80808080u);  // b -> b - 128 as signed bytes
 
 // 16 bytes, all 0 but a 1 at byte `at` (none outside 0 .. 15).
@@ -88,11 +114,10 @@ static_assert(DL_DMS + 1 <= 4, "a wave evaluates its trials' and the smallest de
 
 __global__ __launch_bounds__(64 * DL_WAVES, 4) void k_dedisperse_lds(const uint8_t *__restrict__ fil, int nchan,
                                                                   int64_t nsamp, Dispersion disp, int ndm, int64_t nout,
-                                                                  int row, int64_t total, int64_t per,
-                                                                  float *__restrict__ out) {
+                                                                  int row, Items items, float *__restrict__ out) {
     extern __shared__ __align__(16) uint8_t stage[];  // 2 x DL_CH rows of `row` bytes
-    const int64_t u = int64_t(blockIdx.x % kDdXcds) * per + blockIdx.x / kDdXcds;
-    if (u >= total) return;
+    const int64_t u = items.mine();
+    if (u >= items.end) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int q = lane >> 4;
@@ -259,11 +284,11 @@ struct ChannelSums {
 
 template <int TILES, bool SPLIT>
 __global__ __launch_bounds__(64 * DD_WAVES) void k_dedisperse(const uint8_t *__restrict__ fil, int nchan, int64_t nsamp,
-                                                              Dispersion disp, int ndm, int64_t nout, int64_t total,
-                                                              int64_t per, float *__restrict__ out) {
+                                                              Dispersion disp, int ndm, int64_t nout, Items items,
+                                                              float *__restrict__ out) {
     constexpr int SPAN = 256 * TILES;
-    const int64_t u = int64_t(blockIdx.x % kDdXcds) * per + blockIdx.x / kDdXcds;
-    if (u >= total) return;
+    const int64_t u = items.mine();
+    if (u >= items.end) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ngrp = SPLIT ? ndm : (ndm + DD_WAVES - 1) / DD_WAVES;
@@ -310,11 +335,10 @@ hipError_t launch_spans(const uint8_t *fil, int nchan, int64_t nsamp, const Disp
                         float *out, hipStream_t st) {
     const int64_t spans = (nout + 256 * TILES - 1) / (256 * TILES);
     const int64_t total = spans * (SPLIT ? ndm : (ndm + DD_WAVES - 1) / DD_WAVES);
-    const int64_t per = (total + kDdXcds - 1) / kDdXcds;
-    if (per * kDdXcds > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_dedisperse<TILES, SPLIT>), dim3(unsigned(per * kDdXcds)), dim3(64 * DD_WAVES), 0, st, fil,
-                       nchan, nsamp, disp, ndm, nout, total, per, out);
-    return hipGetLastError();
+    return launch_items(total, 64 * DD_WAVES, [&](unsigned grid, Items items) {
+        hipLaunchKernelGGL((k_dedisperse<TILES, SPLIT>), dim3(grid), dim3(64 * DD_WAVES), 0, st, fil, nchan, nsamp, disp,
+                           ndm, nout, items, out);
+    });
 }
 
 // Row bytes of the LDS form for these trials: the span and one more piece, the
@@ -346,11 +370,10 @@ hipError_t launch_trials(const uint8_t *fil, int nchan, int64_t nsamp, const Dis
     const int64_t total = (nout + DL_SPAN - 1) / DL_SPAN * ((ndm + DL_GROUP - 1) / DL_GROUP);
     const int64_t row = lds_row(disp, nchan, ndm);
     if (nout >= DL_SPAN && total >= 205 && row <= DL_MAX_ROW && ndm >= 7) {
-        const int64_t per = (total + kDdXcds - 1) / kDdXcds;
-        if (per * kDdXcds > 0x7fffffff) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_dedisperse_lds, dim3(unsigned(per * kDdXcds)), dim3(64 * DL_WAVES),
-                           size_t(2 * DL_CH * row), st, fil, nchan, nsamp, disp, ndm, nout, int(row), total, per, out);
-        return hipGetLastError();
+        return launch_items(total, 64 * DL_WAVES, [&](unsigned grid, Items items) {
+            hipLaunchKernelGGL(k_dedisperse_lds, dim3(grid), dim3(64 * DL_WAVES), size_t(2 * DL_CH * row), st, fil, nchan,
+                               nsamp, disp, ndm, nout, int(row), items, out);
+        });
     }
     // Otherwise spans of 1024 samples, a wave each, or spans of 256 with the
     // channels split over a workgroup's waves.  The split is for work too
