@@ -1709,9 +1709,12 @@ hipError_t launch_harmsum(const float *plane, const uint8_t *codes, int nz, int6
     const int64_t cols = int64_t(SC_WAVE_COLS) * SC_WAVES, ncolt = (nb + cols - 1) / cols;
     const int rows = int(std::max<int64_t>(1, std::min<int64_t>(SC_TZ, ncolt * nz / 2048)));
     const dim3 grid1(unsigned(ncolt), unsigned((nz + rows - 1) / rows));
-    // a step of the exact sums and the neighbour test for every 2^14 plane
-    // cells, so that a small plane's launches are small too
-    const unsigned grid2 = unsigned(std::min<int64_t>(2048, std::max<int64_t>(64, (int64_t(nz) * nb) >> 14)));
+    // The exact sums and the neighbour test loop over lists whose lengths only
+    // the device knows, and any plane may be dense: 21 templates x 2^14
+    // columns with 19577 records 122 us a search, 214 with a workgroup for
+    // every 2^14 cells; x 2^18 with 91189 records 275 and 362; nothing listed,
+    // 51 us either way.
+    const unsigned grid2 = 2048;
 #define CALL(LV)                                                                                                   \
     hipLaunchKernelGGL((k_screen<LV>), grid1, dim3(64 * SC_WAVES), 0, st, codes, nz, nb, rows, izc, T, groups, blocks, \
                        group_map, count, group_cap, cell_cap);                                                     \
