@@ -49,14 +49,16 @@ __device__ __forceinline__ double norm_scale(double m) {
     return m > 0.0 && m < __builtin_inf() ? r : 0.0;
 }
 
-// Screening code of a power: floor(P / delta) + 1, at most 255, with
-// code_inv = 1 / delta: above P / delta (a fused multiply-add rounds
-// monotonically, so also after its rounding; a conversion that rounded to
-// nearest would bound it too), so integer sums of codes bound power sums from
-// above; NaN and huge powers saturate at 255 (the minimum drops a NaN).
-// Inserted as byte `b` of w: three instructions a code.
+// Screening code of a power: P / delta, code_inv = 1 / delta, rounded up, at
+// most 255, so integer sums of codes bound power sums from above (up to one
+// FP32 rounding of the sum below, which the thresholds in code units leave room
+// for); NaN and huge powers saturate at 255 (the minimum drops a NaN).  The
+// conversion rounds to the nearest integer, hence the half: with a whole unit
+// the codes come out half a unit high, and the screen passes 28 % more cells
+// on at 3 sigma, 16 harmonics (762078 against 597532 of 2^18 columns x 21
+// templates).  Inserted as byte `b` of w: three instructions a code.
 __device__ __forceinline__ uint32_t put_code(float pw, float code_inv, int b, uint32_t w) {
-    return __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaf(pw, code_inv, 1.f), 255.f), uint32_t(b), w);
+    return __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaf(pw, code_inv, 0.5f), 255.f), uint32_t(b), w);
 }
 
 // exp(-2 pi i k / 2M), which separates the spectrum of a real series of 2M

@@ -53,7 +53,7 @@ hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t n
 //   y = IDFT_S(segspec[s] * bank[iz]) (unnormalised; bank carries 1/S),
 //   plane[iz][s L + n - h] = |y[n]|^2 for n in [h, h + L), inside [0, nb),
 // and beside it the screening codes of 2-bin blocks (nz x nb/2 bytes)
-//   codes[iz][b] = max_{k in {2b, 2b + 1}} min(255, floor(plane[iz][k] * code_inv) + 1).
+//   codes[iz][b] = max_{k in {2b, 2b + 1}} min(255, ceil(plane[iz][k] * code_inv)).
 // With bank_half (the half-bin offsets' bank) each plane row holds 2 nb
 // floats, the bins k from bank in [0, nb) and the points k + 1/2 from
 // bank_half in [nb, 2 nb), and the nz x nb codes cover the pairs
