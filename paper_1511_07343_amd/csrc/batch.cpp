@@ -497,14 +497,20 @@ extern "C" fdas_status fdas_search_batch(fdas_plan_t *plan, int32_t n, const flo
 
     fdas_status first_err = FDAS_OK;
     bool overflow = false;
+    // A batch's trials are much alike: after one with a long list, the next
+    // ones' long-list kernels are enqueued behind their graphs, and the host
+    // need not wait for their counters first.
+    bool expect_long = false;
+    bool enqueued_all[2] = {false, false};
     // Finish trial j: its counters are on the host (event ev[j % 2]); sort a
-    // long list and copy the records.
+    // long list that is not sorted yet and copy the records.
     auto finish = [&](int32_t j) -> fdas_status {
         const int slot = j % 2;
         hipError_t ee = hipEventSynchronize(plan->events[slot]);
         if (ee != hipSuccess) return hip_fail(plan, ee, "batch trial");
         fdas_status r = FDAS_OK;
-        if (long_list(plan, slot_ws(plan, slot)) && !finishes_all(plan, false))
+        expect_long = long_list(plan, slot_ws(plan, slot)) && !finishes_all(plan, false);
+        if (expect_long && !enqueued_all[slot])
             r = finish_rest(plan, slot_ws(plan, slot), nsamp[j], nullptr, plan->aux[slot]);
         if (r != FDAS_OK) return r;
         r = copy_candidates(plan, slot_ws(plan, slot), cands_host + offset[size_t(j)], cap[j], &ncands[j],
@@ -531,6 +537,11 @@ extern "C" fdas_status fdas_search_batch(fdas_plan_t *plan, int32_t n, const flo
         if (e != hipSuccess) {
             first_err = hip_fail(plan, e, "batch trial launch");
             break;
+        }
+        enqueued_all[slot] = expect_long;
+        if (expect_long) {
+            first_err = finish_rest(plan, ws, nsamp[i], nullptr, plan->aux[slot]);
+            if (first_err != FDAS_OK) break;
         }
         e = hipEventRecord(plan->events[slot], plan->aux[slot]);
         if (e != hipSuccess) {

@@ -1,0 +1,71 @@
+"""Lists of more than 4096 records, foreseen or not while a search runs: the
+records are those of a timed search, which enqueues every kernel at once."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SMALL = 4096  # records finished by the one-kernel form
+
+
+def _tones(nb, ntones, k_min, seed, noise=0.0):
+    rng = np.random.default_rng(seed)
+    X = (noise * (rng.standard_normal(nb) + 1j * rng.standard_normal(nb))).astype(np.complex64)
+    k = k_min + 8 * rng.permutation((nb - k_min) // 8 - 1)[:ntones]
+    X[k] = (10.0 + 30.0 * rng.random(ntones)) * np.exp(2j * np.pi * rng.random(ntones))
+    return X
+
+
+@pytest.mark.parametrize("zmax,dz,nharm,ntones,k_min,noise,long_list,many_cells", [
+    (0.0, 1.0, 16, 600, 1 << 14, 0.0, True, False),   # five records for the two cells of a tone: not foreseen
+    (10.0, 1.0, 1, 1000, 8, 0.3, False, True),         # many cells, few of them maxima: foreseen in vain
+    (10.0, 1.0, 4, 3000, 8, 0.3, True, True),
+])
+def test_lists_foreseen_or_not(gpu_lib, zmax, dz, nharm, ntones, k_min, noise, long_list, many_cells):
+    import torch
+    nb = 1 << 15
+    bank = gpu_lib.make_templates(zmax, dz)
+    plan = gpu_lib.Plan(bank, 2 * nb, 256, nharm_max=nharm, sigma=6.0, cand_capacity=1 << 18)
+    X = torch.from_numpy(_tones(nb, ntones, k_min, ntones, noise)).cuda()
+    kind = gpu_lib.IN_SPECTRUM_NORMALISED
+    plan.enable_timing(True)
+    want, found = plan.search(X, kind=kind)
+    plan.enable_timing(False)
+    _, cells, _ = plan.search_counts()
+    assert found == len(want) and (found > SMALL) == long_list and (cells > 2 * SMALL) == many_cells
+    key = (np.log2(want["nharm"]).astype(np.int64) * nb + want["k"]) * bank.nz + want["iz"]
+    assert np.all(np.diff(key) > 0)
+    for _ in range(3):
+        pageable, n = plan.search(X, kind=kind)
+        assert n == found and np.array_equal(pageable, want)
+        pinned, n = plan.search(X, kind=kind, out=gpu_lib.pinned_candidates(found))
+        assert n == found and np.array_equal(pinned, want)
+        for cap in (0, 100, SMALL + 1, found - 1):
+            short, n = plan.search(X, kind=kind, cap=cap, allow_overflow=True)
+            assert n == found and np.array_equal(short, want[:cap])
+    plan.close()
+    bank.close()
+
+
+@pytest.mark.parametrize("order", ["lsslllslss", "sl", "lll", "l"])
+def test_batch_of_long_and_short_lists(gpu_lib, order):
+    import torch
+    n = 1 << 16
+    bank = gpu_lib.make_templates(10.0, 1.0)
+    plan = gpu_lib.Plan(bank, n, 256, nharm_max=4, sigma=6.0, median_window=256, cand_capacity=1 << 17)
+    rng = np.random.default_rng(len(order))
+    xs = []
+    for c in order:
+        spec = np.fft.rfft(rng.standard_normal(n))
+        if c == "l":
+            spec[8 * (1 + rng.permutation(n // 16 - 2)[:1500])] += 40.0 * np.sqrt(n)
+        xs.append(torch.from_numpy(np.fft.irfft(spec, n).astype(np.float32)).cuda())
+    want = [plan.search(x)[0] for x in xs]
+    assert [len(w) > SMALL for w in want] == [c == "l" for c in order]
+    caps = [len(w) + 1 for w in want]
+    pinned = gpu_lib.pinned_candidates(sum(caps))
+    for _ in range(2):
+        for got in (plan.search_batch(xs, caps=caps), plan.search_batch(xs, caps=caps, out=pinned)):
+            assert all(np.array_equal(g, w) for g, w in zip(got, want))
+    plan.close()
+    bank.close()
