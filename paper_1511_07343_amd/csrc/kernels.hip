@@ -861,6 +861,8 @@ constexpr int SC_TZ = 8;      // most rows per wave
 constexpr int SC_WAVES = 4;   // waves per workgroup
 constexpr int SC_COLS = 32;   // columns per lane (one group)
 constexpr int SC_WAVE_COLS = 64 * SC_COLS;
+// A tile's LDS: row masks, then the waves' totals and the workgroup's places.
+constexpr int SC_LDS_WORDS = SC_WAVES * SC_TZ * 64 + SC_WAVES + 2;
 
 // 0x8000 - T_0, then T_(l-1) - T_l, times 0x10001 modulo 2^32: added level by
 // level to the sums of both halves, which stay below 2^16 throughout.
@@ -965,7 +967,7 @@ using FracAll = FracSet<std::make_integer_sequence<int, 16>>;
 
 // Screen tile (bx, by) of a workgroup of 64 SC_WAVES threads: columns
 // [bx SC_WAVES 2048, + SC_WAVES 2048), rows [by tile_rows, + tile_rows),
-// tile_rows <= SC_TZ.  rowmask_lds: SC_WAVES SC_TZ 64 words of LDS.
+// tile_rows <= SC_TZ.  rowmask_lds: SC_LDS_WORDS words of LDS.
 template <int LEVELS>
 __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, int by, int tile_rows,
                                             const uint8_t *__restrict__ Q,
@@ -981,12 +983,13 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
     const int64_t ngr = nb / SC_COLS;
     const int64_t qlen = nb / 2;  // codes per row
     const bool valid = m < ngr;
-    if (!__any(valid) || rows <= 0) return;
+    if (rows <= 0) return;
     const uint32_t mm = valid ? uint32_t(m) : 0u;  // lanes past the end read group 0 and report nothing
     uint32_t *__restrict__ rowmask = rowmask_lds + wave * (SC_TZ * 64) + lane;  // row r at rowmask[64 r]
     uint32_t mycells = 0, mygroups = 0;
+    const int last = __any(valid) ? rows : 0;  // none for a wave past the end, which meets the barriers only
 #pragma unroll 1
-    for (int r = 0; r < rows; ++r) {
+    for (int r = 0; r < last; ++r) {
         const int iz = iz0 + r;
         const int d = iz - izc;
         FracAll fs;
@@ -1024,27 +1027,41 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
         mygroups += mask != 0 ? 1u : 0u;
     }
     // One group record per (lane, row) with flagged blocks; a lane's records
-    // and cells get consecutive indices.  One atomic per wave reserves both
-    // lists; crossing a capacity raises the overflow flag at once (so a count
-    // that later wraps cannot hide it).  (Each lane reads back only its own
-    // LDS words, so no barrier is needed.)
-    if (!__any(mycells != 0)) return;
-    // cells (<= 32 SC_TZ 64 = 16384) in the low half, groups in the high half
+    // and cells get consecutive indices.  One atomic per workgroup reserves
+    // both lists: all atomics meet on one address, and with one per wave tiles
+    // of a row each, as planes of few columns have, waited for them longer than
+    // the sums take where most waves flag something (2^17 columns x 101 rows
+    // with a pulsar, 16 harmonics, 61 us against 26).  Crossing a capacity
+    // raises the overflow flag at once (so a count that later wraps cannot hide
+    // it).  (Each lane reads back only its own row masks.)
+    // per wave: cells (<= 32 SC_TZ 64 = 16384) in the low half, groups in the high half
     const uint32_t incl = wave_scan((mygroups << 16) | mycells);
-    const uint32_t total = __shfl(incl, 63);
-    uint32_t cbase = 0, gbase = 0;
-    if (lane == 0) {
-        const uint32_t tc = total & 0xffffu, tg = total >> 16;
+    uint32_t *__restrict__ totals = rowmask_lds + SC_WAVES * SC_TZ * 64;
+    if (lane == 63) totals[wave] = incl;
+    __syncthreads();
+    uint32_t first = (incl & 0xffffu) - mycells, g = (incl >> 16) - mygroups, tc = 0, tg = 0;
+#pragma unroll
+    for (int w = 0; w < SC_WAVES; ++w) {
+        const uint32_t c = totals[w] & 0xffffu, n = totals[w] >> 16;
+        first += w < wave ? c : 0u;
+        g += w < wave ? n : 0u;
+        tc += c;
+        tg += n;
+    }
+    if (tc == 0) return;
+    if (threadIdx.x == 0) {
         const unsigned long long old = atomicAdd(reinterpret_cast<unsigned long long *>(cnt + CNT_PAIR),
                                                  (static_cast<unsigned long long>(tg) << 32) | tc);
-        cbase = uint32_t(old);
-        gbase = uint32_t(old >> 32);
+        const uint32_t cbase = uint32_t(old), gbase = uint32_t(old >> 32);
+        totals[SC_WAVES] = cbase;
+        totals[SC_WAVES + 1] = gbase;
         if (uint64_t(cbase) + tc > cell_cap || uint64_t(gbase) + tg > group_cap) cnt[CNT_OVERFLOW] = 1u;
     }
-    uint32_t first = __shfl(cbase, 0) + (incl & 0xffffu) - mycells;
-    uint32_t g = __shfl(gbase, 0) + (incl >> 16) - mygroups;
+    __syncthreads();
+    first += totals[SC_WAVES];
+    g += totals[SC_WAVES + 1];
 #pragma unroll 1
-    for (int r = 0; r < rows; ++r) {
+    for (int r = 0; r < last; ++r) {
         const uint32_t mask = rowmask[64 * r];
         if (mask == 0) continue;
         const uint32_t ncell = 2u * __popc(mask);
@@ -1073,7 +1090,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 3) void k_screen(const uint8_t *__re
                                                           uint32_t *__restrict__ cnt, uint32_t group_cap,
                                                           uint32_t cell_cap) {
     // Row masks of the waves, kept until their records are written.
-    __shared__ uint32_t rowmask_lds[SC_WAVES * SC_TZ * 64];
+    __shared__ uint32_t rowmask_lds[SC_LDS_WORDS];
     screen_tile<LEVELS>(rowmask_lds, blockIdx.x, blockIdx.y, tile_rows, Q, nz, nb, izc, T, groups, blocks, group_map, cnt,
                         group_cap, cell_cap);
 }
@@ -1390,7 +1407,7 @@ __global__ __launch_bounds__(256, 2) void k_batch(BatchArgs a) {
     using Sh = FftShape<LOG2S, 256>;
     static_assert(corr_threads(LOG2S) == 256 && fft_threads(LOG2S) == 256, "256-thread transforms");
     static_assert(SC_WAVES * 64 == 256, "screen tiles of 256 threads");
-    static_assert(Sh::LDS_FLOAT2 * 2 >= SC_WAVES * SC_TZ * 64, "screen masks fit the transform buffer");
+    static_assert(Sh::LDS_FLOAT2 * 2 >= SC_LDS_WORDS, "screen masks fit the transform buffer");
     static_assert(Sh::LDS_FLOAT2 * sizeof(float2) >= PK_STAGE * sizeof(DevCand), "candidates fit the transform buffer");
     __shared__ float2 lds[Sh::LDS_FLOAT2];
     __shared__ uint32_t tinfo[3];
