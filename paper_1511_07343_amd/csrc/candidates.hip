@@ -315,7 +315,7 @@ hipError_t launch_finish_large(const FinishArgs &a, void *scratch, hipStream_t s
     // threads than records (about two each for 241 k records) a wave's writes
     // of one record go out while it computes its next significance, instead
     // of every significance first and then all the writes (about 12 us less).
-    const uint64_t gmax = a.count_dst ? 512 : 1024;
+    const uint64_t gmax = a.to_host ? 512 : 1024;
     const unsigned grid = unsigned(blocks < gmax ? blocks : gmax);
     hipLaunchKernelGGL(k_cand_keys, dim3(RS_BLOCKS), dim3(RS_THREADS), 0, st, a.dc, a.count, cap, a.nb, a.nz, k0, v0,
                        hist);

@@ -138,6 +138,7 @@ static FinishArgs finish_args(const fdas_plan_s *p, const Workspace &ws, const D
     FinishArgs a = finish_args(p, dc, count, ncol);
     a.out = direct ? direct->out : ws.final;
     if (direct) a.out_cap = direct->cap;
+    a.to_host = direct != nullptr;
     a.count_dst = ws.d_h_count;
     return a;
 }

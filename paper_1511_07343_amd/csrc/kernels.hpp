@@ -134,6 +134,7 @@ struct FinishArgs {
     double zmax, dz;
     fdas_cand *out;
     uint32_t out_cap;
+    bool to_host;  // out is host memory
     uint32_t *count_dst;
 };
 // Lists of at most this many records are finished by launch_finish_small;
