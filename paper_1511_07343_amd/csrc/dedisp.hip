@@ -362,14 +362,23 @@ hipError_t launch_trials(const uint8_t *fil, int nchan, int64_t nsamp, const Dis
                            int(nout), out);
         return hipGetLastError();
     }
-    // The LDS form from about half a group of trials (64 channels, 2^22
-    // samples: 8 trials 176 us against 209, 4 trials 175 against 101) and 2^18
-    // samples of groups on (64 channels, 2^16 samples, 64 trials: 208
-    // workgroups, 36 us against 44; 52 workgroups, 34 against 26), while the
-    // trials are close enough together for its rows.
-    const int64_t total = (nout + DL_SPAN - 1) / DL_SPAN * ((ndm + DL_GROUP - 1) / DL_GROUP);
+    // The LDS form while the trials are close enough together for its rows.
+    // Its time hardly depends on how many trials a group has nor, up to the 256
+    // workgroups that run at once, on how many spans there are; that of the
+    // direct forms is proportional to both.  Groups of ten trials and more
+    // cross at about 2048 spans times trials (staged and direct, 64 channels:
+    // 16 trials, 100 spans 35.8 us and 33.5, 120 spans 36.2 and 36.4, 160 spans
+    // 36.4 and 41.2; 33 trials, 60 spans 36.4 and 36.6; 10 trials, 205 spans
+    // 35.8 and 36.5; 257 channels, 16 trials, 120 spans 85.9 and 79.9, 140
+    // spans 85.8 and 89.6).  Groups half empty, whose waves are half idle, cross
+    // only with several workgroups a compute unit (257 channels: 8 trials, 205
+    // spans 84.9 and 70.4, 410 spans 105.7 and 133.8; 7 trials, 520 spans 157.9
+    // and 122.7, 1000 spans 205 and 260).
+    const int64_t spans = (nout + DL_SPAN - 1) / DL_SPAN, groups = (ndm + DL_GROUP - 1) / DL_GROUP;
+    const int64_t least = ndm >= 10 * groups ? 2048 : ndm >= 8 * groups ? 3200 : 7000;
     const int64_t row = lds_row(disp, nchan, ndm);
-    if (nout >= DL_SPAN && total >= 205 && row <= DL_MAX_ROW && ndm >= 7) {
+    if (nout >= DL_SPAN && ndm >= 7 && spans * ndm >= least && row <= DL_MAX_ROW) {
+        const int64_t total = spans * groups;
         return launch_items(total, 64 * DL_WAVES, [&](unsigned grid, Items items) {
             hipLaunchKernelGGL(k_dedisperse_lds, dim3(grid), dim3(64 * DL_WAVES), size_t(2 * DL_CH * row), st, fil, nchan,
                                nsamp, disp, ndm, nout, int(row), items, out);
