@@ -7,6 +7,7 @@
 #include "device_common.hpp"
 #include "fft_wg.hpp"
 #include "kernels.hpp"
+#include "resample.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -88,15 +89,9 @@ struct PackedSeries {
     __device__ __forceinline__ float2 operator()(int64_t i) const { return z[i]; }
 };
 
-// Trials of the time-domain search: y[m] = x at position s_m = N (v_m + 1/2),
-// v_m + alpha v_m^2 / 2 = tau_m = m / N - 1/2, the time axis on which a tone
-// drifting by alpha (relative to its mean frequency) keeps one frequency.
-// Linear interpolation between the neighbouring samples (x[N] = 0), zero
-// outside the series.  The position is formed in FP64 (it needs ~24 bits of
-// integer part plus the fraction): two Newton steps from the FP32 root
-// v = 2 tau / (1 + sqrt(q)), q = 1 + 2 alpha tau in [1/2, 3/2], whose slope
-// 1 + alpha v is sqrt(q), so no FP64 root or division is taken; the first
-// leaves about 1e-14, the second a rounding.  Forming the samples here rather
+// Trials of the time-domain search: y[m] = x at the positions of
+// DriftPositions, by linear interpolation between the neighbouring samples
+// (x[N] = 0), zero outside the series.  Forming the samples here rather
 // than in a pass of their own saves a write and a read of the series, and the
 // instructions hide under the pass's loads and stores (sixteen trials of 2^20
 // samples: 38 us, against 36 us and 28 us in two passes).
@@ -105,16 +100,13 @@ struct ResampledSeries {
     int n;
     double zmax, dz;
     int nz, iz0;
-    double h, inv_n;  // alpha / 2, 1 / N
+    DriftPositions pos;
     __device__ __forceinline__ void select(int b, int64_t) {
         // -alpha_max + d iz with two roundings, as the trials are defined
 #pragma clang fp contract(off)
         const double alpha = nz == 1 ? 0.0 : -zmax + dz * double(iz0 + b);
-        h = 0.5 * alpha;
-        inv_n = 1.0 / double(n);  // exact: n is a power of two
-    }
-    __device__ __forceinline__ double newton(double v, double inv, double tau) const {
-        return fma(tau - v * fma(h, v, 1.0), inv, v);
+        pos.h = 0.5 * alpha;
+        pos.inv_n = 1.0 / double(n);  // exact: n is a power of two
     }
     __device__ __forceinline__ float sample(double v) const {
         const double nd = double(n);
@@ -136,15 +128,8 @@ struct ResampledSeries {
         return __int_as_float(__float_as_int(float(a * (1.0 - f) + b * f)) & keep);
     }
     __device__ __forceinline__ float2 operator()(int64_t i) const {
-        const double tau0 = fma(double(int(2 * i)), inv_n, -0.5), tau1 = tau0 + inv_n;  // exact
-        const float tf = float(tau0);
-        const float q = fmaf(4.f * float(h), tf, 1.f);
-        const float r = __builtin_amdgcn_rsqf(q);
-        const double inv = double(r);
-        double v = double(2.f * tf * __builtin_amdgcn_rcpf(fmaf(q, r, 1.f)));
-        v = newton(newton(v, inv, tau0), inv, tau0);
-        double w = fma(inv_n, inv, v);
-        w = newton(newton(w, inv, tau1), inv, tau1);
+        double v, w;
+        pos.pair(i, v, w);
         return make_float2(sample(v), sample(w));
     }
 };
@@ -1600,7 +1585,7 @@ hipError_t launch_r2c_packed(const float *x, int64_t nsamp, float2 *Z, float2 *w
 hipError_t launch_r2c_resampled(const float *x, int64_t nsamp, double zmax, double dz, int nz, int iz0, int count,
                                 float2 *Z, float2 *work, hipStream_t st) {
     if (nsamp < 2 || nsamp > (int64_t(1) << 26) || count < 1 || count > 65535) return hipErrorInvalidValue;
-    return launch_r2c(ResampledSeries{x, int(nsamp), zmax, dz, nz, iz0, 0.0, 0.0}, nsamp, Z, work, st, count);
+    return launch_r2c(ResampledSeries{x, int(nsamp), zmax, dz, nz, iz0, {0.0, 0.0}}, nsamp, Z, work, st, count);
 }
 
 hipError_t launch_unpack_median(const float2 *Z, int64_t nsamp, float2 *X, double *med, int W, hipStream_t st,
