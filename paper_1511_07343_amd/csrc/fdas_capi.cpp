@@ -256,9 +256,8 @@ fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &
         e = launch_segfft(X, med, p->W, g.nb, p->log2s, p->h, g.nseg, ws.seg, dcount, st);
         if (e != hipSuccess) return hip_fail(p, e, "segment DFT");
         if ((e = mark(3)) != hipSuccess) return hip_fail(p, e, "timing event");
-        e = launch_correlate(ws.seg, p->d_bank, p->d_bank_half, p->nz, p->opts.templates_per_block, g.nb, p->log2s, p->h, g.nseg, plane,
-                             ws.codes,
-                             p->code_inv, st);
+        e = launch_correlate(ws.seg, p->d_bank, p->d_bank_half, p->nz, p->opts.templates_per_block, g.nb, p->log2s, p->h,
+                             g.nseg, plane, ws.codes, p->code_inv, p->num_cu, st);
         if (e != hipSuccess) return hip_fail(p, e, "correlate");
     } else {
         const bool bf16 = p->corr == FDAS_CORR_GEMM_BF16;

@@ -1638,11 +1638,12 @@ hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t n
 // 2^17 samples, 101 templates, 2048 points: 2 instead of 13, 20 us against
 // 42; 2^18, 51, 8192: 2 instead of 7, 23 against 45; 2^20, 201, 2048: 6, 171
 // against 174; 2^22, 201, 2048 would take 7: 636 against 617 with 13.
-static int auto_tpb(int log2s, int nz, int64_t nseg) {
+static int auto_tpb(int log2s, int nz, int64_t nseg, int num_cu) {
     int64_t nzb = (int64_t(nz) + 12) / 13;
     nzb = ((nzb + 7) / 8) * 8;
     const int most = int((nz + nzb - 1) / nzb);
-    const int64_t at_once = 256 * (log2s >= 13 ? 2 : log2s == 12 ? 4 : log2s == 11 ? 8 : 16);
+    // workgroups that run at once: four SIMDs a compute unit, of corr_waves each
+    const int64_t at_once = int64_t(num_cu) * (4 * corr_waves(log2s)) / std::max(1, corr_threads(log2s) / 64);
     if (nseg * nz >= 32 * at_once) return most;
     int best = most;
     double least = INFINITY;
@@ -1659,10 +1660,10 @@ static int auto_tpb(int log2s, int nz, int64_t nseg) {
 
 hipError_t launch_correlate(const float2 *segspec, const float2 *bank, const float2 *bank_half, int nz, int tpb,
                             int64_t nb, int log2s, int h, int64_t nseg, float *plane, uint8_t *codes, float code_inv,
-                            hipStream_t st) {
+                            int num_cu, hipStream_t st) {
     if (nseg <= 0 || nz <= 0) return hipSuccess;
-    if (tpb < 0) return hipErrorInvalidValue;
-    if (tpb == 0) tpb = auto_tpb(log2s, nz, nseg);
+    if (tpb < 0 || num_cu < 1) return hipErrorInvalidValue;
+    if (tpb == 0) tpb = auto_tpb(log2s, nz, nseg, num_cu);
     const int64_t nzb = (nz + tpb - 1) / tpb;
     const int64_t total = nzb * nseg;
     const int64_t per = (total + kXcds - 1) / kXcds;

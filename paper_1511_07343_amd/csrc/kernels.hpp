@@ -58,10 +58,11 @@ hipError_t launch_normalise(const float2 *X, const double *med, int W, int64_t n
 // floats, the bins k from bank in [0, nb) and the points k + 1/2 from
 // bank_half in [nb, 2 nb), and the nz x nb codes cover the pairs
 // (k, k + 1/2): codes[iz][k] = max of the two points' codes.
-// tpb: templates per workgroup, 0 to have it chosen for the launch.
+// tpb: templates per workgroup, 0 to have it chosen for the launch and the
+// num_cu compute units.
 hipError_t launch_correlate(const float2 *segspec, const float2 *bank, const float2 *bank_half, int nz, int tpb,
                             int64_t nb, int log2s, int h, int64_t nseg, float *plane, uint8_t *codes, float code_inv,
-                            hipStream_t st);
+                            int num_cu, hipStream_t st);
 
 // Matrix-core correlator (BF16 or FP16 operands, FP32 accumulation).
 // gemm_ksteps(h): K steps of 16 taps (2h + 1, zero padded); at most
