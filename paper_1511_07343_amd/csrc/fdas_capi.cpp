@@ -15,7 +15,6 @@
 #include <cstring>
 #include <new>
 #include <string>
-#include <thread>
 
 namespace fdas {
 
@@ -176,7 +175,6 @@ static bool foresees_long_list(const fdas_plan_s *p, const Workspace &ws, hipEve
                 const uint32_t cells = __atomic_load_n(ws.h_count + kCellsWord, __ATOMIC_RELAXED);
                 if (cells != kCellsUnknown) return cells > line;
             }
-            std::this_thread::yield();  // to the caller's other threads, if any wait for a processor
         } while (clock::now() < look);
         if (hipEventQuery(enqueued) != hipErrorNotReady) return false;  // done, or an error that the wait reports
     }
