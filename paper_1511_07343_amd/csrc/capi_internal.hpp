@@ -87,7 +87,6 @@ struct fdas_plan_s {
     std::array<fdas::Workspace, 3> ws{};
     std::array<hipStream_t, 2> aux{};
     std::array<hipEvent_t, 4> events{};
-    hipEvent_t enqueued = nullptr;  // behind a search's kernels, long lists' apart
     // batched path: captured per-trial launch sequence, per slot and length
     std::array<std::map<int64_t, hipGraphExec_t>, 2> graphs{};
     // persistent batch launch (one launch per up to 64 trials)

@@ -156,27 +156,24 @@ fdas_status finish_rest(fdas_plan_s *p, const Workspace &ws, int64_t nsamp, cons
     return e == hipSuccess ? FDAS_OK : hip_fail(p, e, "candidate sort");
 }
 
-// Whether the search in front of `enqueued` is likely to leave a long list:
-// waits until the screen has counted the cells it passes on, while the exact
-// sums and the neighbour test have yet to run, so that the long lists' kernels
-// can be enqueued behind them.  A wrong answer costs time, not records: the
-// kernels return at once for a short list (16 us), and a long one not foreseen
-// is finished after the wait for the counters (20 us).  The line lies at the
-// fewest cells seen to a record: 8.7 in planes of pulsars (938226 cells, 107103
-// records; 84108 and 7611), two with a single template; noise alone passes
-// more (8318 cells and 2 records in 2^22 columns x 201 templates).
-static bool foresees_long_list(const fdas_plan_s *p, const Workspace &ws, hipEvent_t enqueued) {
-    const uint32_t line = kFinishSmall * 2 * uint32_t(std::min(p->nz, 4));
+// Whether the search enqueued on st is likely to leave a long list: waits until
+// the screen has counted the cells it passes on, while the exact sums and the
+// neighbour test have yet to run, so that the long lists' kernels can be
+// enqueued behind them.  A wrong answer costs time, not records: the kernels
+// return at once for a short list, and a long one not foreseen is finished
+// after the wait for the counters.  (A cell is seldom a record: 2^18 columns x
+// 21 templates, 83160 cells and 7582 records; 762078 and 10413.)
+static bool foresees_long_list(const Workspace &ws, hipStream_t st) {
     using clock = std::chrono::steady_clock;
     for (;;) {
         const auto look = clock::now() + std::chrono::milliseconds(1);
         do {
             for (int i = 0; i < 100; ++i) {
                 const uint32_t cells = __atomic_load_n(ws.h_count + kCellsWord, __ATOMIC_RELAXED);
-                if (cells != kCellsUnknown) return cells > line;
+                if (cells != kCellsUnknown) return cells > 2 * kFinishSmall;
             }
         } while (clock::now() < look);
-        if (hipEventQuery(enqueued) != hipErrorNotReady) return false;  // done, or an error that the wait reports
+        if (hipStreamQuery(st) != hipErrorNotReady) return false;  // done, or an error that the wait reports
     }
 }
 
@@ -813,7 +810,6 @@ void fdas_plan_destroy(fdas_plan_t *plan) {
         if (ev) (void)hipEventDestroy(ev);
         ev = nullptr;
     }
-    if (plan->enqueued) (void)hipEventDestroy(plan->enqueued);
     for (auto &m : plan->graphs)
         for (auto &kv : m) (void)hipGraphExecDestroy(kv.second);
     destroy_pbatch(plan->pbatch);
@@ -869,10 +865,6 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
         (void)hipGetLastError();  // a pageable destination is not an error
     }
     __atomic_store_n(ws.h_count + kCellsWord, kCellsUnknown, __ATOMIC_RELAXED);
-    if (!plan->enqueued) {
-        const hipError_t e = hipEventCreateWithFlags(&plan->enqueued, hipEventDisableTiming);
-        if (e != hipSuccess) return hip_fail(plan, e, "event create");
-    }
     fdas_status s = enqueue_search(plan, ws, g, in_kind, in_dev, plane, ws.cands, ws.count, st, timed, &X, &med,
                                    use_direct ? &direct : nullptr);
     if (s != FDAS_OK) return s;
@@ -883,17 +875,12 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
     if (use_direct) {
         const DirectOut *rest_out = staged ? nullptr : &direct;
         bool all = finishes_all(plan, timed);
-        // The marker that the wait needs goes into the stream now, as
-        // hipStreamSynchronize would have put it there: behind the look at the
-        // cells it would be late by its own 10 us.
-        hipError_t e = all ? hipSuccess : hipEventRecord(plan->enqueued, st);
-        if (e != hipSuccess) return hip_fail(plan, e, "event record");
-        if (!all && foresees_long_list(plan, ws, plan->enqueued)) {
+        if (!all && foresees_long_list(ws, st)) {
             s = finish_rest(plan, ws, plan->nsamp, rest_out, st);
             if (s != FDAS_OK) return s;
             all = true;
         }
-        e = all ? hipStreamSynchronize(st) : hipEventSynchronize(plan->enqueued);
+        hipError_t e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
             s = hip_fail(plan, e, "search");
         } else if (long_list(plan, ws) && (staged || !all)) {
