@@ -45,7 +45,7 @@ struct Workspace {
     void *sort = nullptr;         // radix-sort scratch
     fdas_cand *final = nullptr;   // sorted public records
     // Page-locked: the host copy of the counters (the finishing kernel writes
-    // it; word kCellsWord the exact sums' kernel), then kFinishSmall records, where a search whose caller's buffer is
+    // it), then kFinishSmall records, where a search whose caller's buffer is
     // ordinary memory has its records written; and their device aliases.
     uint32_t *h_count = nullptr, *d_h_count = nullptr;
     fdas_cand *h_final = nullptr, *d_h_final = nullptr;
@@ -136,8 +136,7 @@ void destroy_workspace(Workspace &ws);
 // direct (may be NULL; plans without refinement only), at most direct->cap of
 // them to direct->out (a device alias of page-locked host memory).  Unless
 // finishes_all(p, timed), a list of more than kFinishSmall records is left
-// unfinished; finish_rest does it, enqueued behind the search where a long
-// list is foreseen, else once the counters are on the host.
+// unfinished: once the counters are on the host, finish_rest does it.
 struct DirectOut {
     fdas_cand *out;
     uint32_t cap;
@@ -153,7 +152,6 @@ inline bool long_list(const fdas_plan_s *p, const Workspace &ws) {
     return std::min(ws.h_count[0], p->cand_cap) > kFinishSmall;
 }
 fdas_status finish_rest(fdas_plan_s *p, const Workspace &ws, int64_t nsamp, const DirectOut *direct, hipStream_t st);
-constexpr int kCellsWord = 8;  // of Workspace::h_count
 FinishArgs finish_args(const fdas_plan_s *p, const DevCand *dc, const uint32_t *count, int64_t ncol);
 // Trial value of plane row iz: the drift z(iz) of a template plan, the
 // acceleration trial alpha_iz of a time-domain plan.

@@ -10,7 +10,6 @@
 #include "capi_internal.hpp"
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -156,27 +155,6 @@ fdas_status finish_rest(fdas_plan_s *p, const Workspace &ws, int64_t nsamp, cons
     return e == hipSuccess ? FDAS_OK : hip_fail(p, e, "candidate sort");
 }
 
-// Whether the search enqueued on st is likely to leave a long list: waits until
-// the screen has counted the cells it passes on, while the exact sums and the
-// neighbour test have yet to run, so that the long lists' kernels can be
-// enqueued behind them.  A wrong answer costs time, not records: the kernels
-// return at once for a short list, and a long one not foreseen is finished
-// after the wait for the counters.  (A cell is seldom a record: 2^18 columns x
-// 21 templates, 83160 cells and 7582 records; 762078 and 10413.)
-static bool foresees_long_list(const Workspace &ws, hipStream_t st) {
-    using clock = std::chrono::steady_clock;
-    for (;;) {
-        const auto look = clock::now() + std::chrono::milliseconds(1);
-        do {
-            for (int i = 0; i < 100; ++i) {
-                const uint32_t cells = __atomic_load_n(ws.h_count + kCellsWord, __ATOMIC_RELAXED);
-                if (cells != kCellsUnknown) return cells > 2 * kFinishSmall;
-            }
-        } while (clock::now() < look);
-        if (hipStreamQuery(st) != hipErrorNotReady) return false;  // done, or an error that the wait reports
-    }
-}
-
 // The time-domain resampling search on `st`: per trial, resample, real DFT,
 // block medians, normalised powers and codes into plane row iz; then the
 // harmonic sums along each row (izc < 0), peaks, candidates and their drift.
@@ -203,7 +181,7 @@ static fdas_status enqueue_td_search(fdas_plan_s *p, const Workspace &ws, const 
     if (e == hipSuccess) e = launch_zero_u32(dcount, 6, st);
     if (e == hipSuccess)
         e = launch_harmsum(plane, ws.codes, p->nz, g.nb, 0, -1, p->opts.nharm_max, p->thr_f, p->code_thr, ws.hits,
-                           p->hit_cap, p->group_cap, dcands, dcount, p->cand_cap, ws.d_h_count + kCellsWord, st);
+                           p->hit_cap, p->group_cap, dcands, dcount, p->cand_cap, st);
     if (e == hipSuccess) e = enqueue_finish(p, ws, dcands, dcount, g.nb, direct, finishes_all(p, timed), st);
     for (int i = 5; i <= FDAS_NSTAGES && e == hipSuccess; ++i) e = mark(i);
     if (e != hipSuccess) return hip_fail(p, e, "time-domain harmonic sums");
@@ -266,7 +244,7 @@ fdas_status enqueue_search(fdas_plan_s *p, const Workspace &ws, const Geometry &
     }
     if ((e = mark(4)) != hipSuccess) return hip_fail(p, e, "timing event");
     e = launch_harmsum(plane, ws.codes, p->nz, g.ncol, p->opts.interbin ? g.nb : 0, p->izc, p->opts.nharm_max, p->thr_f, p->code_thr, ws.hits,
-                       p->hit_cap, p->group_cap, dcands, dcount, p->cand_cap, ws.d_h_count + kCellsWord, st);
+                       p->hit_cap, p->group_cap, dcands, dcount, p->cand_cap, st);
     if (e != hipSuccess) return hip_fail(p, e, "harmonic sum");
     if (direct && p->opts.refine_levels > 0) {
         set_error("records written to the host directly need a plan without refinement");
@@ -864,7 +842,6 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
         }
         (void)hipGetLastError();  // a pageable destination is not an error
     }
-    __atomic_store_n(ws.h_count + kCellsWord, kCellsUnknown, __ATOMIC_RELAXED);
     fdas_status s = enqueue_search(plan, ws, g, in_kind, in_dev, plane, ws.cands, ws.count, st, timed, &X, &med,
                                    use_direct ? &direct : nullptr);
     if (s != FDAS_OK) return s;
@@ -873,18 +850,11 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
     plan->last_nb = g.nb;
     plan->searched = true;
     if (use_direct) {
-        const DirectOut *rest_out = staged ? nullptr : &direct;
-        bool all = finishes_all(plan, timed);
-        if (!all && foresees_long_list(ws, st)) {
-            s = finish_rest(plan, ws, plan->nsamp, rest_out, st);
-            if (s != FDAS_OK) return s;
-            all = true;
-        }
         hipError_t e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
             s = hip_fail(plan, e, "search");
-        } else if (long_list(plan, ws) && (staged || !all)) {
-            if (!all) s = finish_rest(plan, ws, plan->nsamp, rest_out, st);
+        } else if (long_list(plan, ws) && !finishes_all(plan, timed)) {
+            s = finish_rest(plan, ws, plan->nsamp, staged ? nullptr : &direct, st);
             if (s == FDAS_OK && staged) {
                 s = copy_candidates(plan, ws, cands_host, cap, ncands, st);
             } else if (s == FDAS_OK) {

@@ -1121,10 +1121,7 @@ template <int LEVELS>
 __global__ __launch_bounds__(256) void k_exact(const float *__restrict__ P, int nz, int64_t nb, int64_t split,
                                                int izc, const uint2 *__restrict__ blocks,
                                                const uint32_t *__restrict__ cnt, uint32_t cell_cap,
-                                               float *__restrict__ sums, uint32_t *__restrict__ cells_dst) {
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        __hip_atomic_store(cells_dst, min(cell_count(cnt), kCellsUnknown - 1u), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
+                                               float *__restrict__ sums) {
     exact_tile<LEVELS>(blockIdx.x, gridDim.x, P, nz, nb, split, izc, blocks, cnt, cell_cap, sums);
 }
 
@@ -1691,8 +1688,7 @@ size_t harmsum_scratch_bytes(int nz, int64_t nb, uint32_t cell_cap, uint32_t gro
 hipError_t launch_harmsum(const float *plane, const uint8_t *codes, int nz, int64_t nb, int64_t split, int izc,
                           int nharm_max,
                           const float *thr_host, const uint32_t *code_thr, void *scratch, uint32_t cell_cap,
-                          uint32_t group_cap, DevCand *cands, uint32_t *count, uint32_t cap,
-                          uint32_t *cells_dst, hipStream_t st) {
+                          uint32_t group_cap, DevCand *cands, uint32_t *count, uint32_t cap, hipStream_t st) {
     int levels = 0;
     while ((1 << levels) < nharm_max) ++levels;
     if ((1 << levels) != nharm_max || levels > 4) return hipErrorInvalidValue;
@@ -1726,7 +1722,7 @@ hipError_t launch_harmsum(const float *plane, const uint8_t *codes, int nz, int6
     hipLaunchKernelGGL((k_screen<LV>), grid1, dim3(64 * SC_WAVES), 0, st, codes, nz, nb, rows, izc, T, groups, blocks, \
                        group_map, count, group_cap, cell_cap);                                                     \
     hipLaunchKernelGGL((k_exact<LV>), dim3(grid2), dim3(256), 0, st, plane, nz, nb, split, izc, blocks, count,      \
-                       cell_cap, sums, cells_dst);                                                                 \
+                       cell_cap, sums);                                                                            \
     hipLaunchKernelGGL((k_peaks<LV>), dim3(grid2), dim3(256), 0, st, nz, nb, thr, groups, group_map, blocks, sums,  \
                        count, group_cap, cell_cap, cands, cap);
     switch (levels) {

@@ -102,16 +102,11 @@ hipError_t launch_corr_gemm(const uint32_t *xl, int64_t nb, int h, const void *b
 // split > 0 marks a half-bin plane stored as two
 // halves per row: column c (in half bins) at c / 2 for even c and at
 // split + c / 2 for odd c.
-// cells_dst: a word in page-locked host memory (device alias) to which the
-// number of cells that the screen passed on is written as soon as it is known
-// (less than kCellsUnknown).
-constexpr uint32_t kCellsUnknown = 0xffffffffu;
 size_t harmsum_scratch_bytes(int nz, int64_t nb, uint32_t cell_cap, uint32_t group_cap);
 hipError_t launch_harmsum(const float *plane, const uint8_t *codes, int nz, int64_t nb, int64_t split, int izc,
                           int nharm_max,
                           const float *thr_host, const uint32_t *code_thr, void *scratch, uint32_t cell_cap,
-                          uint32_t group_cap, DevCand *cands, uint32_t *count, uint32_t cap, uint32_t *cells_dst,
-                          hipStream_t st);
+                          uint32_t group_cap, DevCand *cands, uint32_t *count, uint32_t cap, hipStream_t st);
 
 // min(*count, cap) records from src to dst and count[0..5] to count_dst, both
 // destinations device aliases of page-locked host memory.

@@ -1,4 +1,4 @@
-"""Lists of more than 4096 records, foreseen or not while a search runs: the
+"""Lists around and beyond 4096 records, into every kind of destination: the
 records are those of a timed search, which enqueues every kernel at once."""
 import numpy as np
 import pytest
@@ -16,12 +16,12 @@ def _tones(nb, ntones, k_min, seed, noise=0.0):
     return X
 
 
-@pytest.mark.parametrize("zmax,dz,nharm,ntones,k_min,noise,long_list,many_cells", [
-    (0.0, 1.0, 16, 600, 1 << 14, 0.0, True, False),   # five records for the two cells of a tone: not foreseen
-    (10.0, 1.0, 1, 1000, 8, 0.3, False, True),         # many cells, few of them maxima: foreseen in vain
-    (10.0, 1.0, 4, 3000, 8, 0.3, True, True),
+@pytest.mark.parametrize("zmax,dz,nharm,ntones,k_min,noise,long_list", [
+    (0.0, 1.0, 16, 600, 1 << 14, 0.0, True),   # five records for the two cells of a tone
+    (10.0, 1.0, 1, 1000, 8, 0.3, False),       # many cells, few of them maxima
+    (10.0, 1.0, 4, 3000, 8, 0.3, True),
 ])
-def test_lists_foreseen_or_not(gpu_lib, zmax, dz, nharm, ntones, k_min, noise, long_list, many_cells):
+def test_list_destinations(gpu_lib, zmax, dz, nharm, ntones, k_min, noise, long_list):
     import torch
     nb = 1 << 15
     bank = gpu_lib.make_templates(zmax, dz)
@@ -31,8 +31,7 @@ def test_lists_foreseen_or_not(gpu_lib, zmax, dz, nharm, ntones, k_min, noise, l
     plan.enable_timing(True)
     want, found = plan.search(X, kind=kind)
     plan.enable_timing(False)
-    _, cells, _ = plan.search_counts()
-    assert found == len(want) and (found > SMALL) == long_list and (cells > 2 * SMALL) == many_cells
+    assert found == len(want) and (found > SMALL) == long_list
     key = (np.log2(want["nharm"]).astype(np.int64) * nb + want["k"]) * bank.nz + want["iz"]
     assert np.all(np.diff(key) > 0)
     for _ in range(3):
