@@ -66,39 +66,49 @@ __device__ __forceinline__ fdas_cand public_record(const DevCand &c, const Finis
     return o;
 }
 
-// Lists of at most kFinishSmall records: every workgroup loads all the keys
-// into LDS and ranks FS_RECORDS of the records among them, a quarter of the
-// keys per wave, all lanes reading the same key (no two records share a key,
-// so the ranks are the order); then it writes its records at their ranks.
-// One launch and no pass over memory in between: 130 records take 6 us, where
-// a one-workgroup sort, seven empty radix kernels and the records' kernel
-// took 40.
+// Lists of at most kFinishSmall records: every workgroup takes FS_RECORDS of
+// the records and ranks them among all keys, FS_TILE keys at a time in LDS, a
+// quarter of them per wave, all lanes reading the same key (no two records
+// share a key, so the ranks are the order); then it writes its records at
+// their ranks.  One launch and no pass over memory in between: 130 records
+// take 6 us, where a one-workgroup sort, seven empty radix kernels and the
+// records' kernel took 40.  The work grows with the square of the list; from
+// about 9000 records on the radix sort's launches and the host's wait for the
+// counters in front of them are less (a search with 5000 records 65 us against
+// 82 with the sort, 10000 records 91 against 86).
 constexpr int FS_RECORDS = 64;
 constexpr int FS_THREADS = 256;
+constexpr int FS_TILE = 4096;
 
 __global__ __launch_bounds__(FS_THREADS) void k_finish_small(FinishArgs a) {
-    __shared__ __align__(16) uint64_t key[kFinishSmall];
+    __shared__ __align__(16) uint64_t key[FS_TILE];
     __shared__ uint32_t less[FS_THREADS / 64][FS_RECORDS];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     if (a.count_dst && blockIdx.x == 0 && t < 6) a.count_dst[t] = a.count[t];
     const uint32_t n = clamp_count(a.count, a.cap), first = blockIdx.x * FS_RECORDS;
     if (n > kFinishSmall || first >= n) return;
-    const uint32_t share = (n + 7) / 8 * 2;  // keys per wave, a whole number of pairs
-    for (uint32_t i = t; i < 4 * share; i += FS_THREADS) key[i] = i < n ? cand_key(a.dc[i], a.nb, a.nz) : ~uint64_t(0);
-    __syncthreads();
     const uint32_t r = first + lane;
-    const uint64_t mine = key[min(r, n - 1)];
+    const DevCand c = a.dc[min(r, n - 1)];
+    const uint64_t mine = cand_key(c, a.nb, a.nz);
     uint32_t below = 0;
+    for (uint32_t at = 0; at < n; at += FS_TILE) {
+        const uint32_t m = min(n - at, uint32_t(FS_TILE));
+        const uint32_t share = (m + 7) / 8 * 2;  // keys per wave, a whole number of pairs
+        if (at > 0) __syncthreads();
+        for (uint32_t i = t; i < 4 * share; i += FS_THREADS)
+            key[i] = i < m ? cand_key(a.dc[at + i], a.nb, a.nz) : ~uint64_t(0);
+        __syncthreads();
 #pragma unroll 4
-    for (uint32_t i = w * share; i < (w + 1) * share; i += 2) {
-        const ulonglong2 k2 = *reinterpret_cast<const ulonglong2 *>(key + i);
-        below += (k2.x < mine ? 1u : 0u) + (k2.y < mine ? 1u : 0u);
+        for (uint32_t i = w * share; i < (w + 1) * share; i += 2) {
+            const ulonglong2 k2 = *reinterpret_cast<const ulonglong2 *>(key + i);
+            below += (k2.x < mine ? 1u : 0u) + (k2.y < mine ? 1u : 0u);
+        }
     }
     less[w][lane] = below;
     __syncthreads();
     if (w != 0 || r >= n) return;
     const uint32_t rank = less[0][lane] + less[1][lane] + less[2][lane] + less[3][lane];
-    if (rank < a.out_cap) a.out[rank] = public_record(a.dc[r], a);
+    if (rank < a.out_cap) a.out[rank] = public_record(c, a);
 }
 
 // The radix sort of longer lists.  One workgroup per block range (RS_BLOCKS of

@@ -29,6 +29,12 @@ struct Geometry {
 };
 
 // Device buffers for one series in flight (sized for `nsamp`).
+// Lists of at most this many records reach a buffer in ordinary memory through
+// the workspace's page-locked one (1.3 MB): the host copies them out, where the
+// runtime would copy them from the device in pieces, with waits of its own
+// (10000 records 214 us a search against 262).
+constexpr uint32_t kStaged = 32768;
+
 struct Workspace {
     int64_t nsamp = 0;
     float2 *Z = nullptr;     // complex DFT of the packed series, M = nsamp/2
@@ -45,7 +51,7 @@ struct Workspace {
     void *sort = nullptr;         // radix-sort scratch
     fdas_cand *final = nullptr;   // sorted public records
     // Page-locked: the host copy of the counters (the finishing kernel writes
-    // it), then kFinishSmall records, where a search whose caller's buffer is
+    // it), then kStaged records, where a search whose caller's buffer is
     // ordinary memory has its records written; and their device aliases.
     uint32_t *h_count = nullptr, *d_h_count = nullptr;
     fdas_cand *h_final = nullptr, *d_h_final = nullptr;

@@ -380,7 +380,7 @@ static fdas_status try_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp, i
     FDAS_ALLOC(ws.hits, harmsum_scratch_bytes(p->nz, g.ncol, p->hit_cap, p->group_cap));
     FDAS_ALLOC(ws.final, int64_t(p->cand_cap) * int64_t(sizeof(fdas_cand)));
 #undef FDAS_ALLOC
-    e = hipHostMalloc(reinterpret_cast<void **>(&ws.h_count), 64 + kFinishSmall * sizeof(fdas_cand), hipHostMallocDefault);
+    e = hipHostMalloc(reinterpret_cast<void **>(&ws.h_count), 64 + kStaged * sizeof(fdas_cand), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&ws.d_h_count), ws.h_count, 0);
     ws.h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.h_count) + 64);
     ws.d_h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.d_h_count) + 64);
@@ -837,7 +837,7 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
             direct = DirectOut{static_cast<fdas_cand *>(dev_out), uint32_t(std::min<int64_t>(cap, plan->cand_cap))};
             use_direct = true;
         } else if (!finishes_all(plan, timed)) {
-            direct = DirectOut{ws.d_h_final, kFinishSmall};
+            direct = DirectOut{ws.d_h_final, kStaged};
             use_direct = staged = true;
         }
         (void)hipGetLastError();  // a pageable destination is not an error
@@ -851,18 +851,19 @@ fdas_status fdas_search(fdas_plan_t *plan, int32_t in_kind, const void *in_dev, 
     plan->searched = true;
     if (use_direct) {
         hipError_t e = hipStreamSynchronize(st);
-        if (e != hipSuccess) {
-            s = hip_fail(plan, e, "search");
-        } else if (long_list(plan, ws) && !finishes_all(plan, timed)) {
-            s = finish_rest(plan, ws, plan->nsamp, staged ? nullptr : &direct, st);
-            if (s == FDAS_OK && staged) {
-                s = copy_candidates(plan, ws, cands_host, cap, ncands, st);
-            } else if (s == FDAS_OK) {
-                e = hipStreamSynchronize(st);
-                s = e != hipSuccess ? hip_fail(plan, e, "search") : count_status(plan, ws, cap, ncands);
-            }
+        if (e != hipSuccess) return hip_fail(plan, e, "search");
+        const uint32_t list = std::min(ws.h_count[0], plan->cand_cap);
+        if (staged && list > kStaged) {  // through the runtime's copy
+            s = finish_rest(plan, ws, plan->nsamp, nullptr, st);
+            if (s == FDAS_OK) s = copy_candidates(plan, ws, cands_host, cap, ncands, st);
         } else {
-            const int64_t n = std::min<int64_t>(std::min<int64_t>(ws.h_count[0], plan->cand_cap), cap);
+            if (long_list(plan, ws) && !finishes_all(plan, timed)) {
+                s = finish_rest(plan, ws, plan->nsamp, &direct, st);
+                if (s != FDAS_OK) return s;
+                e = hipStreamSynchronize(st);
+                if (e != hipSuccess) return hip_fail(plan, e, "search");
+            }
+            const int64_t n = std::min<int64_t>(list, cap);
             if (staged && n > 0) std::memcpy(cands_host, ws.h_final, size_t(n) * sizeof(fdas_cand));
             s = count_status(plan, ws, cap, ncands);
         }

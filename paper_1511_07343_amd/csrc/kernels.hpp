@@ -136,7 +136,7 @@ struct FinishArgs {
 // Lists of at most this many records are finished by launch_finish_small;
 // launch_finish_large does the longer ones, and nothing for the others.
 // scratch: cand_sort_scratch_bytes(cap) bytes.
-constexpr uint32_t kFinishSmall = 4096;
+constexpr uint32_t kFinishSmall = 8192;
 size_t cand_sort_scratch_bytes(uint32_t cap);
 hipError_t launch_finish_small(const FinishArgs &a, hipStream_t st);
 hipError_t launch_finish_large(const FinishArgs &a, void *scratch, hipStream_t st);

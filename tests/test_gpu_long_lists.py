@@ -68,3 +68,31 @@ def test_batch_of_long_and_short_lists(gpu_lib, order):
             assert all(np.array_equal(g, w) for g, w in zip(got, want))
     plan.close()
     bank.close()
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 8191, 8192, 8193, 12289, 32767, 32768, 32769, 40000])
+def test_lengths_where_the_form_changes(gpu_lib, n):
+    """8192 records: one kernel below, a sort above; 32768: the last that reach
+    ordinary memory through the plan's page-locked records."""
+    import torch
+    nb = 1 << 19
+    bank = gpu_lib.make_templates(0.0, 1.0)
+    plan = gpu_lib.Plan(bank, 2 * nb, 256, nharm_max=1, sigma=6.0, cand_capacity=1 << 16)
+    X = _tones(nb, n, 8, n)
+    k = np.flatnonzero(X)
+    X, kind = torch.from_numpy(X).cuda(), gpu_lib.IN_SPECTRUM_NORMALISED
+    plan.enable_timing(True)
+    want, found = plan.search(X, kind=kind)
+    plan.enable_timing(False)
+    assert found == n and np.array_equal(want["k"], k)
+    pageable, found = plan.search(X, kind=kind)
+    assert found == n and np.array_equal(pageable, want)
+    pinned, found = plan.search(X, kind=kind, out=gpu_lib.pinned_candidates(n))
+    assert found == n and np.array_equal(pinned, want)
+    for cap in (1, n // 2, n - 1):
+        short, found = plan.search(X, kind=kind, cap=cap, allow_overflow=True)
+        assert found == n and np.array_equal(short, want[:cap])
+        short, found = plan.search(X, kind=kind, out=gpu_lib.pinned_candidates(cap), allow_overflow=True)
+        assert found == n and np.array_equal(short, want[:cap])
+    plan.close()
+    bank.close()
