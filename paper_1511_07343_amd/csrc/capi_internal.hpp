@@ -51,8 +51,9 @@ struct Workspace {
     void *sort = nullptr;         // radix-sort scratch
     fdas_cand *final = nullptr;   // sorted public records
     // Page-locked: the host copy of the counters (the finishing kernel writes
-    // it), then kStaged records, where a search whose caller's buffer is
-    // ordinary memory has its records written; and their device aliases.
+    // it), then, in the plan's own, kStaged records, where a search whose
+    // caller's buffer is ordinary memory has its records written; and their
+    // device aliases.
     uint32_t *h_count = nullptr, *d_h_count = nullptr;
     fdas_cand *h_final = nullptr, *d_h_final = nullptr;
     float *series = nullptr;      // graph input: the trial is copied here first (batched path)

@@ -380,10 +380,14 @@ static fdas_status try_workspace(fdas_plan_s *p, Workspace &ws, int64_t nsamp, i
     FDAS_ALLOC(ws.hits, harmsum_scratch_bytes(p->nz, g.ncol, p->hit_cap, p->group_cap));
     FDAS_ALLOC(ws.final, int64_t(p->cand_cap) * int64_t(sizeof(fdas_cand)));
 #undef FDAS_ALLOC
-    e = hipHostMalloc(reinterpret_cast<void **>(&ws.h_count), 64 + kStaged * sizeof(fdas_cand), hipHostMallocDefault);
+    const bool staged = &ws == &p->ws[0];  // fdas_search's; batches and servers copy from the device
+    e = hipHostMalloc(reinterpret_cast<void **>(&ws.h_count), 64 + (staged ? kStaged * sizeof(fdas_cand) : 0),
+                      hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&ws.d_h_count), ws.h_count, 0);
-    ws.h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.h_count) + 64);
-    ws.d_h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.d_h_count) + 64);
+    if (staged) {
+        ws.h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.h_count) + 64);
+        ws.d_h_final = reinterpret_cast<fdas_cand *>(reinterpret_cast<char *>(ws.d_h_count) + 64);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_workspace(ws);
