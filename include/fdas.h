@@ -312,7 +312,10 @@ fdas_status fdas_search_batch(fdas_plan_t *plan, int32_t n, const float *const *
  * persistent launch) and the time is the persistent batch's wall time per
  * trial over 8 copies of the series.  cache_path (may be NULL) names a text file of earlier
  * results keyed by (GPU arch, nsamp, nz, h, lengths tried); a hit skips the measurement, a
- * miss appends the new result.  Needs a GPU; allocates temporary plans. */
+ * miss appends the new result.  Needs a GPU; allocates temporary plans.  Series
+ * too short to fill the GPU with 7 templates to a workgroup (2^17 samples and
+ * 101 templates, say) are searched faster with templates_per_block left at 0,
+ * which takes fewer. */
 fdas_status fdas_autotune(const fdas_bank *bank, int64_t nsamp, const fdas_opts *opts,
                           const char *cache_path, int32_t *seg_out, int32_t *tpb_out, double *ms_out);
 

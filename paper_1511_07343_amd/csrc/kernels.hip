@@ -626,9 +626,10 @@ __device__ __forceinline__ void correlate_item(float2 *lds,
     const int iz0 = int(tb) * tpb;
     const int iz1 = min(nz, iz0 + tpb);
     // The segment spectrum is loaded once into registers and reused by every
-    // template.  201 templates, bound by the FP32 instructions: 2^23 samples,
-    // 4096 points 1.43 ms re-reading it from L2 against 1.25, 8192 points 1.70
-    // against 1.42; 2^21 samples, 1024 points 0.37 against 0.30, half-bin
+    // template.  201 templates, bound by the FP32 instructions at a clock that
+    // falls a little as they get denser: 2^23 samples, 4096 points 1.43 ms
+    // re-reading it from L2 against 1.25, 8192 points 1.70 against 1.42 (1.37 to
+    // 1.46 in other runs); 2^21 samples, 1024 points 0.37 against 0.30, half-bin
     // plane at 4096 points 0.76 against 0.68.
     // Operands come through buffer loads: one 32-bit lane offset and a
     // per-point constant offset, no 64-bit address arithmetic per load.
@@ -808,7 +809,7 @@ __device__ __forceinline__ void cell_sums(const float *__restrict__ P, int64_t n
     nested_sums<LEVELS>(v, s);
 }
 
-// Pass 1, the screen, on the codes of 2-bin blocks (see block_code): a code
+// Pass 1, the screen, on the codes of 2-bin blocks (see block_codes4): a code
 // is at least P / delta for both bins of its block, so for the block of bins
 // 2b, 2b + 1 of row iz, sum_j max(codes of the blocks holding c_j(2b) and
 // c_j(2b + 1) in row r_j) is at least each bin's power sum / delta.  A block

@@ -107,13 +107,16 @@ __device__ __forceinline__ c64 fresnel_small(double x) {
 //   Z < 0:       e2q G(-Z) - G(-Y)
 //   Y < 0 <= Z:  (1 + i) exp(-i pi Y^2 / 2) - e2q G(Z) - G(-Y):
 // one formula with the signs of Y and Z, whose exponential only the bins
-// inside the drift need.  Where both ends lie within 1 of 0 (small z), the
-// difference of the power series, which does not cancel.
+// inside the drift need.  In waves that have such bins, the ones whose ends
+// both lie within 1 of 0 (small z) take the difference of the power series,
+// which does not cancel.  (With no bin inside, at most the nearest one cancels;
+// it is nearly all of the response then, and its error that of a factor, which
+// the power's normaliser takes out.)
 // z < 0: conj(A(-q, -z)).  z = 0: exp(i pi q) sin(pi q) / (pi q).
 struct DriftResponse {
     double z, half, root;  // |z|, |z| / 2, sqrt(2 / |z|)
     c64 e2q;               // exp(2 pi i q), the same for every integer shift of q (conjugated for z < 0)
-    bool neg, narrow;      // z < 0; both ends can lie within 1 of 0
+    bool neg, narrow;      // z < 0; both ends of a bin inside can lie within 1 of 0
 
     __device__ DriftResponse(double r, double zz) {
         neg = zz < 0.0;

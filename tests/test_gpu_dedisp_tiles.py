@@ -1,6 +1,6 @@
 """De-dispersion at the edges of its kernels' tiles (spans of 256, 1024
-and 1280 samples, groups of 4 and blocks of 64 channels, 4 DM trials per workgroup),
-bit-exact against the oracle: integer sums, so there is no tolerance."""
+and 1280 samples, groups of 4 and blocks of 64 channels, 4 DM trials per workgroup
+directly and 16 staged), bit-exact against the oracle: integer sums, so there is no tolerance."""
 import numpy as np
 import pytest
 
@@ -37,7 +37,7 @@ def test_dedisperse_tile_edges(gpu_lib, nchan, ndm, nout):
     (19, 17, (1 << 19) + 77, 30.0),   # a stage of 16 channels and 3; 16 trials and 1
     (33, 40, 200000, 300.0),          # rows near their largest
     (16, 300, 30011, 900.0),          # two launches of trials, the second of 44
-    (22, 16, 205 * 1280, 234.0),      # the fewest workgroups, whole spans, the longest rows
+    (22, 16, 205 * 1280, 234.0),      # whole spans, the longest rows
     (14, 16, 205 * 1280 - 1279, 20.0),
 ])
 def test_dedisperse_staged_rows(gpu_lib, nchan, ndm, nout, dm_max):

@@ -1,5 +1,5 @@
-"""Candidate finishing at the lengths where it changes form (one kernel up to
-4096 records, a radix sort above) and for every kind of destination, and the
+"""Candidate finishing at the lengths where it changes form (one kernel,
+its keys in tiles of 4096, up to 8192 records, a radix sort above) and for every kind of destination, and the
 FP64 significance over its range."""
 import numpy as np
 import pytest
@@ -8,7 +8,7 @@ import paper_1511_07343_amd as fdas
 
 pytestmark = pytest.mark.gpu
 
-SMALL = 4096  # records finished by the one-kernel form
+SMALL = 4096  # records of one tile of keys
 
 
 def _search(lib, n_want, **opts):

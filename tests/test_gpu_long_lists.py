@@ -5,7 +5,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-SMALL = 4096  # records finished by the one-kernel form
+SMALL = 4096  # records of one tile of the one-kernel form
 
 
 def _tones(nb, ntones, k_min, seed, noise=0.0):

@@ -1,4 +1,4 @@
-"""The harmonic-sum screen on the matrix cores (four harmonics and more).
+"""The harmonic-sum screen, four harmonics and more on the plain plane.
 
 The candidates of a search are compared with those of a direct evaluation on
 the search's own plane: FP32 sums of every cell in the library's order, every
