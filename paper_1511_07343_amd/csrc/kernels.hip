@@ -962,7 +962,7 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
                                             uint32_t *__restrict__ group_map, uint32_t *__restrict__ cnt,
                                             uint32_t group_cap, uint32_t cell_cap) {
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // a workgroup covers SC_WAVES * 2048 columns
     const int64_t m = (bx * SC_WAVES + wave) * 64 + lane;  // column group
     const int iz0 = by * tile_rows, rows = min(tile_rows, nz - iz0);
@@ -1069,8 +1069,10 @@ __device__ __forceinline__ void screen_tile(uint32_t *rowmask_lds, int64_t bx, i
     }
 }
 
+// Four waves per SIMD: 16 harmonics need 129 registers unasked and 128 without
+// a spill, and 8 % more cycles at three waves.
 template <int LEVELS>
-__global__ __launch_bounds__(64 * SC_WAVES, 3) void k_screen(const uint8_t *__restrict__ Q, int nz, int64_t nb,
+__global__ __launch_bounds__(64 * SC_WAVES, 4) void k_screen(const uint8_t *__restrict__ Q, int nz, int64_t nb,
                                                           int tile_rows, int izc, ScreenThr T, Group *__restrict__ groups,
                                                           uint2 *__restrict__ blocks, uint32_t *__restrict__ group_map,
                                                           uint32_t *__restrict__ cnt, uint32_t group_cap,
