@@ -45,6 +45,14 @@ __device__ __forceinline__ uint64_t cand_key(const DevCand &c, int64_t nb, int n
     return (level * uint64_t(nb) + uint64_t(uint32_t(c.k))) * uint64_t(nz) + uint64_t(uint32_t(c.iz));
 }
 
+// The drift (or acceleration) of plane row iz with two roundings, as the
+// templates and trials are formed: a fused multiply-add would round once and
+// can differ in the last bit.
+__device__ __forceinline__ double row_value(const FinishArgs &a, int iz) {
+#pragma clang fp contract(off)
+    return a.td && a.nz == 1 ? 0.0 : -a.zmax + a.dz * double(iz);
+}
+
 // The public record of c.
 __device__ __forceinline__ fdas_cand public_record(const DevCand &c, const FinishArgs &a) {
     fdas_cand o;
@@ -53,13 +61,9 @@ __device__ __forceinline__ fdas_cand public_record(const DevCand &c, const Finis
     o.nharm = c.nharm;
     o.r = double(c.k) / (double(c.nharm) * double(a.cpb));
     if (a.td) {
-        // -alpha_max + d iz with two roundings, as the trials are formed (a
-        // fused multiply-add would round once and can differ in the last bit)
-#pragma clang fp contract(off)
-        const double alpha = a.nz == 1 ? 0.0 : -a.zmax + a.dz * double(c.iz);
-        o.z = alpha * o.r;
+        o.z = row_value(a, c.iz) * o.r;
     } else {
-        o.z = (-a.zmax + double(c.iz) * a.dz) / double(c.nharm);
+        o.z = row_value(a, c.iz) / double(c.nharm);
     }
     o.power = c.power;
     o.sigma = float(significance_d(double(c.power), c.nharm));
